@@ -41,6 +41,25 @@ constexpr int kKrowLdsMaxWide = 160 * 1024;
 // (measured: three streams in all gave C20H42 7.83 ms per build against 9.06 on
 // one, (H2O)64 238.6 against 244.2; four were slower on (H2O)64)
 constexpr int kAuxStreams = 2;
+// Work tiles (fk_build_quartets): no tile takes more than kTileShare times the
+// serial work that one of two waves per SIMD would have if the class filled the
+// chip alone, or kMinTileFlops flops of one lane where that is more.  Classes
+// share the chip, three streams at a time, so twice the share balances as well
+// as half of it and digests less often (0.5, 1, 2 and 4 shares: organic molecule
+// of 7 heavy atoms, s to f, 324 functions, 21.9, 19.0, 18.0 and 17.7 ms per
+// build; C20H42 9.0, 8.1, 8.0 and 8.0; (H2O)9 cc-pVDZ-type 3.9, 3.3, 3.3 and
+// 3.7; 19.6, 8.2 and 10.1 with whole tiles).  The least matters for the smallest
+// calls: (H2O)4 / STO-3G takes 0.12 ms with 3000-4000, 0.13 with 6000, 0.20
+// with 12000 and 0.70 with whole tiles.
+constexpr double kTileShare = 2.0, kMinTileFlops = 4000.0;
+// the fixed part of a bra's pass over a round of kets (lists, screen, flushes)
+constexpr double kBraOverheadFlops = 600.0;
+// groups of kets (fk_build_quartets): (H2O)9 cc-pVDZ-type 3.2 ms per build
+// against 4.2 with one group per primitive-pair count.  Lists with longer runs
+// of a count lose by mixing: merged within 0.9 at any length, (H2O)64 took
+// 222.0 ms against 220.3 (223.6 with one group per count).
+constexpr double kGroupFar = 0.6;
+constexpr size_t kGroupLen = 128;
 inline int pair_class(int la, int lb) { return la * (la + 1) / 2 + lb; }
 // Hermite functions of total order up to L
 inline int nherm_host(int L) { return (L + 1) * (L + 2) * (L + 3) / 6; }
@@ -108,10 +127,11 @@ struct fk_ctx {
     std::vector<int> pr_sa, pr_sb, pr_ppoff, pr_npp, pr_cls;
     std::vector<double> pr_AB, pr_G, pp;
     std::vector<int> cls_list[NPC];              // sorted pair indices per class
-    std::vector<std::pair<int, int>> cls_groups[NPC];  // [begin, end) of equal npp
+    std::vector<std::pair<int, int>> cls_groups[NPC];  // [begin, end) of a run of similar npp
     std::vector<int> ket_list_all;               // concatenated class lists
     int ket_off[NPC + 1] = {0};
     std::vector<int> lst_sa, lst_sb;
+    std::vector<int> lst_npp;
     std::vector<double> lst_CD, lst_G, ppT;
     std::vector<FkGroup> groups;
     std::vector<int> cls_group0;                 // first global group of each class
@@ -129,7 +149,7 @@ struct fk_ctx {
     int64_t nq_schwarz = 0;
     int npair_kept = 0;
     // device buffers
-    DevBuf<int> d_sh_bf, d_pr_sa, d_pr_sb, d_pr_ppoff, d_pr_npp, d_ket, d_lst_sa, d_lst_sb;
+    DevBuf<int> d_sh_bf, d_pr_sa, d_pr_sb, d_pr_ppoff, d_pr_npp, d_ket, d_lst_sa, d_lst_sb, d_lst_npp;
     DevBuf<int> d_sh_lend, d_mol_sh0, d_mol_nsh, d_mol_bf0, d_mol_nbf;
     DevBuf<long long> d_mol_base, d_mol_shbase;
     DevBuf<double> d_bf_scale, d_pr_AB, d_pr_G, d_pp, d_rys, d_Ds, d_Dsh, d_X, d_Din, d_Jout, d_Kout;
@@ -492,7 +512,7 @@ void order_for_xcds(fk_ctx *c, const QuartetClass &q)
     };
     auto item_cost = [&](int64_t i) {
         auto tc = [&](const FkTile &t) {
-            return (double)c->blk_nppsum[t.blk] * c->groups[t.grp & ~FK_TILE_SAME].npp * t.ket_count;
+            return (double)c->blk_nppsum[t.blk] * (t.p1 - t.p0) * t.ket_count;
         };
         if (!tasks) return tc(c->tiles[q.tile_off + i]);
         const int2 tk = c->tasks[q.task_off + i];
@@ -585,8 +605,8 @@ int validate_lists(fk_ctx *c)
             G.base < 0 || G.base + (long long)G.npp * FK_NFLD * G.len > (long long)c->ppT.size())
             return fail(c, FK_ERR_STATE, "internal: group %zu is inconsistent", g);
         for (int r = 0; r < G.len; ++r)
-            if (c->pr_npp[c->ket_list_all[G.begin + r]] != G.npp)
-                return fail(c, FK_ERR_STATE, "internal: group %zu mixes primitive counts", g);
+            if (c->pr_npp[c->ket_list_all[G.begin + r]] > G.npp || c->lst_npp[G.begin + r] != c->pr_npp[c->ket_list_all[G.begin + r]])
+                return fail(c, FK_ERR_STATE, "internal: group %zu holds fewer primitives than a pair", g);
     }
     if (c->blk_pos.size() != c->blk_bra.size()) return fail(c, FK_ERR_STATE, "internal: bra block arrays differ in size");
     for (size_t b = 0; b < c->blocks.size(); ++b) {
@@ -605,7 +625,7 @@ int validate_lists(fk_ctx *c)
             const FkTile &T = c->tiles[t];
             const int gid = T.grp & ~FK_TILE_SAME;
             if (T.blk < 0 || T.blk >= (int)c->blocks.size() || gid < 0 || gid >= (int)c->groups.size() ||
-                T.ket_count < 1 || T.ket_count > 64)
+                T.ket_count < 1 || T.ket_count > 64 || T.p0 >= T.p1 || T.p1 > c->groups[gid].npp)
                 return fail(c, FK_ERR_STATE, "internal: tile %lld is inconsistent", (long long)t);
             const FkBraBlock &B = c->blocks[T.blk];
             if (B.count > qc.info.bra_block)
@@ -1029,11 +1049,25 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
             if (c->pr_npp[x] != c->pr_npp[y]) return c->pr_npp[x] > c->pr_npp[y];
             return c->pr_G[x] > c->pr_G[y];
         });
-        // groups: runs of one molecule and one primitive-pair count
+        // groups: runs of one molecule with primitive-pair counts close to the
+        // run's first (largest) one, each sorted by G.  The kets of a tile come
+        // from one group and step through its largest count together (shorter
+        // kets' records are padded with K = 0), so a run takes in the next
+        // smaller count while that keeps lanes from idling: down to kGroupFar of
+        // the first count while the run is shorter than kGroupLen, then down to
+        // kGroupNear of it while it is shorter than kGroupLong.  Pruning leaves nearly every count
+        // from 1 to 81 in a small molecule, each with few pairs.
         for (size_t i = 0; i < L.size();) {
             size_t j = i;
-            const int mi = c->sh_mol[c->pr_sa[L[i]]];
-            while (j < L.size() && c->pr_npp[L[j]] == c->pr_npp[L[i]] && c->sh_mol[c->pr_sa[L[j]]] == mi) ++j;
+            const int mi = c->sh_mol[c->pr_sa[L[i]]], top = c->pr_npp[L[i]];
+            while (j < L.size() && c->sh_mol[c->pr_sa[L[j]]] == mi) {
+                const int np = c->pr_npp[L[j]];
+                size_t k = j;
+                while (k < L.size() && c->pr_npp[L[k]] == np && c->sh_mol[c->pr_sa[L[k]]] == mi) ++k;
+                if (np < (j - i < kGroupLen ? kGroupFar * top : top)) break;
+                j = k;
+            }
+            std::stable_sort(L.begin() + i, L.begin() + j, [&](int x, int y) { return c->pr_G[x] > c->pr_G[y]; });
             c->cls_groups[P].push_back({(int)i, (int)j});
             i = j;
         }
@@ -1045,7 +1079,7 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
         const size_t nl = c->ket_list_all.size();
         c->lst_sa.assign(nl, 0); c->lst_sb.assign(nl, 0);
         c->lst_sa_loc.assign(nl, 0); c->lst_sb_loc.assign(nl, 0);
-        c->lst_CD.assign(3 * std::max<size_t>(nl, 1), 0.0); c->lst_G.assign(nl, 0.0);
+        c->lst_CD.assign(3 * std::max<size_t>(nl, 1), 0.0); c->lst_G.assign(nl, 0.0); c->lst_npp.assign(nl, 0);
         for (size_t q = 0; q < nl; ++q) {
             const int p = c->ket_list_all[q];
             c->lst_sa[q] = c->pr_sa[p];
@@ -1054,6 +1088,7 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
             c->lst_sb_loc[q] = c->sh_loc[c->pr_sb[p]];
             for (int k = 0; k < 3; ++k) c->lst_CD[k * nl + q] = c->pr_AB[3 * p + k];
             c->lst_G[q] = c->pr_G[p];
+            c->lst_npp[q] = c->pr_npp[p];
         }
         c->groups.clear();
         c->cls_group0.assign(NPC + 1, 0);
@@ -1064,16 +1099,19 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
                 FkGroup G;
                 G.begin = c->ket_off[P] + g.first;
                 G.len = g.second - g.first;
-                G.npp = c->pr_npp[c->cls_list[P][g.first]];
+                G.npp = 0;
+                for (int r = g.first; r < g.second; ++r) G.npp = std::max(G.npp, c->pr_npp[c->cls_list[P][r]]);
                 G.mol = c->sh_mol[c->pr_sa[c->cls_list[P][g.first]]];
                 G.base = (long long)c->ppT.size();
                 c->ppT.resize(c->ppT.size() + (size_t)G.npp * FK_NFLD * G.len);
                 for (int r = 0; r < G.len; ++r) {
                     const int p = c->ket_list_all[G.begin + r];
+                    // beyond the pair's own count: its first record with K = 0 (field 8)
                     for (int j = 0; j < G.npp; ++j)
                         for (int f = 0; f < FK_NFLD; ++f)
                             c->ppT[G.base + ((size_t)j * FK_NFLD + f) * G.len + r] =
-                                c->pp[((size_t)c->pr_ppoff[p] + j) * FK_NPP_REC + f];
+                                j < c->pr_npp[p] ? c->pp[((size_t)c->pr_ppoff[p] + j) * FK_NPP_REC + f]
+                                                 : (f == 8 ? 0.0 : c->pp[(size_t)c->pr_ppoff[p] * FK_NPP_REC + f]);
                 }
                 c->groups.push_back(G);
             }
@@ -1208,6 +1246,25 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
                 }
                 return lo - first;
             };
+            // bra blocks, their quartet counts and, per ket group, the kets their
+            // bras reach (the union of the bras' prefixes)
+            struct Reach { int i0, i1, blk, gi; };
+            std::vector<Reach> reach;
+            // kets [0, cnt) of group gi that bra position pb takes
+            auto bra_reach = [&](int pb, size_t gi) {
+                const auto &g = c->cls_groups[Q][gi];
+                int cnt = opts.tau > 0 ? prefix(g.first, g.second, c->pr_G[LP[pb]], opts.tau) : g.second - g.first;
+                if (P == Q) cnt = std::min(cnt, std::max(0, pb + 1 - g.first));
+                return cnt;
+            };
+            // serial work of a lane (in flops): per bra and round of kets a fixed
+            // part (screen, digestion) and the primitive loops
+            const double f_prim = qc.flops_prim() / ts * (ts > 1 ? 2.0 : 1.0);
+            const double f_bra = kBraOverheadFlops + 2.0 * qc.info.flops_quartet / ts;
+            auto rounds_of = [&](int kets) { return (kets + qpw - 1) / qpw; };
+            std::vector<int64_t> npp_before(LQ.size() + 1, 0);  // primitive pairs before each list position
+            for (size_t k = 0; k < LQ.size(); ++k) npp_before[k + 1] = npp_before[k] + c->pr_npp[LQ[k]];
+            double serial_total = 0;
             for (size_t i0 = 0; i0 < ord.size();) {
                 size_t i1 = i0;
                 const int sa0 = c->pr_sa[LP[ord[i0]]];
@@ -1225,42 +1282,85 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
                 for (size_t gi = 0; gi < c->cls_groups[Q].size(); ++gi) {
                     const auto &g = c->cls_groups[Q][gi];
                     if (c->sh_mol[c->pr_sa[LQ[g.first]]] != bmol) continue;  // kets of the bra's molecule only
-                    const int gnpp = c->pr_npp[LQ[g.first]];
-                    // ket range [0, hi) of the group: the union of the bras' prefixes
+                    const int gnpp = c->groups[c->cls_group0[Q] + gi].npp;
                     int hi = 0;
                     for (size_t x = i0; x < i1; ++x) {
-                        const int pb = ord[x], bra = LP[pb];
-                        const double gb = c->pr_G[bra];
-                        int cnt = opts.tau > 0 ? prefix(g.first, g.second, gb, opts.tau) : g.second - g.first;
-                        if (P == Q) cnt = std::min(cnt, std::max(0, pb + 1 - g.first));
-                        if (cnt <= 0) continue;
+                        const int cnt = bra_reach(ord[x], gi);
                         hi = std::max(hi, cnt);
                         qc.nquartet += cnt;
-                        qc.nprim += (int64_t)cnt * c->pr_npp[bra] * gnpp;
+                        qc.nprim += c->pr_npp[LP[ord[x]]] * (npp_before[g.first + cnt] - npp_before[g.first]);
+                        serial_total += rounds_of(cnt) * (f_bra + f_prim * c->pr_npp[LP[ord[x]]] * gnpp);
                     }
-                    for (int kk = 0; kk < hi; kk += tile_kets) {
-                        FkTile t;
-                        t.blk = blk;
-                        t.ket_begin = c->ket_off[Q] + g.first + kk;
-                        t.ket_count = std::min(tile_kets, hi - kk);
-                        t.grp = (c->cls_group0[Q] + (int)gi) | ((P == Q) ? FK_TILE_SAME : 0);
-                        tl.push_back(t);
-                        // lane slots of the tile's primitive loops: rounds of
-                        // (quartets per wave) kets, 64 lanes each (a group of
-                        // waves per quartet for the wave kernels), for every bra
-                        const int64_t rounds = (t.ket_count + qpw - 1) / qpw;
-                        const int64_t lanes = qc.info.wave_per_quartet == 3 ? std::max(64, qc.info.team_size) : 64;
-                        qc.prim_slots += rounds * lanes * nppsum * gnpp;
-                    }
+                    if (hi > 0) reach.push_back(Reach{(int)i0, (int)i1, blk, (int)gi});
                 }
                 i0 = i1;
             }
+            // A tile is one wave's serial work.  Where a class has few tiles, whole
+            // blocks against deeply contracted kets would leave most of the chip
+            // waiting for a handful of waves, so a tile's serial work is bounded
+            // (kTileShare, kMinTileFlops): first the block is cut into runs of bras (each
+            // a block of its own), then a single bra's tile over the kets'
+            // primitive pairs.  Large classes keep their whole blocks.
+            const double t_max = std::max(kMinTileFlops, kTileShare * serial_total / (8.0 * (c->ncu > 0 ? c->ncu : 256)));
+            std::map<std::pair<int, int>, int> runs;  // runs of the present block: (first, count) -> block
+            int runs_blk = -1;
+            for (const Reach &R : reach) {
+                if (R.blk != runs_blk) { runs.clear(); runs_blk = R.blk; }
+                const auto &g = c->cls_groups[Q][R.gi];
+                const int gnpp = c->groups[c->cls_group0[Q] + R.gi].npp;
+                const int full_rounds = rounds_of(std::min(tile_kets, g.second - g.first));
+                for (int x0 = R.i0; x0 < R.i1;) {
+                    int hi = 0, x1 = x0;
+                    int64_t nppsum = 0;
+                    double cost1 = 0;  // one round of kets against the run
+                    for (; x1 < R.i1; ++x1) {
+                        const int np = c->pr_npp[LP[ord[x1]]];
+                        const double add = f_bra + f_prim * np * gnpp;
+                        if (x1 > x0 && full_rounds * (cost1 + add) > t_max) break;
+                        cost1 += add;
+                        nppsum += np;
+                        hi = std::max(hi, bra_reach(ord[x1], R.gi));
+                    }
+                    int blk = R.blk;
+                    if (hi > 0 && (x0 > R.i0 || x1 < R.i1)) {
+                        const auto key = std::make_pair(x0 - R.i0, x1 - x0);
+                        const auto it = runs.find(key);
+                        if (it != runs.end()) blk = it->second;
+                        else {
+                            blk = (int)c->blocks.size();
+                            runs[key] = blk;
+                            c->blocks.push_back(FkBraBlock{c->blocks[R.blk].first + key.first, key.second});
+                            c->blk_nppsum.push_back(nppsum);
+                        }
+                    }
+                    int kets = tile_kets, parts = 1;
+                    if (x1 - x0 == 1 && full_rounds * cost1 > t_max) {
+                        kets = std::min(tile_kets, qpw);
+                        parts = (int)std::min<double>(gnpp, std::ceil(cost1 / t_max));
+                    }
+                    x0 = x1;
+                    for (int kk = 0; kk < hi; kk += kets)
+                        for (int s = 0; s < parts; ++s) {
+                            FkTile t;
+                            t.blk = blk;
+                            t.ket_begin = c->ket_off[Q] + g.first + kk;
+                            t.ket_count = (unsigned char)std::min(kets, hi - kk);
+                            t.p0 = (unsigned char)(gnpp * s / parts);
+                            t.p1 = (unsigned char)(gnpp * (s + 1) / parts);
+                            t.pad = 0;
+                            t.grp = (c->cls_group0[Q] + R.gi) | ((P == Q) ? FK_TILE_SAME : 0);
+                            tl.push_back(t);
+                            // lane slots of the tile's primitive loops: rounds of
+                            // (quartets per wave) kets, 64 lanes each (a group of
+                            // waves per quartet for the wave kernels), for every bra
+                            const int64_t lanes = qc.info.wave_per_quartet == 3 ? std::max(64, qc.info.team_size) : 64;
+                            qc.prim_slots += rounds_of(t.ket_count) * lanes * nppsum * (t.p1 - t.p0);
+                        }
+                }
+            }
             if (tl.empty()) continue;
             // most expensive tiles first (bra primitives x ket primitives x kets)
-            auto cost = [&](const FkTile &t) {
-                const FkGroup &gg = c->groups[t.grp & ~FK_TILE_SAME];
-                return c->blk_nppsum[t.blk] * gg.npp * t.ket_count;
-            };
+            auto cost = [&](const FkTile &t) { return c->blk_nppsum[t.blk] * (t.p1 - t.p0) * t.ket_count; };
             std::stable_sort(tl.begin(), tl.end(), [&](const FkTile &x, const FkTile &y) { return cost(x) > cost(y); });
             // block tasks: the tiles of one bra block, cut into chunks that share
             // the block's tiles round-robin (each a similar mix of costs),
@@ -1274,7 +1374,14 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
                 for (size_t i = 0; i < tl.size();) {
                     size_t j = i;
                     while (j < tl.size() && tl[j].blk == tl[i].blk) ++j;
-                    const int64_t len = (int64_t)(j - i), nch = (len + ch - 1) / ch;
+                    const int64_t len = (int64_t)(j - i);
+                    // chunks no longer than ch tiles, nor than twice the longest
+                    // tile's time for the four or eight waves of the workgroup
+                    double serial = 0;
+                    for (size_t k = i; k < j; ++k)
+                        serial += c->blocks[tl[k].blk].count * f_bra + f_prim * c->blk_nppsum[tl[k].blk] * (tl[k].p1 - tl[k].p0);
+                    const int64_t nch = std::min<int64_t>((len + qc.nw - 1) / qc.nw,
+                                                          std::max<int64_t>((len + ch - 1) / ch, (int64_t)(serial / (2 * qc.nw * t_max))));
                     const size_t c0 = chunks.size();
                     chunks.resize(c0 + nch);
                     ccost.resize(c0 + nch, 0.0);
@@ -1337,6 +1444,7 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
         if ((rc = dev_upload(c, c->d_ket, c->ket_list_all.data(), c->ket_list_all.size()))) return rc;
         if ((rc = dev_upload(c, c->d_lst_sa, c->lst_sa_loc.data(), c->lst_sa_loc.size()))) return rc;
         if ((rc = dev_upload(c, c->d_lst_sb, c->lst_sb_loc.data(), c->lst_sb_loc.size()))) return rc;
+        if ((rc = dev_upload(c, c->d_lst_npp, c->lst_npp.data(), c->lst_npp.size()))) return rc;
         if ((rc = dev_upload(c, c->d_lst_CD, c->lst_CD.data(), c->lst_CD.size()))) return rc;
         if ((rc = dev_upload(c, c->d_lst_G, c->lst_G.data(), c->lst_G.size()))) return rc;
         if ((rc = dev_upload(c, c->d_ppT, c->ppT.data(), c->ppT.size()))) return rc;
@@ -1709,6 +1817,7 @@ int build_jk_impl(fk_ctx *c, const double *D, double *J, double *K, unsigned fla
         a.ket_list = c->d_ket.p;
         a.lst_sa = c->d_lst_sa.p;
         a.lst_sb = c->d_lst_sb.p;
+        a.lst_npp = c->d_lst_npp.p;
         a.lst_CD = c->d_lst_CD.p;
         a.lst_G = c->d_lst_G.p;
         a.nlist = (int)c->ket_list_all.size();
@@ -2348,6 +2457,7 @@ int fk_check_indices(fk_ctx *c)
                 return fail(c, FK_ERR_STATE, "tile %lld: bra shells do not match the class", (long long)t);
             if (gsa != c->pr_sa[c->blk_bra[BB.first]])
                 return fail(c, FK_ERR_STATE, "tile %lld: bra block members differ in their first shell", (long long)t);
+            if (T.p0 >= T.p1 || T.p1 > g.npp) return fail(c, FK_ERR_STATE, "tile %lld: ket primitive range", (long long)t);
             if (T.ket_count < 1 || T.ket_count > 64)
                 return fail(c, FK_ERR_STATE, "tile %lld: ket count %d", (long long)t, T.ket_count);
             for (int k = 0; k < 64; ++k) {
@@ -2365,7 +2475,7 @@ int fk_check_indices(fk_ctx *c)
                 if (c->sh_mol[gsc] != g.mol || c->sh_mol[gsd] != g.mol)
                     return fail(c, FK_ERR_STATE, "tile %lld lane %d: ket outside the tile's molecule", (long long)t, k);
                 const int sc = c->sh_loc[gsc], sd = c->sh_loc[gsd];
-                if (ncart(c->sh_l[gsc]) != NC || ncart(c->sh_l[gsd]) != ND || c->pr_npp[kp] != g.npp)
+                if (ncart(c->sh_l[gsc]) != NC || ncart(c->sh_l[gsd]) != ND || c->pr_npp[kp] > g.npp)
                     return fail(c, FK_ERR_STATE, "tile %lld lane %d: ket does not match class/group", (long long)t, k);
                 const long long last = g.base + ((long long)(g.npp - 1) * FK_NFLD + FK_NFLD - 1) * g.len + r;
                 if (g.base < 0 || last >= nT) return fail(c, FK_ERR_STATE, "tile %lld lane %d: ket records", (long long)t, k);

@@ -14,11 +14,16 @@
 // 64 consecutive ket shell pairs of one ket class, all from one
 // primitive-count group.  Every (bra, ket) combination of the tile is a
 // candidate quartet; the kernels apply the Schwarz, same-class and density
-// tests per combination.
+// tests per combination.  A tile whose serial primitive loop would outlast the
+// rest of its launch is cut into several over the kets' primitive pairs: J and
+// K are linear in the integrals, so each part digests its own partial sums
+// (the part with p0 = 0 counts the quartets).
 struct FkTile {
     int blk;        // bra block (index into FkJKArgs::blocks)
     int ket_begin;  // position in the concatenated sorted pair lists
-    int ket_count;  // 1..64
+    unsigned char ket_count;  // 1..64
+    unsigned char p0, p1;     // the kets' primitive pairs p0 <= j < p1 this tile sums (at most FK_MAX_K^2 = 81)
+    unsigned char pad;
     int grp;        // primitive-count group of the kets; bit 30: bra and ket from the same class
 };
 #define FK_TILE_SAME (1 << 30)
@@ -35,13 +40,13 @@ struct FkBraBlock {
 };
 #define FK_MAX_BRA_BLOCK 32
 
-// A run of equal primitive-pair count inside one class's sorted pair list.
+// A run of similar primitive-pair counts inside one class's sorted pair list.
 // Its primitive records are stored transposed, [j][field][position in run],
 // so that lanes holding consecutive kets read consecutive addresses.
 struct FkGroup {
     int begin;      // first list position
     int len;        // number of pairs
-    int npp;        // primitive pairs per pair
+    int npp;        // primitive pairs per pair (the largest; shorter pairs end in records with K = 0)
     int mol;        // molecule of the run's pairs (0 unless the context holds a batch)
     long long base; // offset of the run's records in the transposed array
 };
@@ -69,6 +74,7 @@ struct FkJKArgs {
     const double *pp;        // [nprimpair * FK_NPP_REC]
     const int *ket_list;     // sorted pair indices (all classes, concatenated)
     const int *lst_sa, *lst_sb;   // shells (within the molecule) of the pair at each list position
+    const int *lst_npp;      // its primitive pairs (its group's records hold at least as many)
     const double *lst_CD;    // [3][nlist] A - B of the pair at each list position
     const double *lst_G;     // Schwarz factor at each list position
     int nlist;

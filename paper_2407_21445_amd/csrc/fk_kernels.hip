@@ -85,6 +85,22 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
+// Primitive quartets are counted per lane (lanes hold kets of different
+// primitive counts) and summed over the wave once, or before a lane's count
+// could overflow.
+__device__ __forceinline__ void count_flush(unsigned &lane_n, unsigned long long &sum)
+{
+    unsigned long long v = lane_n;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    sum += v;
+    lane_n = 0;
+}
+__device__ __forceinline__ void count_check(unsigned &lane_n, unsigned long long &sum)
+{
+    if (__ballot(lane_n >= 1u << 31) != 0ull) count_flush(lane_n, sum);
+}
+
 __device__ __forceinline__ void wave_sync_lds()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -573,6 +589,7 @@ __global__ void __launch_bounds__(64 * NW, (LpqBounds<LA, LB, LC, LD, NW>::value
     const int stg = a.ntask > 0 ? LpqStageTask<LA, LB, LC, LD>::value : LpqStage<LA, LB, LC, LD>::value;
     double *s_stage = s_dyn + rys_lds_size(Q::NR) + wave * stg;
     unsigned long long cq = 0, cp = 0;
+    unsigned lane_cp = 0;
 
     constexpr int NBK = LpqKetOuter<LA, LB, LC, LD>::value;
     // instantiations that take block tasks: the ket-outer ones and the wide ones
@@ -585,6 +602,7 @@ __global__ void __launch_bounds__(64 * NW, (LpqBounds<LA, LB, LC, LD, NW>::value
         const FkTile tile = a.tiles[t];
         const bool same = (tile.grp & FK_TILE_SAME) != 0;
         const FkGroup g = a.groups[tile.grp & ~FK_TILE_SAME];
+        const int p0 = tile.p0, p1 = tile.p1;
         // the tile's molecule: its blocks of D, D_sh, X_J, X_K and shells
         const int mol = g.mol;
         const int n = a.mol_nbf[mol], ns = a.mol_nsh[mol];
@@ -603,6 +621,8 @@ __global__ void __launch_bounds__(64 * NW, (LpqBounds<LA, LB, LC, LD, NW>::value
         const int oc = shbf[sc], od = shbf[sd];
         const int sa = a.pair_sa[a.blk_bra[blk.first]];
         const int oa = shbf[sa];
+        // the ket's own primitive pairs in the tile's range (the rest is padding)
+        const int kpp = max(min(a.lst_npp[pos], p1) - p0, 0);
         int colc = 0, cold = 0;
         if (kr) {
             const int *kcol = a.krow_col + a.mol_sh0[mol];
@@ -648,16 +668,18 @@ __global__ void __launch_bounds__(64 * NW, (LpqBounds<LA, LB, LC, LD, NW>::value
                     ppo[jb] = __builtin_amdgcn_readfirstlane(a.pair_ppoff[bra]);
                     bnpp[jb] = __builtin_amdgcn_readfirstlane(a.pair_npp[bra]);
                     const int nact = __popcll(__ballot(active));
-                    cq += nact;
-                    cp += (unsigned long long)nact * bnpp[jb] * g.npp;
-                    if (active) act |= 1u << jb;
+                    cq += p0 == 0 ? nact : 0;
+                    if (active) {
+                        act |= 1u << jb;
+                        lane_cp += bnpp[jb] * kpp;
+                    }
                 }
             }
             if (act) {
-                fk::PrimPair qn = load_ket_pp(a.ppT, g, 0, r);
-                for (int j = 0; j < g.npp; ++j) {
+                fk::PrimPair qn = load_ket_pp(a.ppT, g, p0, r);
+                for (int j = p0; j < p1; ++j) {
                     const fk::PrimPair q = qn;
-                    if (j + 1 < g.npp) qn = load_ket_pp(a.ppT, g, j + 1, r);
+                    if (j + 1 < p1) qn = load_ket_pp(a.ppT, g, j + 1, r);
 #pragma unroll
                     for (int jb = 0; jb < NBK; ++jb) {
                         if (jb < nb && ((act >> jb) & 1u)) {
@@ -725,8 +747,8 @@ __global__ void __launch_bounds__(64 * NW, (LpqBounds<LA, LB, LC, LD, NW>::value
             const unsigned long long mask = __ballot(active);
             if (mask == 0ull) continue;
             const int nact = __popcll(mask);
-            cq += nact;
-            cp += (unsigned long long)nact * B.npp * g.npp;
+            cq += p0 == 0 ? nact : 0;
+            if (active) lane_cp += B.npp * kpp;
 
             const int ppo = __builtin_amdgcn_readfirstlane(B.ppo);
             const int bnpp = __builtin_amdgcn_readfirstlane(B.npp);
@@ -735,10 +757,10 @@ __global__ void __launch_bounds__(64 * NW, (LpqBounds<LA, LB, LC, LD, NW>::value
             for (int o = 0; o < NOUT; ++o) acc[o] = (R)0;
             if constexpr (ENG == 0) {
                 if (active) {
-                    fk::PrimPair qn = load_ket_pp(a.ppT, g, 0, r);
-                    for (int j = 0; j < g.npp; ++j) {
+                    fk::PrimPair qn = load_ket_pp(a.ppT, g, p0, r);
+                    for (int j = p0; j < p1; ++j) {
                         const fk::PrimPair q = qn;
-                        if (j + 1 < g.npp) qn = load_ket_pp(a.ppT, g, j + 1, r);
+                        if (j + 1 < p1) qn = load_ket_pp(a.ppT, g, j + 1, r);
                         // two bra primitives per step for the small classes: their
                         // quartets are independent straight-line code the compiler
                         // interleaves (larger classes would spill)
@@ -763,10 +785,10 @@ __global__ void __launch_bounds__(64 * NW, (LpqBounds<LA, LB, LC, LD, NW>::value
 #pragma unroll
                 for (int o = 0; o < H::NACC; ++o) acce[o] = (R)0;
                 if (active) {
-                    fk::PrimPair qn = load_ket_pp(a.ppT, g, 0, r);
-                    for (int j = 0; j < g.npp; ++j) {
+                    fk::PrimPair qn = load_ket_pp(a.ppT, g, p0, r);
+                    for (int j = p0; j < p1; ++j) {
                         const fk::PrimPair q = qn;
-                        if (j + 1 < g.npp) qn = load_ket_pp(a.ppT, g, j + 1, r);
+                        if (j + 1 < p1) qn = load_ket_pp(a.ppT, g, j + 1, r);
                         for (int i = 0; i < bnpp; ++i)
                             fk::hgp_prim<LA, LB, LC, LD, R>(s_tab, sload_pp(a.pp, ppo + i), q, acce);
                     }
@@ -779,6 +801,7 @@ __global__ void __launch_bounds__(64 * NW, (LpqBounds<LA, LB, LC, LD, NW>::value
                                           kr ? kr + jb * NB * a.krow_ncol : nullptr, a.krow_ncol, colc, cold,
                                           kr ? kr + (nbk * NB + NA) * a.krow_ncol + jb * NA * NB : nullptr);
         }
+        count_check(lane_cp, cp);
         // block sums: a lane without work holds zeros, which are not added
         if (__ballot(any) != 0ull) {
             if (wk && kr) {
@@ -856,7 +879,8 @@ __global__ void __launch_bounds__(64 * NW, (LpqBounds<LA, LB, LC, LD, NW>::value
         const int nwt = gridDim.x * NW;
         for (int t = blockIdx.x * NW + wave; t < a.ntiles; t += nwt) do_tile(t, nullptr);
     }
-    if (lane == 0 && cq) {
+    count_flush(lane_cp, cp);
+    if (lane == 0 && (cq | cp)) {
         atomicAdd(&a.counters[0], cq);
         atomicAdd(&a.counters[1], cp);
     }
@@ -947,11 +971,13 @@ __global__ void __launch_bounds__(FK_BLOCK, (TpqMinBlocks<LA, LB, LC, LD>::value
     const int bx[3] = {fk::kCart.x[LB][ib0], fk::kCart.y[LB][ib0], fk::kCart.z[LB][ib0]};
     double *tsum = s_team + (lane_ok ? slot : 0) * NV;
     unsigned long long cq = 0, cp = 0;
+    unsigned lane_cp = 0;  // counted by each team's first lane
 
     for (int t = blockIdx.x * FK_WAVES + wave; t < a.ntiles; t += nwt) {
         const FkTile tile = a.tiles[t];
         const bool same = (tile.grp & FK_TILE_SAME) != 0;
         const FkGroup g = a.groups[tile.grp & ~FK_TILE_SAME];
+        const int p0 = tile.p0, p1 = tile.p1;
         // the tile's molecule: its blocks of D, D_sh, X_J, X_K and shells
         const int mol = g.mol;
         const int n = a.mol_nbf[mol], ns = a.mol_nsh[mol];
@@ -994,18 +1020,18 @@ __global__ void __launch_bounds__(FK_BLOCK, (TpqMinBlocks<LA, LB, LC, LD>::value
                 const unsigned long long mask = __ballot(active);
                 if (mask == 0ull) continue;
                 const int nact = __popcll(mask) / TS;
-                cq += nact;
-                cp += (unsigned long long)nact * B.npp * g.npp;
+                cq += p0 == 0 ? nact : 0;
+                if (active && comp == 0) lane_cp += B.npp * max(min(a.lst_npp[pos], p1) - p0, 0);
                 const int ppo = __builtin_amdgcn_readfirstlane(B.ppo);
                 const int bnpp = __builtin_amdgcn_readfirstlane(B.npp);
                 R acc[NOL];
 #pragma unroll
                 for (int o = 0; o < NOL; ++o) acc[o] = (R)0;
                 if (active) {
-                    fk::PrimPair qn = load_ket_pp(a.ppT, g, 0, r);
-                    for (int j = 0; j < g.npp; ++j) {
+                    fk::PrimPair qn = load_ket_pp(a.ppT, g, p0, r);
+                    for (int j = p0; j < p1; ++j) {
                         const fk::PrimPair q = qn;
-                        if (j + 1 < g.npp) qn = load_ket_pp(a.ppT, g, j + 1, r);
+                        if (j + 1 < p1) qn = load_ket_pp(a.ppT, g, j + 1, r);
                         for (int i = 0; i < bnpp; ++i)
                             fk::rys_prim_team<LA, LB, LC, LD, MODE, R>(s_tab, sload_pp(a.pp, ppo + i), q, B.AB, Kt.CD,
                                                                       ax, bx, acc);
@@ -1092,6 +1118,7 @@ __global__ void __launch_bounds__(FK_BLOCK, (TpqMinBlocks<LA, LB, LC, LD>::value
                     atomic_add(&XJ[(size_t)(oc + v / ND) * n + od + v % ND], 2.0 * tsum[v]);
             wave_sync_lds();
         }
+        count_check(lane_cp, cp);
         // X_J[a, b] of every bra of the block, summed over the tile's kets
         for (int x = lane; x < blk.count * NA * NB; x += 64) {
             const int jb = x / (NA * NB), ab = x % (NA * NB);
@@ -1100,7 +1127,8 @@ __global__ void __launch_bounds__(FK_BLOCK, (TpqMinBlocks<LA, LB, LC, LD>::value
             if (v != 0.0) atomic_add(&XJ[(size_t)(oa + ab / NB) * n + ob + ab % NB], 2.0 * v);
         }
     }
-    if (lane == 0 && cq) {
+    count_flush(lane_cp, cp);
+    if (lane == 0 && (cq | cp)) {
         atomicAdd(&a.counters[0], cq);
         atomicAdd(&a.counters[1], cp);
     }
@@ -1159,6 +1187,7 @@ __global__ void __launch_bounds__(FK_BLOCK) k_jk_wpq(FkJKArgs a)
         const int bra = a.blk_bra[a.blocks[tile.blk].first];
         const bool same = (tile.grp & FK_TILE_SAME) != 0;
         const FkGroup g = a.groups[tile.grp & ~FK_TILE_SAME];
+        const int p0 = tile.p0, p1 = tile.p1;
         // the tile's molecule: its blocks of D, D_sh, X_J, X_K and shells
         const int mol = g.mol;
         const int n = a.mol_nbf[mol], ns = a.mol_nsh[mol];
@@ -1190,15 +1219,15 @@ __global__ void __launch_bounds__(FK_BLOCK) k_jk_wpq(FkJKArgs a)
             const int sc = Kt.sc, sd = Kt.sd;
             const int r = pos - g.begin;
             if (half == 0) {
-                cq += 1;
-                cp += (unsigned long long)B.npp * g.npp;
+                cq += p0 == 0 ? 1 : 0;
+                cp += (unsigned long long)B.npp * max(min(a.lst_npp[pos], p1) - p0, 0);
             }
             double acc[ITEMS][NCD];
 #pragma unroll
             for (int it = 0; it < ITEMS; ++it)
 #pragma unroll
                 for (int o = 0; o < NCD; ++o) acc[it][o] = 0.0;
-            for (int j = 0; j < g.npp; ++j) {
+            for (int j = p0; j < p1; ++j) {
                 const fk::PrimPair q = load_ket_pp(a.ppT, g, j, r);
                 for (int i = 0; i < bnpp; ++i) {
                     const fk::PrimPair p = sload_pp(a.pp, ppo + i);
@@ -1265,7 +1294,7 @@ __global__ void __launch_bounds__(FK_BLOCK) k_jk_wpq(FkJKArgs a)
             }
         }
     }
-    if (lane == 0 && cq) {
+    if (lane == 0 && (cq | cp)) {
         atomicAdd(&a.counters[0], cq);
         atomicAdd(&a.counters[1], cp);
     }

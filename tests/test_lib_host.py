@@ -634,3 +634,26 @@ def test_xcd_region_order_keeps_the_lists_valid():
     assert any(x["block_tasks"] > 0 for x in a)
     for x, y in zip(a, b):
         assert x["class"] == y["class"] and x["quartets"] == y["quartets"]
+
+
+# ------------------------------------------------- small work: cut tiles, ket groups
+@pytest.mark.parametrize("name", ["water2_ccpvdz", "water9_ccpvdz", "spdf"])
+def test_cut_tiles_keep_the_quartets(name):
+    """Few quartets: tiles are cut by runs of bras and over the kets'
+    primitive pairs, and kets of similar primitive counts share a group whose
+    records are padded.  The Schwarz counts are the sums over all pairs (no
+    screening: every quartet once, padding not counted) and every address stays
+    in bounds (fk_build_quartets checks the ranges itself)."""
+    s = _rand_sys(33, lmax=3, natom=3, kmax=2) if name == "spdf" else wl.water_sys(int(name[5]), "ccpvdz-type")
+    s["charge"] = s.get("charge", 0) if name != "spdf" else 1
+    c = fk.FockJK(device=-1).set_system(s).build_quartets(tau=0.0)
+    c.check_indices()
+    ns = len(s["sh_nprim"])
+    npair = ns * (ns + 1) // 2
+    assert c.info()["nquartet_schwarz"] == npair * (npair + 1) // 2
+    a = fk.FockJK(device=-1).set_system(s).build_quartets(tau=1e-10, tau_prim=1e-12)
+    a.check_indices()
+    one = fk.FockJK(device=-1).set_system(s).build_quartets(tau=1e-10, tau_prim=1e-12, bra_block=1)
+    one.check_indices()
+    assert a.info()["nquartet_schwarz"] == one.info()["nquartet_schwarz"]
+    assert a.info()["flops_schwarz"] == pytest.approx(one.info()["flops_schwarz"], rel=1e-14)
