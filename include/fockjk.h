@@ -106,7 +106,7 @@ typedef struct {
                           K_xy whose fitted density bound stays below tau_k are
                           skipped, see fk_density_bound; the paper uses 5e-6).
                           0 = no block skip */
-    int    block_tasks; /* lane classes: 0 = a workgroup takes all ket tiles of
+    int    block_tasks; /* 0 = a workgroup takes all ket tiles of
                           one bra block (a, b_1..b_m) at a time and sums
                           X_K[b_j, x], X_K[a, x] and X_J[a, b_j] in LDS, which
                           reaches memory once per block instead of once per tile
@@ -117,7 +117,10 @@ typedef struct {
                           autotuner), the bra-outer (ps|ps), (pp|ss), (pp|ps),
                           (ds|ss), (ds|ps), (dp|ss), (dp|ps) with eight-wave
                           workgroups, the bra block lowered until the rows fit
-                          (fk_stats reports both);
+                          (fk_stats reports both).  The team- and
+                          wave-per-quartet kernels do the same where their rows
+                          fit with the whole bra block (fk_stats does not count
+                          these);
                           -1 = every wave takes tiles on its own */
 } fk_screen_opts;
 
@@ -162,8 +165,9 @@ typedef struct {
     int     bra_block[FK_MAX_QCLASS];     /* the schedule in effect (fk_set_class_schedule) */
     int     kets_per_tile[FK_MAX_QCLASS];
     double  grid_fraction[FK_MAX_QCLASS];
-    int64_t block_tasks[FK_MAX_QCLASS];   /* workgroup tasks of the class (fk_screen_opts
-                                             .block_tasks), 0 if its waves take tiles */
+    int64_t block_tasks[FK_MAX_QCLASS];   /* workgroup tasks of a lane class (fk_screen_opts
+                                             .block_tasks), 0 if its waves take tiles; 0 for
+                                             team and wave kernels */
     int     waves_per_group[FK_MAX_QCLASS]; /* waves per workgroup of the launch (4, or 8 for
                                              the bra-outer lane classes with block tasks) */
 } fk_stats_t;
@@ -309,8 +313,7 @@ int fk_set_class_engine(fk_ctx *ctx, int la, int lb, int lc, int ld, int engine)
  * a call (or a schedule file) the ket-outer lane classes take them and the
  * bra-outer ones do not.  Takes effect at the next fk_build_quartets;
  * FK_ERR_UNSUPPORTED for a class not built.  Classes other than the lane
- * classes listed at fk_screen_opts.block_tasks never take block tasks,
- * whatever is set. */
+ * classes listed at fk_screen_opts.block_tasks do not follow this setting. */
 int fk_set_class_block_tasks(fk_ctx *ctx, int la, int lb, int lc, int ld, int enable);
 
 /* Lanes per quartet of a class's kernel.  Every class has its own kernel

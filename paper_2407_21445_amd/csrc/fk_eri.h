@@ -30,6 +30,15 @@
 
 #include "fk_rys.h"
 
+// From this many roots on the root loop of the team and wave kernels stays
+// rolled: unrolled, (ff|fp) to (ff|ff) and (fd|fd) outgrow the registers and the
+// instruction cache ((ff|ff) spills 734 registers, 59 rolled).  With fewer roots
+// the unrolled loop hides the table's LDS latency behind the next root's
+// arithmetic and is faster at the one or two waves per SIMD these kernels run
+// ((pp|pp), 3 roots, (H2O)64: 14.4 ms unrolled, 15.5 rolled; (fd|ps), 4 roots,
+// organic molecule of 324 functions: 1.40 and 1.78 ms).
+#define FK_ROLL_MIN_NR 6
+
 namespace fk {
 
 constexpr int ncart(int l) { return (l + 1) * (l + 2) / 2; }
@@ -224,6 +233,26 @@ FK_HD void rys_prim_all(const double *__restrict tab, const PrimPair &p, const P
     }
 }
 
+// f(u_r, w_r) for every root of T, rolled from FK_ROLL_MIN_NR roots on
+template <int N, class F>
+FK_HD void each_root(double T, const double *__restrict tab, F &&f)
+{
+    if constexpr (N >= FK_ROLL_MIN_NR) {
+        const RysAt<N> at = rys_at<N>(T, tab);
+#pragma unroll 1
+        for (int r = 0; r < N; ++r) {
+            double u, w;
+            rys_root_at<N>(at, r, u, w);
+            f(u, w);
+        }
+    } else {
+        double u[N], w[N];
+        rys_roots<N, true>(T, tab, u, w);
+#pragma unroll
+        for (int r = 0; r < N; ++r) f(u[r], w[r]);
+    }
+}
+
 // Binomial coefficients for the closed form of the horizontal recurrence
 // (x - B)^b = sum_k C(b,k) (A - B)^(b-k) (x - A)^k.
 FK_HD constexpr double binom(int n, int k)
@@ -245,11 +274,7 @@ FK_HD void rys_prim_bra_comp(const double *__restrict tab, const PrimPair &p, co
     using Q = QClass<LA, LB, LC, LD>;
     constexpr int LAB = Q::LAB, LCD = Q::LCD;
     QuartetSetup s = quartet_setup(p, q);
-    double u[Q::NR], w[Q::NR];
-    rys_roots<Q::NR, true>(s.T, tab, u, w);
-#pragma unroll
-    for (int r = 0; r < Q::NR; ++r) {
-        const double ur = u[r];
+    each_root<Q::NR>(s.T, tab, [&](double ur, double wr) __attribute__((always_inline)) {
         const double B00 = 0.5 * s.inv * ur;
         const double B10 = p.oo2z * (1.0 - s.ez * ur);
         const double B01 = q.oo2z * (1.0 - s.zz * ur);
@@ -259,7 +284,7 @@ FK_HD void rys_prim_bra_comp(const double *__restrict tab, const PrimPair &p, co
             const double C00 = p.PA[k] - s.ez * s.PQ[k] * ur;
             const double C00p = q.PA[k] + s.zz * s.PQ[k] * ur;
             double G[LAB + 1][LCD + 1];
-            G[0][0] = (k == 2) ? w[r] * s.pref : 1.0;
+            G[0][0] = (k == 2) ? wr * s.pref : 1.0;
             if constexpr (LAB > 0) {
                 G[1][0] = C00 * G[0][0];
 #pragma unroll
@@ -317,7 +342,7 @@ FK_HD void rys_prim_bra_comp(const double *__restrict tab, const PrimPair &p, co
                 acc[ic * Q::ND + id] += I[0][kCart.x[LC][ic]][kCart.x[LD][id]]
                                       * I[1][kCart.y[LC][ic]][kCart.y[LD][id]]
                                       * I[2][kCart.z[LC][ic]][kCart.z[LD][id]];
-    }
+    });
 }
 
 // Team form: the lane owns bra component a (exponents a[3], run-time) and,
@@ -332,11 +357,8 @@ FK_HD void rys_prim_team(const double *__restrict tab, const PrimPair &p, const 
     constexpr int LAB = Q::LAB, LCD = Q::LCD;
     constexpr int NBL = (MODE == 1) ? Q::NB : 1;
     QuartetSetup s = quartet_setup(p, q);
-    double u[Q::NR], w[Q::NR];
-    rys_roots<Q::NR, (Q::L > 0)>(s.T, tab, u, w);
-#pragma unroll
-    for (int r = 0; r < Q::NR; ++r) {
-        const R ur = (Q::L > 0) ? (R)u[r] : (R)0;
+    each_root<Q::NR>(s.T, tab, [&](double uu, double ww) __attribute__((always_inline)) {
+        const R ur = (R)uu;
         const R B00 = (R)(0.5 * s.inv) * ur;
         const R B10 = (R)p.oo2z * ((R)1 - (R)s.ez * ur);
         const R B01 = (R)q.oo2z * ((R)1 - (R)s.zz * ur);
@@ -346,7 +368,7 @@ FK_HD void rys_prim_team(const double *__restrict tab, const PrimPair &p, const 
             const R C00 = (R)p.PA[k] - (R)(s.ez * s.PQ[k]) * ur;
             const R C00p = (R)q.PA[k] + (R)(s.zz * s.PQ[k]) * ur;
             R G[LAB + 1][LCD + 1];
-            G[0][0] = (k == 2) ? (R)(w[r] * s.pref) : (R)1;
+            G[0][0] = (k == 2) ? (R)(ww * s.pref) : (R)1;
             if constexpr (LAB > 0) {
                 G[1][0] = C00 * G[0][0];
 #pragma unroll
@@ -437,7 +459,7 @@ FK_HD void rys_prim_team(const double *__restrict tab, const PrimPair &p, const 
                     acc[(ib * Q::NC + ic) * Q::ND + id] += I[0][ib][kCart.x[LC][ic]][kCart.x[LD][id]]
                                                          * I[1][ib][kCart.y[LC][ic]][kCart.y[LD][id]]
                                                          * I[2][ib][kCart.z[LC][ic]][kCart.z[LD][id]];
-    }
+    });
 }
 
 // Algorithmic flop count of one primitive quartet of class (LA LB|LC LD) for

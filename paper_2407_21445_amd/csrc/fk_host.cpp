@@ -37,10 +37,19 @@ constexpr int ncart(int l) { return (l + 1) * (l + 2) / 2; }
 constexpr int kKrowLdsMax = 65536;
 // and with workgroups of eight waves (one workgroup per CU)
 constexpr int kKrowLdsMaxWide = 160 * 1024;
-// streams besides the caller's for the class launches of fk_build_jk
-// (measured: three streams in all gave C20H42 7.83 ms per build against 9.06 on
-// one, (H2O)64 238.6 against 244.2; four were slower on (H2O)64)
-constexpr int kAuxStreams = 2;
+// streams besides the caller's for the class launches of fk_build_jk, and how
+// many of them a build uses.  Classes of a small molecule leave most of the
+// chip idle, so four streams in all (the hardware queues of a process) beat
+// three: C20H42 7.65 ms per build against 8.05, organic batch of five 7.51
+// against 7.69, C6H14 1.10 against 1.14 (2.13 on one stream).  (H2O)64, whose
+// classes fill the chip, took 219.1 ms on four and 217.4 on three; with few
+// classes ((H2O)4 / STO-3G: six) the fourth stream's events cost more than it
+// gives (126 against 145 us).
+constexpr int kAuxStreams = 3;
+inline int aux_streams_used(size_t nclass, int64_t nmat)
+{
+    return nclass >= 12 && nmat * 8 <= (4 << 20) ? 3 : 2;
+}
 // Work tiles (fk_build_quartets): no tile takes more than kTileShare times the
 // serial work that one of two waves per SIMD would have if the class filled the
 // chip alone, or kMinTileFlops flops of one lane where that is more.  Classes
@@ -1099,8 +1108,11 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
                 FkGroup G;
                 G.begin = c->ket_off[P] + g.first;
                 G.len = g.second - g.first;
-                G.npp = 0;
-                for (int r = g.first; r < g.second; ++r) G.npp = std::max(G.npp, c->pr_npp[c->cls_list[P][r]]);
+                G.npp = G.npp_min = c->pr_npp[c->cls_list[P][g.first]];
+                for (int r = g.first; r < g.second; ++r) {
+                    G.npp = std::max(G.npp, c->pr_npp[c->cls_list[P][r]]);
+                    G.npp_min = std::min(G.npp_min, c->pr_npp[c->cls_list[P][r]]);
+                }
                 G.mol = c->sh_mol[c->pr_sa[c->cls_list[P][g.first]]];
                 G.base = (long long)c->ppT.size();
                 c->ppT.resize(c->ppT.size() + (size_t)G.npp * FK_NFLD * G.len);
@@ -1189,15 +1201,18 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
             // bra blocks: the class's pairs ordered by (first shell, G descending),
             // cut into runs of at most bmax pairs with the same first shell
             int bmax = std::max(1, std::min(sch.bb > 0 ? std::min(sch.bb, FK_MAX_BRA_BLOCK) : bra_block, qc.info.bra_block));
-            // block tasks (fk_screen_opts.block_tasks): the lane classes whose K rows
-            // fit the LDS without costing waves per CU -- the ket-outer ones with
-            // their four-wave workgroups, the others with workgroups of eight
-            // waves (one Rys table for eight waves) and as many bras per block as
-            // fit; decided here, since it may lower the bra block
+            // block tasks (fk_screen_opts.block_tasks): the classes whose K rows fit
+            // the LDS without costing waves per CU -- the team and wave kernels and
+            // the ket-outer lane kernels with their four-wave workgroups, the other
+            // lane kernels with workgroups of eight waves (one Rys table for eight
+            // waves) and as many bras per block as fit; decided here, since it may
+            // lower the bra block
             qc.krow_ncol = 0;
             qc.nw = 4;
-            if (qc.info.wave_per_quartet == 0 && (qc.info.ket_outer > 0 || qc.info.wide > 0) &&
-                opts.block_tasks == 0 && (sch.bt < 0 ? qc.info.ket_outer > 0 : sch.bt != 0)) {
+            const int kind = qc.info.wave_per_quartet;
+            const bool may_task = kind != 0 || ((qc.info.ket_outer > 0 || qc.info.wide > 0) &&
+                                                (sch.bt < 0 ? qc.info.ket_outer > 0 : sch.bt != 0));
+            if (may_task && opts.block_tasks == 0) {
                 int ncol = 0;
                 for (int m = 0; m < c->nmol; ++m)
                     ncol = std::max(ncol, c->krow_cnt[4 * m + qc.info.lc] +
@@ -1205,16 +1220,21 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
                 // waves per CU of a launch (0: the LDS does not fit); without a
                 // device the LDS bound alone decides
                 auto waves_cu = [&](int nw, int nbk, int nc) {
-                    const int lds = fk_kernels_jk_lds_bytes(P, Q, qc.bra_slot, nc, 0, nbk, nw);
-                    if (lds < 0 || lds > (nw == 4 ? kKrowLdsMax : kKrowLdsMaxWide)) return 0;
+                    const int lds = fk_kernels_jk_lds_bytes(P, Q, qc.bra_slot, nc, kind, nbk, nw);
+                    if (lds < 0 || lds > (nw == 4 && kind == 0 ? kKrowLdsMax : kKrowLdsMaxWide)) return 0;
                     if (!dev) return nw;
                     int nb = 0;
-                    if (fk_kernels_max_blocks(P, Q, lds, qc.engine, 0, nw, &nb) != 0) return 0;
+                    if (fk_kernels_max_blocks(P, Q, lds, qc.engine, kind, nw, &nb) != 0) return 0;
                     return nb * nw;
                 };
                 const int w0 = dev ? waves_cu(4, bmax, 0) : 1;
                 if (ncol > 0 && w0 > 0) {
-                    if (qc.info.ket_outer > 0) {
+                    if (kind != 0) {
+                        // with the whole bra block or not at all: (pp|pp) of
+                        // (H2O)64 takes 14.4 ms with rows and blocks of four,
+                        // 12.6 ms with blocks of eight and no rows
+                        if (waves_cu(4, bmax, ncol) >= w0) qc.krow_ncol = ncol;
+                    } else if (qc.info.ket_outer > 0) {
                         if (waves_cu(4, bmax, ncol) >= w0) qc.krow_ncol = ncol;
                     } else if (qc.engine == 0) {
                         for (int b = bmax; b >= 1; b = b / 2)
@@ -1760,7 +1780,7 @@ int build_jk_impl(fk_ctx *c, const double *D, double *J, double *K, unsigned fla
     // atomics; the other streams fork from and join the caller's.
     std::vector<hipStream_t> cls_st(c->qclasses.size(), st);
     int nfork = 0;
-    const int nst = 1 + (int)c->aux.size();
+    const int nst = 1 + std::min((int)c->aux.size(), aux_streams_used(c->qclasses.size(), (int64_t)nn / c->nmol));
     if (multi && nst > 1 && !c->timed && want_rys && c->qclasses.size() > 1) {
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         HIPCHK(c, hipStreamIsCapturing(st, &cs));
@@ -1975,7 +1995,7 @@ int fk_stats(fk_ctx *c, fk_stats_t *s)
         s->bra_block[i] = q.bra_block;
         s->kets_per_tile[i] = q.kets_per_tile;
         s->grid_fraction[i] = q.grid_frac;
-        s->block_tasks[i] = q.ntask;
+        s->block_tasks[i] = q.info.wave_per_quartet == 0 ? q.ntask : 0;
         s->waves_per_group[i] = q.nw;
         s->tiles[i] = q.ntile;
         s->team_size[i] = std::max(1, q.info.team_size);
@@ -2297,7 +2317,7 @@ int fk_autotune(fk_ctx *c, const double *D, unsigned flags, int reps, void *stre
             rep->kets_per_tile[i] = q.info.wave_per_quartet == 0 ? 64 : (sc.kt > 0 ? sc.kt : 2 * (q.info.wave_per_quartet == 3 ? 1 : 64 / std::max(1, q.info.team_size)));
             rep->grid_fraction[i] = sc.gf;
             rep->engine[i] = q.engine;
-            rep->block_tasks[i] = q.ntask > 0 ? 1 : 0;
+            rep->block_tasks[i] = q.info.wave_per_quartet == 0 && q.ntask > 0 ? 1 : 0;
             rep->lanes_per_quartet[i] = q.info.wave_per_quartet == 0 ? 1 : q.info.team_size;
             const auto s0 = start.find(q.P * NPC + q.Q);
             const fk_ctx::ClassSched sc0 = s0 == start.end() ? fk_ctx::ClassSched{} : s0->second;

@@ -47,6 +47,7 @@ struct FkGroup {
     int begin;      // first list position
     int len;        // number of pairs
     int npp;        // primitive pairs per pair (the largest; shorter pairs end in records with K = 0)
+    int npp_min;    // the smallest count of the run's pairs
     int mol;        // molecule of the run's pairs (0 unless the context holds a batch)
     long long base; // offset of the run's records in the transposed array
 };

@@ -85,20 +85,18 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-// Primitive quartets are counted per lane (lanes hold kets of different
-// primitive counts) and summed over the wave once, or before a lane's count
-// could overflow.
-__device__ __forceinline__ void count_flush(unsigned &lane_n, unsigned long long &sum)
+// Primitive quartets of one bra primitive with the kets of the wave's lanes
+// that are `mine` (of a team: its first lane; n of them), over the kets'
+// primitive pairs [p0, p1).  All lanes count the same where no ket of the group is padded;
+// holding a count per lane instead costs (ps|ss) a wave per SIMD (169 VGPRs).
+__device__ __forceinline__ unsigned ket_prims(const FkGroup &g, const int *__restrict lst_npp, int pos, int p0, int p1,
+                                              bool mine, unsigned n)
 {
-    unsigned long long v = lane_n;
+    if (g.npp_min >= p1) return n * (unsigned)(p1 - p0);
+    int v = mine ? max(min(lst_npp[pos], p1) - p0, 0) : 0;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    sum += v;
-    lane_n = 0;
-}
-__device__ __forceinline__ void count_check(unsigned &lane_n, unsigned long long &sum)
-{
-    if (__ballot(lane_n >= 1u << 31) != 0ull) count_flush(lane_n, sum);
+    return (unsigned)__builtin_amdgcn_readfirstlane(v);
 }
 
 __device__ __forceinline__ void wave_sync_lds()
@@ -109,7 +107,12 @@ __device__ __forceinline__ void wave_sync_lds()
 }
 
 __device__ __forceinline__ void atomic_add(double *p, double v) { unsafeAtomicAdd(p, v); }
-__device__ __forceinline__ void lds_add(double *p, double v) { unsafeAtomicAdd(p, v); }
+// p in LDS, by its own address space: an add to LDS and one to memory in the two
+// arms of a branch would otherwise be merged into one flat atomic
+__device__ __forceinline__ void lds_add(double *p, double v)
+{
+    (void)__builtin_amdgcn_ds_atomic_fadd_f64((__attribute__((address_space(3))) double *)p, v);
+}
 
 // FP64 atomic adds to device memory are served one 32-byte sector request per
 // lane unless lanes of the same instruction address the same sector (measured
@@ -326,14 +329,84 @@ __device__ __forceinline__ int nth_bit(unsigned long long m, int n)
 }
 
 
+// Block tasks: the workgroup's NW waves share the tiles of one bra block
+// (a, b_j) and sum its rows in LDS -- X_K[b_j, x], X_K[a, x] over the columns x
+// of the ket shells' functions, and X_J[a, b_j] -- which reach memory once per
+// task; SPLIT consecutive waves take a tile together.  An atomic add to memory
+// is a request to the fabric whatever its scope (2.4e10 requests/s, no L2 hit),
+// so per-quartet adds bound a kernel that makes more than a few of them; LDS
+// adds do not leave the CU.  Team and wave kernels, organic molecule of 324
+// functions (s to f): 3.3e8 requests per build without rows, 6.7e7 with them,
+// (ff|fs) 1.27 -> 0.62 ms, (ff|dp) 0.96 -> 0.63, the build 18.0 -> 16.1 ms.
+// Without tasks a unit is one tile per wave and there are no rows; both forms
+// share one copy of the tile code (two copies of (ps|ss) were 78 KB, more than
+// the instruction cache).
+template <int LA, int LB, int LC, int LD, int NW, int SPLIT = 1, class Tile>
+__device__ __forceinline__ void task_loop(const FkJKArgs &a, double *kr, bool tasks, int wave, bool wj, bool wk, Tile &&do_tile)
+{
+    constexpr int NA = fk::ncart(LA), NB = fk::ncart(LB);
+    const int nbk = a.krow_nbk, ncol = a.krow_ncol;
+    const int nkr = (nbk * NB + NA) * ncol + nbk * NA * NB;
+    constexpr int NG = NW / SPLIT;
+    const int units = tasks ? a.ntask : (a.ntiles + NG - 1) / NG;
+    for (int u = blockIdx.x; u < units; u += gridDim.x) {
+        const int2 tk = tasks ? a.tasks[u] : int2{u * NG, min(NG, a.ntiles - u * NG)};
+        if (tasks) {
+            for (int i = threadIdx.x; i < nkr; i += 64 * NW) kr[i] = 0.0;
+            __syncthreads();
+        }
+        for (int t = tk.x + wave / SPLIT; t < tk.x + tk.y; t += NG) do_tile(t);
+        if (!tasks) continue;
+        __syncthreads();
+        // the block's rows to memory: nonzero entries, consecutive threads
+        // on consecutive columns of a row
+        const FkTile t0 = a.tiles[tk.x];
+        const int mol = a.groups[t0.grp & ~FK_TILE_SAME].mol;
+        const int n = a.mol_nbf[mol];
+        const int *__restrict shbf = a.sh_bf + a.mol_sh0[mol];
+        const long long xoff = (long long)(blockIdx.x % FK_XCD_COPIES) * a.xcopy + a.mol_base[mol];
+        const FkBraBlock blk = a.blocks[t0.blk];
+        const int oa = shbf[a.pair_sa[a.blk_bra[blk.first]]];
+        const int cc = a.krow_cnt[4 * mol + LC];
+        const int ncm = cc + (LC != LD ? a.krow_cnt[4 * mol + LD] : 0);
+        const int *fnc = a.krow_fn + a.krow_off[4 * mol + LC];
+        const int *fnd = a.krow_fn + a.krow_off[4 * mol + LD];
+        if (wk) {
+            double *XK = a.XK + xoff;
+            const int nrow = blk.count * NB + NA;
+            for (int e = threadIdx.x; e < nrow * ncm; e += 64 * NW) {
+                const int r = e / ncm, x = e - r * ncm;
+                const int rr = r < blk.count * NB ? r : nbk * NB + (r - blk.count * NB);
+                const double v = kr[rr * ncol + x];
+                if (v == 0.0) continue;
+                const int row = r < blk.count * NB ? shbf[a.pair_sb[a.blk_bra[blk.first + r / NB]]] + r % NB
+                                                   : oa + (r - blk.count * NB);
+                const int fn = x < cc ? fnc[x] : fnd[x - cc];
+                atomic_add(&XK[(size_t)row * n + fn], v);
+            }
+        }
+        if (wj) {
+            double *XJ = a.XJ + xoff;
+            const double *kj = kr + (nbk * NB + NA) * ncol;
+            for (int e = threadIdx.x; e < blk.count * NA * NB; e += 64 * NW) {
+                const double v = kj[e];
+                if (v == 0.0) continue;
+                const int jb = e / (NA * NB), ab = e % (NA * NB);
+                const int ob = shbf[a.pair_sb[a.blk_bra[blk.first + jb]]];
+                atomic_add(&XJ[(size_t)(oa + ab / NB) * n + ob + ab % NB], v);
+            }
+        }
+        __syncthreads();
+    }
+}
+
 // Digestion of one bra's contracted quartets with the lane's ket (paper,
 // "Optimised GPU Implementation": the six Fock blocks of a quartet): scales the
 // integrals by the coincidence factors, forms X_J[a, b] (reduced over the wave
 // and added here) and the per-bra X_K[b, c], X_K[b, d] (flushed here), and adds
 // to the block sums X_K[a, c], X_K[a, d], X_J[c, d] of the caller.  Every lane
 // of the wave calls it (the flushes and the reduction are wave operations);
-// `active` marks the lanes whose quartet is computed.  With kr_b (block
-// tasks) the per-bra sums go to the workgroup's LDS rows instead of memory:
+// `active` marks the lanes whose quartet is computed.  With block tasks the per-bra sums go to the workgroup's LDS rows instead of memory:
 // X_K[b, x] to kr_b[ib * ncol + x] (x = colc + ic for c, cold + id for d) and
 // the wave's X_J[a, b] to kr_jab.
 template <int LA, int LB, int LC, int LD, typename R>
@@ -341,8 +414,7 @@ __device__ __forceinline__ void lpq_digest(R *acc, bool active, bool diag, int s
                                            int ob, int oc, int od, int n, const double *__restrict Ds,
                                            const double *dcd, double *kac, double *kad, double *jcd, double *XJ,
                                            double *XK, double *s_stage, int lane, bool wj, bool wk, bool &any,
-                                           double *kr_b = nullptr, int ncol = 0, int colc = 0, int cold = 0,
-                                           double *kr_jab = nullptr)
+                                           bool tasks, double *kr_b, int ncol, int colc, int cold, double *kr_jab)
 {
     using Q = fk::QClass<LA, LB, LC, LD>;
     constexpr int NA = Q::NA, NB = Q::NB, NC = Q::NC, ND = Q::ND, NOUT = Q::NOUT;
@@ -423,7 +495,7 @@ __device__ __forceinline__ void lpq_digest(R *acc, bool active, bool diag, int s
         }
     }
     if (wk) {
-        if (kr_b) {
+        if (tasks) {
             if (active) {
 #pragma unroll
                 for (int ib = 0; ib < NB; ++ib) {
@@ -444,7 +516,7 @@ __device__ __forceinline__ void lpq_digest(R *acc, bool active, bool diag, int s
         for (int ab = 0; ab < NA * NB; ++ab) {
             const double s = wave_sum(jab[ab]);
             if (lane == 0) {
-                if (kr_jab) lds_add(&kr_jab[ab], 2.0 * s);
+                if (tasks) lds_add(&kr_jab[ab], 2.0 * s);
                 else atomic_add(&XJ[(size_t)(oa + ab / NB) * n + ob + ab % NB], 2.0 * s);
             }
         }
@@ -464,8 +536,7 @@ __device__ __forceinline__ void lpq_digest(R *acc, bool active, bool diag, int s
 // waves per SIMD with some bytes spilled per lane than at one wave without
 // spills (their register demand is just above half of the file); the others
 // keep the compiler's own choice (measured: C20H42, (fs|ss) on the organic
-// batch).  (ps|ss) at three waves
-// spilled 124 bytes per lane, doubled its HBM traffic and gained nothing.
+// batch).
 template <int LA, int LB, int LC, int LD>
 struct LpqMinBlocks {
     static constexpr int value = 1;
@@ -473,6 +544,10 @@ struct LpqMinBlocks {
 template <>
 struct LpqMinBlocks<0, 0, 0, 0> {
     static constexpr int value = 4;
+};
+template <>
+struct LpqMinBlocks<1, 0, 0, 0> {  // 166 VGPRs, no spill; (H2O)64 34.2 ms, 41.3 at 171 (two waves)
+    static constexpr int value = 3;
 };
 template <>
 struct LpqMinBlocks<2, 0, 0, 0> {
@@ -589,16 +664,16 @@ __global__ void __launch_bounds__(64 * NW, (LpqBounds<LA, LB, LC, LD, NW>::value
     const int stg = a.ntask > 0 ? LpqStageTask<LA, LB, LC, LD>::value : LpqStage<LA, LB, LC, LD>::value;
     double *s_stage = s_dyn + rys_lds_size(Q::NR) + wave * stg;
     unsigned long long cq = 0, cp = 0;
-    unsigned lane_cp = 0;
 
     constexpr int NBK = LpqKetOuter<LA, LB, LC, LD>::value;
     // instantiations that take block tasks: the ket-outer ones and the wide ones
     constexpr bool TASKS = NBK > 0 || NW > FK_WAVES;
     // bras per block of the block tasks' rows (the class's bra block)
     const int nbk = a.krow_nbk;
-    // one tile (t) for this wave; kr: the workgroup's K rows of a block task, or null
-    auto do_tile = [&](int t, double *kr) {
-        if constexpr (!TASKS) kr = nullptr;
+    const bool tasks = TASKS && a.ntask > 0;
+    double *const kr = s_dyn + rys_lds_size(Q::NR) + NW * stg;  // the workgroup's K rows of a block task
+    // one tile (t) for this wave
+    auto do_tile = [&](int t) __attribute__((always_inline)) {
         const FkTile tile = a.tiles[t];
         const bool same = (tile.grp & FK_TILE_SAME) != 0;
         const FkGroup g = a.groups[tile.grp & ~FK_TILE_SAME];
@@ -621,10 +696,8 @@ __global__ void __launch_bounds__(64 * NW, (LpqBounds<LA, LB, LC, LD, NW>::value
         const int oc = shbf[sc], od = shbf[sd];
         const int sa = a.pair_sa[a.blk_bra[blk.first]];
         const int oa = shbf[sa];
-        // the ket's own primitive pairs in the tile's range (the rest is padding)
-        const int kpp = max(min(a.lst_npp[pos], p1) - p0, 0);
         int colc = 0, cold = 0;
-        if (kr) {
+        if (tasks) {
             const int *kcol = a.krow_col + a.mol_sh0[mol];
             colc = kcol[sc];
             cold = kcol[sd] + (LC != LD ? a.krow_cnt[4 * mol + LC] : 0);
@@ -669,10 +742,8 @@ __global__ void __launch_bounds__(64 * NW, (LpqBounds<LA, LB, LC, LD, NW>::value
                     bnpp[jb] = __builtin_amdgcn_readfirstlane(a.pair_npp[bra]);
                     const int nact = __popcll(__ballot(active));
                     cq += p0 == 0 ? nact : 0;
-                    if (active) {
-                        act |= 1u << jb;
-                        lane_cp += bnpp[jb] * kpp;
-                    }
+                    if (nact) cp += (unsigned long long)bnpp[jb] * ket_prims(g, a.lst_npp, pos, p0, p1, active, nact);
+                    if (active) act |= 1u << jb;
                 }
             }
             if (act) {
@@ -732,8 +803,8 @@ __global__ void __launch_bounds__(64 * NW, (LpqBounds<LA, LB, LC, LD, NW>::value
                 if (__ballot(active) == 0ull) continue;
                 lpq_digest<LA, LB, LC, LD, R>(acc, active, same && pos == bpos, sa, sb, sc, sd, oa, shbf[sb], oc,
                                               od, n, Ds, dcd, kac, kad, jcd, XJ, XK, s_stage, lane, wj, wk, any,
-                                              kr ? kr + jb * NB * a.krow_ncol : nullptr, a.krow_ncol, colc, cold,
-                                              kr ? kr + (nbk * NB + NA) * a.krow_ncol + jb * NA * NB : nullptr);
+                                              tasks, kr + jb * NB * a.krow_ncol, a.krow_ncol, colc, cold,
+                                              kr + (nbk * NB + NA) * a.krow_ncol + jb * NA * NB);
             }
         } else
         for (int jb = 0; jb < blk.count; ++jb) {
@@ -748,7 +819,7 @@ __global__ void __launch_bounds__(64 * NW, (LpqBounds<LA, LB, LC, LD, NW>::value
             if (mask == 0ull) continue;
             const int nact = __popcll(mask);
             cq += p0 == 0 ? nact : 0;
-            if (active) lane_cp += B.npp * kpp;
+            cp += (unsigned long long)B.npp * ket_prims(g, a.lst_npp, pos, p0, p1, active, nact);
 
             const int ppo = __builtin_amdgcn_readfirstlane(B.ppo);
             const int bnpp = __builtin_amdgcn_readfirstlane(B.npp);
@@ -798,13 +869,12 @@ __global__ void __launch_bounds__(64 * NW, (LpqBounds<LA, LB, LC, LD, NW>::value
             const bool diag = same && pos == bpos;
             lpq_digest<LA, LB, LC, LD, R>(acc, active, diag, sa, sb, sc, sd, oa, shbf[sb], oc, od, n, Ds, dcd, kac,
                                           kad, jcd, XJ, XK, s_stage, lane, wj, wk, any,
-                                          kr ? kr + jb * NB * a.krow_ncol : nullptr, a.krow_ncol, colc, cold,
-                                          kr ? kr + (nbk * NB + NA) * a.krow_ncol + jb * NA * NB : nullptr);
+                                          tasks, kr + jb * NB * a.krow_ncol, a.krow_ncol, colc, cold,
+                                          kr + (nbk * NB + NA) * a.krow_ncol + jb * NA * NB);
         }
-        count_check(lane_cp, cp);
         // block sums: a lane without work holds zeros, which are not added
         if (__ballot(any) != 0ull) {
-            if (wk && kr) {
+            if (wk && tasks) {
                 // X_K[a, c], X_K[a, d] into the block's a rows
                 double *kra = kr + nbk * NB * a.krow_ncol;
 #pragma unroll
@@ -824,62 +894,7 @@ __global__ void __launch_bounds__(64 * NW, (LpqBounds<LA, LB, LC, LD, NW>::value
             }
         }
     };
-    if (TASKS && a.ntask > 0) {
-        // block tasks: the K rows follow the table and the waves' stages
-        double *kr = s_dyn + rys_lds_size(Q::NR) + NW * stg;
-        const int ncol = a.krow_ncol;
-        const int nkr = (nbk * NB + NA) * ncol + nbk * NA * NB;
-        for (int task = blockIdx.x; task < a.ntask; task += gridDim.x) {
-            const int2 tk = a.tasks[task];
-            for (int i = threadIdx.x; i < nkr; i += 64 * NW) kr[i] = 0.0;
-            __syncthreads();
-            for (int t = tk.x + wave; t < tk.x + tk.y; t += NW) do_tile(t, kr);
-            __syncthreads();
-            // the block's rows to memory: nonzero entries, consecutive threads
-            // on consecutive columns of a row
-            const FkTile t0 = a.tiles[tk.x];
-            const int mol = a.groups[t0.grp & ~FK_TILE_SAME].mol;
-            const int n = a.mol_nbf[mol];
-            const int *__restrict shbf = a.sh_bf + a.mol_sh0[mol];
-            const long long xoff = (long long)(blockIdx.x % FK_XCD_COPIES) * a.xcopy + a.mol_base[mol];
-            const FkBraBlock blk = a.blocks[t0.blk];
-            const int oa = shbf[a.pair_sa[a.blk_bra[blk.first]]];
-            const int cc = a.krow_cnt[4 * mol + LC];
-            const int ncm = cc + (LC != LD ? a.krow_cnt[4 * mol + LD] : 0);
-            const int *fnc = a.krow_fn + a.krow_off[4 * mol + LC];
-            const int *fnd = a.krow_fn + a.krow_off[4 * mol + LD];
-            if (wk) {
-                double *XK = a.XK + xoff;
-                const int nrow = blk.count * NB + NA;
-                for (int e = threadIdx.x; e < nrow * ncm; e += 64 * NW) {
-                    const int r = e / ncm, x = e - r * ncm;
-                    const int rr = r < blk.count * NB ? r : nbk * NB + (r - blk.count * NB);
-                    const double v = kr[rr * ncol + x];
-                    if (v == 0.0) continue;
-                    const int row = r < blk.count * NB ? shbf[a.pair_sb[a.blk_bra[blk.first + r / NB]]] + r % NB
-                                                       : oa + (r - blk.count * NB);
-                    const int fn = x < cc ? fnc[x] : fnd[x - cc];
-                    atomic_add(&XK[(size_t)row * n + fn], v);
-                }
-            }
-            if (wj) {
-                double *XJ = a.XJ + xoff;
-                const double *kj = kr + (nbk * NB + NA) * ncol;
-                for (int e = threadIdx.x; e < blk.count * NA * NB; e += 64 * NW) {
-                    const double v = kj[e];
-                    if (v == 0.0) continue;
-                    const int jb = e / (NA * NB), ab = e % (NA * NB);
-                    const int ob = shbf[a.pair_sb[a.blk_bra[blk.first + jb]]];
-                    atomic_add(&XJ[(size_t)(oa + ab / NB) * n + ob + ab % NB], v);
-                }
-            }
-            __syncthreads();
-        }
-    } else {
-        const int nwt = gridDim.x * NW;
-        for (int t = blockIdx.x * NW + wave; t < a.ntiles; t += nwt) do_tile(t, nullptr);
-    }
-    count_flush(lane_cp, cp);
+    task_loop<LA, LB, LC, LD, NW>(a, kr, tasks, wave, wj, wk, do_tile);
     if (lane == 0 && (cq | cp)) {
         atomicAdd(&a.counters[0], cq);
         atomicAdd(&a.counters[1], cp);
@@ -905,8 +920,10 @@ struct TeamShape {
     static constexpr int QPW = 64 / TS;
     static constexpr int NVB = Q::NB * (Q::NC + Q::ND);   // team sums per bra
     static constexpr int NV = NVB > Q::NC * Q::ND ? NVB : Q::NC * Q::ND;
-    // per-wave LDS for the reductions (doubles), after the staged bra records
+    // per-wave LDS for the reductions (doubles), and with block tasks, where
+    // only X_J[c, d] is a team sum
     static constexpr int RED = QPW * NV + FK_TEAM_MAX_BLOCK * Q::NA * Q::NB;
+    static constexpr int RED_TASK = QPW * Q::NC * Q::ND;
 };
 
 
@@ -960,20 +977,23 @@ __global__ void __launch_bounds__(FK_BLOCK, (TpqMinBlocks<LA, LB, LC, LD>::value
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    double *s_team = s_dyn + rys_lds_size(Q::NR) + wave * TSh::RED;  // [QPW][NV] team sums
-    double *s_jab = s_team + QPW * NV;       // [block bra][NA * NB] wave sums of X_J[a, b]
-    const int nwt = gridDim.x * FK_WAVES;
+    const bool tasks = a.ntask > 0;
+    const int nvs = tasks ? NC * ND : NV;
+    double *s_team = s_dyn + rys_lds_size(Q::NR) + wave * (tasks ? TSh::RED_TASK : TSh::RED);  // [QPW][nvs] team sums
+    const int nbk = a.krow_nbk, ncol = a.krow_ncol;
     const int slot = lane / TS, comp = lane % TS;
     const bool lane_ok = slot < QPW;
     const int ia = (MODE == 1) ? comp : comp / NB;
     const int ib0 = (MODE == 1) ? 0 : comp % NB;
     const int ax[3] = {fk::kCart.x[LA][ia], fk::kCart.y[LA][ia], fk::kCart.z[LA][ia]};
     const int bx[3] = {fk::kCart.x[LB][ib0], fk::kCart.y[LB][ib0], fk::kCart.z[LB][ib0]};
-    double *tsum = s_team + (lane_ok ? slot : 0) * NV;
+    double *tsum = s_team + (lane_ok ? slot : 0) * nvs;
     unsigned long long cq = 0, cp = 0;
-    unsigned lane_cp = 0;  // counted by each team's first lane
 
-    for (int t = blockIdx.x * FK_WAVES + wave; t < a.ntiles; t += nwt) {
+    // the workgroup's rows of a block task
+    double *const kr = s_dyn + rys_lds_size(Q::NR) + FK_WAVES * TSh::RED_TASK;
+    // one tile (t) for this wave
+    auto do_tile = [&](int t) __attribute__((always_inline)) {
         const FkTile tile = a.tiles[t];
         const bool same = (tile.grp & FK_TILE_SAME) != 0;
         const FkGroup g = a.groups[tile.grp & ~FK_TILE_SAME];
@@ -982,6 +1002,11 @@ __global__ void __launch_bounds__(FK_BLOCK, (TpqMinBlocks<LA, LB, LC, LD>::value
         const int mol = g.mol;
         const int n = a.mol_nbf[mol], ns = a.mol_nsh[mol];
         const int *__restrict shbf = a.sh_bf + a.mol_sh0[mol];
+        const int *kcol = a.krow_col + a.mol_sh0[mol];
+        const int cold0 = tasks && LC != LD ? a.krow_cnt[4 * mol + LC] : 0;
+        // X_J[a, b] of each bra: the wave's own sums, or the task's
+        double *s_jab = tasks ? kr + (nbk * NB + NA) * ncol : s_team + QPW * NV;
+        double *kra = kr + (nbk * NB + ia) * ncol;
         const double *__restrict Ds = a.Ds + a.mol_base[mol];
         const double *__restrict Dsh = a.Dsh + a.mol_shbase[mol];
         const long long xoff = (long long)(blockIdx.x % FK_XCD_COPIES) * a.xcopy + a.mol_base[mol];
@@ -991,8 +1016,10 @@ __global__ void __launch_bounds__(FK_BLOCK, (TpqMinBlocks<LA, LB, LC, LD>::value
         const int sa = a.pair_sa[a.blk_bra[blk.first]];
         const int oa = shbf[sa];
         const size_t ra = (size_t)(oa + ia) * n;
-        wave_sync_lds();
-        for (int x = lane; x < blk.count * NA * NB; x += 64) s_jab[x] = 0.0;
+        if (!tasks) {
+            wave_sync_lds();
+            for (int x = lane; x < blk.count * NA * NB; x += 64) s_jab[x] = 0.0;
+        }
 
         // rounds of QPW kets, one per team
         for (int k0 = 0; k0 < tile.ket_count; k0 += QPW) {
@@ -1002,6 +1029,7 @@ __global__ void __launch_bounds__(FK_BLOCK, (TpqMinBlocks<LA, LB, LC, LD>::value
             const KetInfo Kt = load_ket(a, pos);
             const int sc = Kt.sc, sd = Kt.sd;
             const int oc = shbf[sc], od = shbf[sd];
+            const int colc = tasks ? kcol[sc] : 0, cold = tasks ? kcol[sd] + cold0 : 0;
             double kac[NC], kad[ND], jcd[NC * ND];
 #pragma unroll
             for (int ic = 0; ic < NC; ++ic) kac[ic] = 0.0;
@@ -1021,7 +1049,7 @@ __global__ void __launch_bounds__(FK_BLOCK, (TpqMinBlocks<LA, LB, LC, LD>::value
                 if (mask == 0ull) continue;
                 const int nact = __popcll(mask) / TS;
                 cq += p0 == 0 ? nact : 0;
-                if (active && comp == 0) lane_cp += B.npp * max(min(a.lst_npp[pos], p1) - p0, 0);
+                cp += (unsigned long long)B.npp * ket_prims(g, a.lst_npp, pos, p0, p1, active && comp == 0, nact);
                 const int ppo = __builtin_amdgcn_readfirstlane(B.ppo);
                 const int bnpp = __builtin_amdgcn_readfirstlane(B.npp);
                 R acc[NOL];
@@ -1040,10 +1068,16 @@ __global__ void __launch_bounds__(FK_BLOCK, (TpqMinBlocks<LA, LB, LC, LD>::value
                 const bool diag = same && pos == bpos;
                 const double fac = (sa == sb ? 0.5 : 1.0) * (sc == sd ? 0.5 : 1.0) * (diag ? 0.5 : 1.0);
                 const int ob = shbf[sb];
-                // team sums of X_K[b, c] and X_K[b, d] for this bra
-                if (lane_ok)
-                    for (int v = comp; v < NV; v += TS) tsum[v] = 0.0;
-                wave_sync_lds();
+                // X_K[b, c] and X_K[b, d] for this bra: team sums, or added to the
+                // task's rows
+                double *const sbc = tasks ? kr + jb * NB * ncol + colc : tsum;
+                double *const sbd = tasks ? kr + jb * NB * ncol + cold : tsum + NB * NC;
+                const int wbc = tasks ? ncol : NC, wbd = tasks ? ncol : ND;
+                if (!tasks) {
+                    if (lane_ok)
+                        for (int v = comp; v < NV; v += TS) tsum[v] = 0.0;
+                    wave_sync_lds();
+                }
                 if (active) {
                     any = true;
 #pragma unroll
@@ -1061,7 +1095,7 @@ __global__ void __launch_bounds__(FK_BLOCK, (TpqMinBlocks<LA, LB, LC, LD>::value
                                     sj += v * Ds[(size_t)(oc + ic) * n + od + id];
                                     jcd[ic * ND + id] += v * dab;
                                 }
-                            lds_add(&s_jab[jb * NA * NB + ia * NB + ib], sj);
+                            lds_add(&s_jab[jb * NA * NB + ia * NB + ib], tasks ? 2.0 * sj : sj);
                         }
                         if (wk) {
 #pragma unroll
@@ -1074,7 +1108,7 @@ __global__ void __launch_bounds__(FK_BLOCK, (TpqMinBlocks<LA, LB, LC, LD>::value
                                     kad[id] += v * Ds[rb + oc + ic];
                                     kbc += v * Ds[ra + od + id];
                                 }
-                                lds_add(&tsum[ib * NC + ic], kbc);
+                                lds_add(&sbc[ib * wbc + ic], kbc);
                             }
 #pragma unroll
                             for (int id = 0; id < ND; ++id) {
@@ -1082,11 +1116,12 @@ __global__ void __launch_bounds__(FK_BLOCK, (TpqMinBlocks<LA, LB, LC, LD>::value
 #pragma unroll
                                 for (int ic = 0; ic < NC; ++ic)
                                     kbd += fac * acc[(jj * NC + ic) * ND + id] * Ds[ra + oc + ic];
-                                lds_add(&tsum[NB * NC + ib * ND + id], kbd);
+                                lds_add(&sbd[ib * wbd + id], kbd);
                             }
                         }
                     }
                 }
+                if (tasks) continue;
                 wave_sync_lds();
                 if (active && wk)
                     for (int v = comp; v < TSh::NVB; v += TS) {
@@ -1100,13 +1135,19 @@ __global__ void __launch_bounds__(FK_BLOCK, (TpqMinBlocks<LA, LB, LC, LD>::value
             // end of the block for this round's kets: X_K[a, c], X_K[a, d] from
             // the lanes, X_J[c, d] as a team sum
             if (lane_ok)
-                for (int v = comp; v < NV; v += TS) tsum[v] = 0.0;
+                for (int v = comp; v < nvs; v += TS) tsum[v] = 0.0;
             wave_sync_lds();
             if (any && wk) {
 #pragma unroll
-                for (int ic = 0; ic < NC; ++ic) atomic_add(&XK[ra + oc + ic], kac[ic]);
+                for (int ic = 0; ic < NC; ++ic) {
+                    if (tasks) lds_add(&kra[colc + ic], kac[ic]);
+                    else atomic_add(&XK[ra + oc + ic], kac[ic]);
+                }
 #pragma unroll
-                for (int id = 0; id < ND; ++id) atomic_add(&XK[ra + od + id], kad[id]);
+                for (int id = 0; id < ND; ++id) {
+                    if (tasks) lds_add(&kra[cold + id], kad[id]);
+                    else atomic_add(&XK[ra + od + id], kad[id]);
+                }
             }
             if (any && wj) {
 #pragma unroll
@@ -1118,16 +1159,16 @@ __global__ void __launch_bounds__(FK_BLOCK, (TpqMinBlocks<LA, LB, LC, LD>::value
                     atomic_add(&XJ[(size_t)(oc + v / ND) * n + od + v % ND], 2.0 * tsum[v]);
             wave_sync_lds();
         }
-        count_check(lane_cp, cp);
         // X_J[a, b] of every bra of the block, summed over the tile's kets
+        if (tasks) return;
         for (int x = lane; x < blk.count * NA * NB; x += 64) {
             const int jb = x / (NA * NB), ab = x % (NA * NB);
             const int ob = shbf[a.pair_sb[a.blk_bra[blk.first + jb]]];
             const double v = s_jab[x];
             if (v != 0.0) atomic_add(&XJ[(size_t)(oa + ab / NB) * n + ob + ab % NB], 2.0 * v);
         }
-    }
-    count_flush(lane_cp, cp);
+    };
+    task_loop<LA, LB, LC, LD, FK_WAVES>(a, kr, tasks, wave, wj, wk, do_tile);
     if (lane == 0 && (cq | cp)) {
         atomicAdd(&a.counters[0], cq);
         atomicAdd(&a.counters[1], cp);
@@ -1165,7 +1206,7 @@ __global__ void __launch_bounds__(FK_BLOCK) k_jk_wpq(FkJKArgs a)
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int half = wave % SPLIT;                  // this wave's part of the group
-    const int nwt = gridDim.x * (FK_WAVES / SPLIT); // wave groups of the grid
+    const int ncol = a.krow_ncol;
     unsigned long long cq = 0, cp = 0;
 
     int iax[ITEMS][3], ibx[ITEMS][3], iab[ITEMS];
@@ -1180,7 +1221,10 @@ __global__ void __launch_bounds__(FK_BLOCK) k_jk_wpq(FkJKArgs a)
         ibx[k][0] = fk::kCart.x[LB][ib]; ibx[k][1] = fk::kCart.y[LB][ib]; ibx[k][2] = fk::kCart.z[LB][ib];
     }
 
-    for (int t = blockIdx.x * (FK_WAVES / SPLIT) + wave / SPLIT; t < a.ntiles; t += nwt) {
+    const bool tasks = a.ntask > 0;
+    double *const kr = s_dyn + rys_lds_size(Q::NR);  // the workgroup's rows of a block task
+    // one tile (t) for this group of waves
+    auto do_tile = [&](int t) __attribute__((always_inline)) {
         const FkTile tile = a.tiles[t];
         // team and wave kernels get blocks of one bra: the tile's kets are
         // exactly that bra's Schwarz prefix (and same-class triangle)
@@ -1208,7 +1252,9 @@ __global__ void __launch_bounds__(FK_BLOCK) k_jk_wpq(FkJKArgs a)
             if (a.dscreen) ok = ok && (B.G * K0.G * dmax_args(a, Dsh, ns, sa, sb, K0.sc, K0.sd) >= a.tau);
             live = __ballot(ok);
         }
-        if (live == 0ull) continue;
+        if (live == 0ull) return;
+        const int *kcol = a.krow_col + a.mol_sh0[mol];
+        const int cold0 = tasks && LC != LD ? a.krow_cnt[4 * mol + LC] : 0;
         const int ppo = __builtin_amdgcn_readfirstlane(B.ppo);
         const int bnpp = __builtin_amdgcn_readfirstlane(B.npp);
         while (live) {
@@ -1239,6 +1285,7 @@ __global__ void __launch_bounds__(FK_BLOCK) k_jk_wpq(FkJKArgs a)
             const bool diag = same && a.ket_list[pos] == bra;
             const double fac = (sa == sb ? 0.5 : 1.0) * (sc == sd ? 0.5 : 1.0) * (diag ? 0.5 : 1.0);
             const int oc = shbf[sc], od = shbf[sd];
+            const int colc = tasks ? kcol[sc] : 0, cold = tasks ? kcol[sd] + cold0 : 0;
             double jcd[NCD];
 #pragma unroll
             for (int o = 0; o < NCD; ++o) jcd[o] = 0.0;
@@ -1259,9 +1306,11 @@ __global__ void __launch_bounds__(FK_BLOCK) k_jk_wpq(FkJKArgs a)
                             sj += v[ic * ND + id] * Ds[(size_t)(oc + ic) * n + od + id];
                             jcd[ic * ND + id] += v[ic * ND + id] * dab;
                         }
-                    atomic_add(&XJ[(size_t)(oa + ia) * n + ob + ib], 2.0 * sj);
+                    if (tasks) lds_add(&kr[(NB + Q::NA) * ncol + iab[it]], 2.0 * sj);
+                    else atomic_add(&XJ[(size_t)(oa + ia) * n + ob + ib], 2.0 * sj);
                 }
                 if (!wk) continue;
+                double *krb = kr + ib * ncol, *kra = kr + (NB + ia) * ncol;
 #pragma unroll
                 for (int ic = 0; ic < NC; ++ic) {
                     double s1 = 0.0, s2 = 0.0;
@@ -1270,8 +1319,13 @@ __global__ void __launch_bounds__(FK_BLOCK) k_jk_wpq(FkJKArgs a)
                         s1 += v[ic * ND + id] * Ds[(size_t)(ob + ib) * n + od + id];
                         s2 += v[ic * ND + id] * Ds[(size_t)(oa + ia) * n + od + id];
                     }
-                    atomic_add(&XK[(size_t)(oa + ia) * n + oc + ic], s1);
-                    atomic_add(&XK[(size_t)(ob + ib) * n + oc + ic], s2);
+                    if (tasks) {
+                        lds_add(&kra[colc + ic], s1);
+                        lds_add(&krb[colc + ic], s2);
+                    } else {
+                        atomic_add(&XK[(size_t)(oa + ia) * n + oc + ic], s1);
+                        atomic_add(&XK[(size_t)(ob + ib) * n + oc + ic], s2);
+                    }
                 }
 #pragma unroll
                 for (int id = 0; id < ND; ++id) {
@@ -1281,8 +1335,13 @@ __global__ void __launch_bounds__(FK_BLOCK) k_jk_wpq(FkJKArgs a)
                         s1 += v[ic * ND + id] * Ds[(size_t)(ob + ib) * n + oc + ic];
                         s2 += v[ic * ND + id] * Ds[(size_t)(oa + ia) * n + oc + ic];
                     }
-                    atomic_add(&XK[(size_t)(oa + ia) * n + od + id], s1);
-                    atomic_add(&XK[(size_t)(ob + ib) * n + od + id], s2);
+                    if (tasks) {
+                        lds_add(&kra[cold + id], s1);
+                        lds_add(&krb[cold + id], s2);
+                    } else {
+                        atomic_add(&XK[(size_t)(oa + ia) * n + od + id], s1);
+                        atomic_add(&XK[(size_t)(ob + ib) * n + od + id], s2);
+                    }
                 }
             }
             if (wj) {
@@ -1293,7 +1352,9 @@ __global__ void __launch_bounds__(FK_BLOCK) k_jk_wpq(FkJKArgs a)
                 }
             }
         }
-    }
+    };
+    // the SPLIT waves of a group take the same tile
+    task_loop<LA, LB, LC, LD, FK_WAVES, SPLIT>(a, kr, tasks, wave, wj, wk, do_tile);
     if (lane == 0 && (cq | cp)) {
         atomicAdd(&a.counters[0], cq);
         atomicAdd(&a.counters[1], cp);
@@ -1485,12 +1546,24 @@ struct Disp {
                        : (const void *)&k_jk_tpq<LA, LB, LC, LD, KIND, double>;
         else return (const void *)&k_jk_wpq<LA, LB, LC, LD>;
     }
+    // doubles of a block task's rows
+    static int task_rows(int ncol, int nbk)
+    {
+        using C = fk::QClass<LA, LB, LC, LD>;
+        return (nbk * C::NB + C::NA) * ncol + nbk * C::NA * C::NB;
+    }
+    template <int MODE>
+    static int team_lds(int ncol, int nbk)
+    {
+        using T = TeamShape<LA, LB, LC, LD, MODE>;
+        return (int)sizeof(double) * (rys_lds_size(fk::QClass<LA, LB, LC, LD>::NR) +
+                                      FK_WAVES * (ncol > 0 ? T::RED_TASK : T::RED) + (ncol > 0 ? task_rows(ncol, nbk) : 0));
+    }
     static int lds_bytes(int bra_slot, int krow_ncol, int kind = KIND, int nbk = 0, int nw = FK_WAVES)
     {
         if constexpr (ALT) {
             if (kind == 1)
-                return (int)sizeof(double) *
-                       (rys_lds_size(fk::QClass<LA, LB, LC, LD>::NR) + FK_WAVES * TeamShape<LA, LB, LC, LD, 1>::RED);
+                return team_lds<1>(krow_ncol, nbk);
         }
         // the Rys segment, and per wave the team reductions (bra records are
         // read from memory by scalar loads: bra_slot needs no LDS); block
@@ -1500,10 +1573,8 @@ struct Disp {
         int extra = 0, rows = 0;
         if constexpr (KIND == 0)
             extra = krow_ncol > 0 ? LpqStageTask<LA, LB, LC, LD>::value : LpqStage<LA, LB, LC, LD>::value;
-        if constexpr (KIND == 1 || KIND == 2) extra = TeamShape<LA, LB, LC, LD, KIND>::RED;
-        if constexpr (KIND == 0) {
-            if (krow_ncol > 0) rows = (nbk * C::NB + C::NA) * krow_ncol + nbk * C::NA * C::NB;
-        }
+        if constexpr (KIND == 1 || KIND == 2) return team_lds<KIND>(krow_ncol, nbk);
+        if (krow_ncol > 0) rows = task_rows(krow_ncol, nbk);
         return (int)sizeof(double) * (rys_lds_size(C::NR) + nw * extra + rows);
     }
     static int launch_jk(const FkJKArgs *a, int grid, hipStream_t st)

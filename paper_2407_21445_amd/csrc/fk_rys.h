@@ -170,6 +170,65 @@ FK_HD void rys_roots(double T, const double *__restrict tab, double *u, double *
     fk::rys_roots_from<N, NEED_U, BRANCHLESS>(T, tab, tab + rys_seg_size(N), tab + rys_seg_size(N) + N, u, w);
 }
 
+// One root at a time, for the classes whose root loop is not unrolled: rys_at
+// finds the interval (or the asymptotic factors) of T once, rys_root_at
+// evaluates root r of it.  `tab` as for rys_roots.
+template <int N>
+struct RysAt {
+    const double *c, *gh;  // the interval's coefficients; y_i^2, then h_i
+    double x, sT, rT;
+    bool in_tab, any_tab;  // this lane below the switch; any lane of the wave
+};
+template <int N>
+FK_HD RysAt<N> rys_at(double T, const double *__restrict tab)
+{
+    RysAt<N> a;
+    a.in_tab = T < fk::rys_tswitch(N);
+#if defined(__HIP_DEVICE_COMPILE__)
+    a.any_tab = __ballot(a.in_tab) != 0ull;
+#else
+    a.any_tab = a.in_tab;
+#endif
+    const double Tc = a.in_tab ? T : 0.0;
+    int iv;
+    if constexpr (N <= RYS_UNI_NMAX) {
+        const double y = Tc * RYS_UNI_INVH;
+        iv = (int)y;
+        a.x = fma(2.0, y - (double)iv, -1.0);
+    } else {
+        int k = (int)(Tc * (1.0 / 16.0));
+        k = k < 3 ? k : 3;
+        const double ih = (double)(2 >> k) + (k == 3 ? 0.25 : 0.0) + (k == 2 ? 0.5 : 0.0);
+        const double y = (Tc - 16.0 * k) * ih;
+        const int j = (int)y;
+        iv = 64 - (64 >> k) + j;
+        a.x = 2.0 * (y - j) - 1.0;
+    }
+    a.c = tab + iv * fk::rys_stride(N);
+    a.gh = tab + rys_seg_size(N);
+    a.sT = fk::rys_rsqrt(a.in_tab ? 1.0 : T);
+    a.rT = a.sT * a.sT;
+    return a;
+}
+template <int N>
+FK_HD void rys_root_at(const RysAt<N> &a, int r, double &u, double &w)
+{
+    constexpr int NF = 2 * N;
+    u = a.gh[r] * a.rT;
+    w = a.gh[N + r] * a.sT;
+    if (a.any_tab) {
+        const double *c = a.c + 2 * r;
+        double vu = c[RYS_DEG * NF], vw = c[RYS_DEG * NF + 1];
+#pragma unroll
+        for (int k = RYS_DEG - 1; k >= 0; --k) {
+            vu = vu * a.x + c[k * NF];
+            vw = vw * a.x + c[k * NF + 1];
+        }
+        u = a.in_tab ? vu : u;
+        w = a.in_tab ? vw : w;
+    }
+}
+
 constexpr int rys_staged_offset(int n)
 {
     int o = 0;

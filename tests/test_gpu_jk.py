@@ -753,3 +753,28 @@ def test_cut_tiles_and_padded_groups(fk, torch, n, tau_prim):
     pp = sorted(int(s["sh_nprim"][i]) * int(s["sh_nprim"][j]) for i in range(ns) for j in range(i + 1))
     full = (sum(pp) ** 2 + sum(x * x for x in pp)) // 2
     assert st["prim_quartets"] == full if tau_prim == 0.0 else st["prim_quartets"] < full
+
+
+def test_team_and_wave_kernels_with_and_without_rows(fk, torch):
+    """Every class up to (ff|ff), unscreened: the team and wave kernels summing
+    a bra block's K rows in LDS (the default) and adding per quartet
+    (block_tasks off) both equal the oracle within 1e-10 and each other
+    (summation order only) within 1e-11, as one molecule and in a batch."""
+    s = _rand_sys(41, lmax=3, natom=4, kmax=2)
+    D = _rand_D(s["nbf"], 77)
+    Jo, Ko = oracle.jk(s, D)
+    res = {}
+    for bt in (True, False):
+        J, K, _ = _gpu_jk(fk, torch, s, D, tau=0.0, block_tasks=bt)
+        assert np.max(np.abs(J - Jo)) <= 1e-10 and np.max(np.abs(K - Ko)) <= 1e-10
+        res[bt] = (J, K)
+    for a, b in zip(res[True], res[False]):
+        assert np.max(np.abs(a - b)) <= 1e-11
+    t = _rand_sys(42, lmax=3, natom=2, kmax=3)
+    E = _rand_D(t["nbf"], 78)
+    c = fk.FockJK(0).set_system(wl.batch([dict(s, charge=0), dict(t, charge=0)]))
+    c.set_molecules(np.repeat([0, 1], [len(s["Z"]), len(t["Z"])])).build_quartets(tau=0.0)
+    J, K = c.build_jk(torch.tensor(np.concatenate([D.ravel(), E.ravel()]), device="cuda"), sync=True)
+    Jt, Kt = oracle.jk(t, E)
+    assert np.max(np.abs(J.cpu().numpy() - np.concatenate([Jo.ravel(), Jt.ravel()]))) <= 1e-10
+    assert np.max(np.abs(K.cpu().numpy() - np.concatenate([Ko.ravel(), Kt.ravel()]))) <= 1e-10
