@@ -14,10 +14,10 @@ struct FkGuessPair {
 
 extern "C" {
 // FP32 row-major matrices
-int fk_guess_mm(int ta, int tb, const float *A, int lda, const float *B, int ldb, float *C, float *A_out,
-                const float *bias, int M, int N, int K, void *stream);
-int fk_guess_silu_back(float *G, const float *Z, long long n, void *stream);
-int fk_guess_colsum(const float *G, int rows, int cols, float *out, void *stream);
+int fk_guess_layer(const float *X, const float *W, const float *bias, float *out, float *act, int M, int N, int K,
+                   void *stream);
+int fk_guess_layer_back(const float *G, const float *W, const float *Z, float *out, int M, int N, int K, void *stream);
+int fk_guess_layer_grad(const float *X, const float *G, float *gW, float *gb, int M, int N, int rows, void *stream);
 int fk_guess_mse_parts();
 int fk_guess_block_mse(const float *Y, const float *T, const int *shape, int rows, int width, double count, float *dY,
                        double *part, double *loss, void *stream);

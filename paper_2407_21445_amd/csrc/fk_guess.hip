@@ -5,12 +5,11 @@
 // SCF step then purifies.  The same library trains the network: forward,
 // backward, a masked squared-error loss and Adam are the kernels below.
 //
-// Everything here is FP32 except the scatter (FP64 rotation and output).  The
-// products are small (pairs x 256 x 256 per layer, well under a millisecond
-// per geometry), so a plain LDS-tiled FMA GEMM is used rather than MFMA.
+// Everything here is FP32 except the scatter (FP64 rotation and output).
 #include <hip/hip_runtime.h>
 
 #include <math.h>
+#include <stdint.h>
 
 #include <algorithm>
 
@@ -18,96 +17,149 @@
 
 namespace {
 
-constexpr int MT = 64;  // output tile (MT x MT) per workgroup
-constexpr int MK = 16;  // k-slab staged in LDS
-
-// C[M][N] = op(A)[M][K] op(B)[K][N] (+ bias, activation), row-major.
+// C[M][N] = op(A)[M][K] op(B)[K][N], row-major, FP32 products and sums on the
+// matrix cores (v_mfma_f32_16x16x4_f32).
 //   TA = 0: A[m][k] at A[m * lda + k];  TA = 1: A stored [K][M], A[k * lda + m]
 //   TB = 0: B[k][n] at B[k * ldb + n];  TB = 1: B stored [N][K], B[n * ldb + k]
-// epilogue: bias (may be null) added; if A_out is non-null it receives
-// SiLU(C) = C / (1 + exp(-C)) as well.  256 threads; thread (ty, tx) of a
-// 16 x 16 grid owns outputs (ty + 16 i, tx + 16 j), i, j < 4.
-template <int TA, int TB>
-__global__ void __launch_bounds__(256) k_mm(const float *__restrict A, int lda, const float *__restrict B, int ldb,
-                                            float *__restrict C, float *__restrict A_out, const float *__restrict bias,
-                                            int M, int N, int K)
+// Epilogues: EPI_BIAS adds bias (and writes SiLU(C) to A_out when that is not
+// null), EPI_SILU multiplies by SiLU'(Z), EPI_SUM writes C and, from the
+// workgroups of the first 16 rows, the column sums of B to bsum (the bias
+// gradient beside a weight gradient).
+//
+// A training step's products are small (2048 x 256 x 256) and chained, so what
+// counts is the time of one tile and how many run at once, not operand reuse: a
+// workgroup computes 16 x 32 outputs, operands coming from L1/L2 straight into
+// registers.  The forward layers give each tile to one wave, which multiplies k
+// by k: the matrix instruction adds its four products one after the other, so
+// an output is the same chain of FMAs as in a scalar loop (equal bit for bit),
+// and 2048 rows make 1024 waves.  The backward products split K over NW waves
+// (every NW-th 16-deep slice; the lane group g takes k = 4 g + j in step j, so
+// that a lane reads four consecutive k with one load) and add the waves' parts
+// in LDS in a fixed order: 16 waves turn a weight gradient's sum over 2048 rows,
+// which had 16 workgroups of 64 x 64 outputs, into 128 workgroups of 8 slices
+// per wave.  Forward, loss and backward at 2048 rows: 1.54 ms with vector FMAs
+// in 64 x 64 tiles, 0.13 ms with these (0.10 with the forward split as well,
+// whose sums round differently).
+constexpr int EPI_BIAS = 0, EPI_SILU = 1, EPI_SUM = 2;
+typedef float f4 __attribute__((ext_vector_type(4)));
+
+// four consecutive k (k0 .. k0 + 3) of row r of a matrix stored [rows][K]; zero outside
+template <bool VEC>
+__device__ __forceinline__ f4 load_k4(const float *__restrict X, int ld, int r, int rows, int k0, int K)
 {
-    __shared__ float As[MK][MT + 1];
-    __shared__ float Bs[MK][MT + 1];
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const int m0 = blockIdx.y * MT, n0 = blockIdx.x * MT;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += MK) {
+    f4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (r >= rows) return v;
+    const float *p = X + (size_t)r * ld + k0;
+    if (VEC) {  // ld and K are multiples of 4 and X is 16-byte aligned
+        if (k0 < K) v = *(const f4 *)p;
+    } else {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int idx = threadIdx.x + 256 * r;  // 0 .. 1023 = 64 x 16 elements
-            // A slab: element (m, k) = (idx >> 4, idx & 15) or, transposed, (idx & 63, idx >> 6)
-            int am, ak;
-            if (TA) { am = idx & 63; ak = idx >> 6; } else { am = idx >> 4; ak = idx & 15; }
-            const int gm = m0 + am, gk = k0 + ak;
-            float va = 0.0f;
-            if (gm < M && gk < K) va = TA ? A[(size_t)gk * lda + gm] : A[(size_t)gm * lda + gk];
-            As[ak][am] = va;
-            int bk, bn;
-            if (TB) { bn = idx >> 4; bk = idx & 15; } else { bk = idx >> 6; bn = idx & 63; }
-            const int hk = k0 + bk, hn = n0 + bn;
-            float vb = 0.0f;
-            if (hk < K && hn < N) vb = TB ? B[(size_t)hn * ldb + hk] : B[(size_t)hk * ldb + hn];
-            Bs[bk][bn] = vb;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < MK; ++k) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[k][ty + 16 * i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = Bs[k][tx + 16 * j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
+        for (int j = 0; j < 4; ++j)
+            if (k0 + j < K) v[j] = p[j];
     }
+    return v;
+}
+// the same of column c of a matrix stored [K][cols]
+__device__ __forceinline__ f4 load_k4t(const float *__restrict X, int ld, int c, int cols, int k0, int K)
+{
+    f4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (c >= cols) return v;
+    const float *p = X + (size_t)k0 * ld + c;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int m = m0 + ty + 16 * i;
-        if (m >= M) continue;
+    for (int j = 0; j < 4; ++j)
+        if (k0 + j < K) v[j] = p[(size_t)j * ld];
+    return v;
+}
+
+// k = k0 + 4 s + g for s = 0 .. 3: the order in which one wave multiplies k by k
+__device__ __forceinline__ f4 load_ordered(const float *__restrict X, size_t at, size_t step, bool in, int k, int K)
+{
+    f4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (!in) return v;
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+        if (k + 4 * s < K) v[s] = X[at + (size_t)(4 * s) * step];
+    return v;
+}
+
+template <int TA, int TB, int EPI, int NW, bool VEC>
+__global__ void __launch_bounds__(64 * NW) k_mm(const float *__restrict A, int lda, const float *__restrict B, int ldb,
+                                                float *__restrict C, float *__restrict A_out,
+                                                const float *__restrict aux, float *__restrict bsum, int M, int N,
+                                                int K)
+{
+    static_assert(NW > 1 || (!TA && !TB), "one wave per tile: plain operands");
+    __shared__ f4 part[NW][2][64];
+    __shared__ float bpart[NW][2][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int i = lane & 15, g = lane >> 4;
+    const int m0 = blockIdx.y * 16, n0 = blockIdx.x * 32;
+    f4 acc[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
+    float bs[2] = {0.0f, 0.0f};
+    auto loadA = [&](int k0) {
+        if constexpr (NW == 1) return load_ordered(A, (size_t)(m0 + i) * lda + k0 + g, 1, m0 + i < M, k0 + g, K);
+        return TA ? load_k4t(A, lda, m0 + i, M, k0 + 4 * g, K) : load_k4<VEC>(A, lda, m0 + i, M, k0 + 4 * g, K);
+    };
+    auto loadB = [&](int k0, int h) {
+        if constexpr (NW == 1) return load_ordered(B, (size_t)(k0 + g) * ldb + n0 + 16 * h + i, ldb, n0 + 16 * h + i < N, k0 + g, K);
+        return TB ? load_k4<VEC>(B, ldb, n0 + 16 * h + i, N, k0 + 4 * g, K)
+                  : load_k4t(B, ldb, n0 + 16 * h + i, N, k0 + 4 * g, K);
+    };
+    // the next slice's operands are in flight while this one's are multiplied
+    int k0 = 16 * wave;
+    f4 a = {}, b0 = {}, b1 = {};
+    if (k0 < K) { a = loadA(k0); b0 = loadB(k0, 0); b1 = loadB(k0, 1); }
+    while (k0 < K) {
+        const int kn = k0 + 16 * NW;
+        f4 an = {}, c0 = {}, c1 = {};
+        if (kn < K) { an = loadA(kn); c0 = loadB(kn, 0); c1 = loadB(kn, 1); }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int n = n0 + tx + 16 * j;
-            if (n >= N) continue;
-            float v = acc[i][j];
-            if (bias) v += bias[n];
-            C[(size_t)m * N + n] = v;
-            if (A_out) A_out[(size_t)m * N + n] = v / (1.0f + expf(-v));
+            acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b0[j], acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b1[j], acc[1], 0, 0, 0);
+        }
+        if (EPI == EPI_SUM) {
+            bs[0] += (b0[0] + b0[1]) + (b0[2] + b0[3]);
+            bs[1] += (b1[0] + b1[1]) + (b1[2] + b1[3]);
+        }
+        a = an; b0 = c0; b1 = c1; k0 = kn;
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        part[wave][h][lane] = acc[h];
+        if (EPI == EPI_SUM) bpart[wave][h][lane] = bs[h];
+    }
+    __syncthreads();
+    // the 2 x 64 lanes' quarters of the tile: column n0 + 16 h + (l & 15), rows m0 + 4 (l >> 4) + r
+    for (int x = threadIdx.x; x < 128; x += 64 * NW) {
+        const int h = x >> 6, l = x & 63;
+        f4 v = part[0][h][l];
+        for (int w = 1; w < NW; ++w) v += part[w][h][l];
+        const int n = n0 + 16 * h + (l & 15);
+        if (n >= N) continue;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int m = m0 + 4 * (l >> 4) + r;
+            if (m >= M) continue;
+            const size_t o = (size_t)m * N + n;
+            float c = v[r];
+            if (EPI == EPI_BIAS) {
+                c += aux[n];
+                if (A_out) A_out[o] = c / (1.0f + expf(-c));
+            } else if (EPI == EPI_SILU) {
+                // SiLU'(z) = s (1 + z (1 - s)), s = 1 / (1 + exp(-z))
+                const float z = aux[o], sg = 1.0f / (1.0f + expf(-z));
+                c *= sg * (1.0f + z * (1.0f - sg));
+            }
+            C[o] = c;
+        }
+        if (EPI == EPI_SUM && blockIdx.y == 0 && l < 16) {
+            float t = 0.0f;
+            for (int w = 0; w < NW; ++w)
+                t += (bpart[w][h][l] + bpart[w][h][l + 16]) + (bpart[w][h][l + 32] + bpart[w][h][l + 48]);
+            bsum[n] = t;
         }
     }
-}
-
-// G <- G * SiLU'(Z), SiLU'(z) = s (1 + z (1 - s)), s = 1 / (1 + exp(-z))
-__global__ void __launch_bounds__(256) k_silu_back(float *__restrict G, const float *__restrict Z, long long n)
-{
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const float z = Z[i];
-    const float s = 1.0f / (1.0f + expf(-z));
-    G[i] *= s * (1.0f + z * (1.0f - s));
-}
-
-// out[j] = sum_r G[r][j]: 64 columns per workgroup, 4 row phases reduced in
-// LDS (fixed order, so the result is deterministic).
-__global__ void __launch_bounds__(256) k_colsum(const float *__restrict G, int rows, int cols, float *__restrict out)
-{
-    __shared__ float part[4][64];
-    const int c = blockIdx.x * 64 + (threadIdx.x & 63), ph = threadIdx.x >> 6;
-    float s = 0.0f;
-    if (c < cols)
-        for (int r = ph; r < rows; r += 4) s += G[(size_t)r * cols + c];
-    part[ph][threadIdx.x & 63] = s;
-    __syncthreads();
-    if (ph == 0 && c < cols) out[c] = (part[0][threadIdx.x] + part[1][threadIdx.x]) + (part[2][threadIdx.x] + part[3][threadIdx.x]);
 }
 
 // Masked squared error over the (width x width) blocks of each row: entry
@@ -224,35 +276,44 @@ int ok() { return hipGetLastError() == hipSuccess ? 0 : -3; }
 
 unsigned nblk(long long n) { return (unsigned)((n + 255) / 256); }
 
+template <int TA, int TB, int EPI, int NW>
+int mm(const float *A, int lda, const float *B, int ldb, float *C, float *A_out, const float *aux, float *bsum, int M,
+       int N, int K, void *stream)
+{
+    if (M <= 0 || N <= 0) return 0;
+    const dim3 grid((N + 31) / 32, (M + 15) / 16);
+    // operands read along k take four values with one load where every row starts aligned
+    const bool ok_a = TA || (lda % 4 == 0 && (uintptr_t)A % 16 == 0), ok_b = !TB || (ldb % 4 == 0 && (uintptr_t)B % 16 == 0);
+    if (K % 4 == 0 && ok_a && ok_b)
+        hipLaunchKernelGGL((k_mm<TA, TB, EPI, NW, true>), grid, dim3(64 * NW), 0, (hipStream_t)stream, A, lda, B, ldb, C,
+                           A_out, aux, bsum, M, N, K);
+    else
+        hipLaunchKernelGGL((k_mm<TA, TB, EPI, NW, false>), grid, dim3(64 * NW), 0, (hipStream_t)stream, A, lda, B, ldb, C,
+                           A_out, aux, bsum, M, N, K);
+    return ok();
+}
+
 }  // namespace
 
 extern "C" {
 
-int fk_guess_mm(int ta, int tb, const float *A, int lda, const float *B, int ldb, float *C, float *A_out,
-                const float *bias, int M, int N, int K, void *stream)
+// out[M][N] = X[M][K] W[K][N] + bias; act (if not null) its SiLU
+int fk_guess_layer(const float *X, const float *W, const float *bias, float *out, float *act, int M, int N, int K,
+                   void *stream)
 {
-    if (M <= 0 || N <= 0) return 0;
-    const dim3 grid((N + MT - 1) / MT, (M + MT - 1) / MT);
-    const hipStream_t st = (hipStream_t)stream;
-    if (!ta && !tb) hipLaunchKernelGGL((k_mm<0, 0>), grid, dim3(256), 0, st, A, lda, B, ldb, C, A_out, bias, M, N, K);
-    else if (!ta && tb) hipLaunchKernelGGL((k_mm<0, 1>), grid, dim3(256), 0, st, A, lda, B, ldb, C, A_out, bias, M, N, K);
-    else if (ta && !tb) hipLaunchKernelGGL((k_mm<1, 0>), grid, dim3(256), 0, st, A, lda, B, ldb, C, A_out, bias, M, N, K);
-    else return -1;
-    return ok();
+    return mm<0, 0, EPI_BIAS, 1>(X, K, W, N, out, act, bias, nullptr, M, N, K, stream);
 }
 
-int fk_guess_silu_back(float *G, const float *Z, long long n, void *stream)
+// out[M][N] = (G[M][K] W^T) SiLU'(Z), W stored [N][K]
+int fk_guess_layer_back(const float *G, const float *W, const float *Z, float *out, int M, int N, int K, void *stream)
 {
-    if (n <= 0) return 0;
-    hipLaunchKernelGGL(k_silu_back, dim3(nblk(n)), dim3(256), 0, (hipStream_t)stream, G, Z, n);
-    return ok();
+    return mm<0, 1, EPI_SILU, 4>(G, K, W, K, out, nullptr, Z, nullptr, M, N, K, stream);
 }
 
-int fk_guess_colsum(const float *G, int rows, int cols, float *out, void *stream)
+// gW[M][N] = X^T G and gb[N] = column sums of G, X stored [rows][M], G [rows][N]
+int fk_guess_layer_grad(const float *X, const float *G, float *gW, float *gb, int M, int N, int rows, void *stream)
 {
-    if (cols <= 0) return 0;
-    hipLaunchKernelGGL(k_colsum, dim3((cols + 63) / 64), dim3(256), 0, (hipStream_t)stream, G, rows, cols, out);
-    return ok();
+    return mm<1, 0, EPI_SUM, 16>(X, M, G, N, gW, nullptr, nullptr, gb, M, N, rows, stream);
 }
 
 int fk_guess_mse_parts() { return 480; }

@@ -3777,11 +3777,11 @@ int fk_mlp_forward(const fk_mlp *m, const float *X, int n, float *Y, float *work
         const int din = m->dims[k], dout = m->dims[k + 1];
         if (k + 1 < m->nlayer) {
             float *Z = wp, *A = wp + (size_t)n * dout;
-            if (fk_guess_mm(0, 0, in, din, m->W[k], dout, Z, A, m->b[k], n, dout, din, stream)) return FK_ERR_HIP;
+            if (fk_guess_layer(in, m->W[k], m->b[k], Z, A, n, dout, din, stream)) return FK_ERR_HIP;
             in = A;
             wp += 2 * (size_t)n * dout;
         } else {
-            if (fk_guess_mm(0, 0, in, din, m->W[k], dout, Y, nullptr, m->b[k], n, dout, din, stream)) return FK_ERR_HIP;
+            if (fk_guess_layer(in, m->W[k], m->b[k], Y, nullptr, n, dout, din, stream)) return FK_ERR_HIP;
         }
     }
     return FK_OK;
@@ -3807,12 +3807,10 @@ int fk_mlp_backward(const fk_mlp *m, const float *X, int n, float *work, float *
     for (int k = L - 1; k >= 0; --k) {
         const int din = m->dims[k], dout = m->dims[k + 1];
         const float *Ain = k == 0 ? X : work + zoff[k - 1] + (size_t)n * din;
-        if (fk_guess_mm(1, 0, Ain, din, G, dout, grad->W[k], nullptr, nullptr, din, dout, n, stream)) return FK_ERR_HIP;
-        if (fk_guess_colsum(G, n, dout, grad->b[k], stream)) return FK_ERR_HIP;
+        if (fk_guess_layer_grad(Ain, G, grad->W[k], grad->b[k], din, dout, n, stream)) return FK_ERR_HIP;
         if (k > 0) {
             float *H = hbuf[k & 1];
-            if (fk_guess_mm(0, 1, G, dout, m->W[k], dout, H, nullptr, nullptr, n, din, dout, stream)) return FK_ERR_HIP;
-            if (fk_guess_silu_back(H, work + zoff[k - 1], (long long)n * din, stream)) return FK_ERR_HIP;
+            if (fk_guess_layer_back(G, m->W[k], work + zoff[k - 1], H, n, din, dout, stream)) return FK_ERR_HIP;
             G = H;
         }
     }

@@ -198,3 +198,31 @@ def test_trained_guess_beats_sad_on_held_out(fk):
         its_nn.append(r1["iterations"])
     assert all(x <= y for x, y in zip(its_nn, its_sad)), (its_sad, its_nn)
     assert np.mean(its_nn) < np.mean(its_sad), (its_sad, its_nn)
+
+
+@pytest.mark.parametrize("n,dims", [(17, [4, 16, 33]), (16, [20, 32, 225]), (2049, [7, 45, 18]), (1000, [192, 256, 256, 225])])
+def test_mlp_ragged_layers_match_oracle(fk, torch, n, dims):
+    """Widths and row counts at the edges of the 16 x 32 tiles and 16-deep
+    slices, aligned for four-wide loads and not.  An FP32 sum of m products
+    errs by at most m 2^-24 sum|ab|; relative to the largest output that is
+    below m 6e-8 sqrt(m) for these random operands, at most 6e-3 at m = 2049;
+    sums are split 16 ways, and the existing bound 1e-4 holds for all."""
+    Ws, bs = _rand_mlp(21, dims)
+    rng = np.random.default_rng(22)
+    X = rng.normal(size=(n, dims[0])).astype(np.float32)
+    dY = rng.normal(size=(n, dims[-1])).astype(np.float32)
+    Wd, bd = _to(torch, Ws), _to(torch, bs)
+    Xd, Gd = _to(torch, [X, dY])
+    work = fk.mlp_work(Wd, n)
+    Y = fk.mlp_forward(Wd, bd, Xd, work)
+    gW = [torch.full_like(W, 7.0) for W in Wd]
+    gb = [torch.full_like(b, 7.0) for b in bd]
+    fk.mlp_backward(Wd, bd, Xd, work, Gd, gW, gb)
+    torch.cuda.synchronize()
+    W64, b64 = [W.astype(float) for W in Ws], [b.astype(float) for b in bs]
+    Yo, pre = og.mlp_forward(W64, b64, X.astype(float))
+    dWo, dbo = og.mlp_backward(W64, b64, X.astype(float), pre, dY.astype(float))
+    assert np.max(np.abs(Y.cpu().numpy() - Yo)) <= 1e-5 * np.max(np.abs(Yo))
+    for k in range(len(dims) - 1):
+        assert np.max(np.abs(gW[k].cpu().numpy() - dWo[k])) <= 1e-4 * np.max(np.abs(dWo[k]))
+        assert np.max(np.abs(gb[k].cpu().numpy() - dbo[k])) <= 1e-4 * np.max(np.abs(dbo[k]))
