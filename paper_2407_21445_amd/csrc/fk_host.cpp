@@ -173,6 +173,7 @@ struct fk_ctx {
     // J engine (built on first use after fk_build_quartets)
     bool jeng_valid = false;
     std::vector<int64_t> jeng_toff;               // tiles of bucket LP * (FK_JENG_MAX_LP + 1) + LQ
+    std::vector<double> jeng_work;                // estimated flops of each bucket
     DevBuf<FkJengTile> d_jeng_tiles;
     DevBuf<long long> d_jp_off, d_dq_base;
     DevBuf<int> d_pos_grp;
@@ -1595,9 +1596,17 @@ int ensure_jeng(fk_ctx *c)
                         }
                         cnt = lo - g.first;
                     }
-                    for (int kk = 0; kk < cnt; kk += 64)
-                        tl.push_back(FkJengTile{bra, c->ket_off[Q] + g.first + kk, std::min(64, cnt - kk),
-                                                c->cls_group0[Q] + (int)gi});
+                    const int grp = c->cls_group0[Q] + (int)gi;
+                    for (int kk = 0; kk < cnt; kk += 64) {
+                        FkJengTile t{};
+                        t.bra = bra;
+                        t.ket_begin = c->ket_off[Q] + g.first + kk;
+                        t.grp = grp;
+                        t.ket_count = (unsigned char)std::min(64, cnt - kk);
+                        t.i1 = (unsigned char)c->pr_npp[bra];
+                        t.j1 = (unsigned char)c->groups[grp].npp;
+                        tl.push_back(t);
+                    }
                 }
             }
             (void)lq;
@@ -1605,11 +1614,35 @@ int ensure_jeng(fk_ctx *c)
     }
     std::vector<FkJengTile> all;
     c->jeng_toff.assign(kJengNB * kJengNB + 1, 0);
+    c->jeng_work.assign(kJengNB * kJengNB, 0.0);
     for (int k = 0; k < kJengNB * kJengNB; ++k) {
-        auto &tl = bucket[k];
-        auto cost = [&](const FkJengTile &t) {
-            return (long long)c->pr_npp[t.bra] * c->groups[t.grp].npp * t.ket_count;
-        };
+        // tiles of bounded serial work, as for the quartet classes: cut over the
+        // bra's primitive pairs (their J_p are separate sums), then the kets'
+        const int lp = k / kJengNB, lq = k % kJengNB, nr = (lp + lq) / 2 + 1;
+        const double f_prim = 60.0 + nr * (36.0 + 3.0 * (lp + lq) * 4 + 4.0 * nherm_host(lp + lq)) +
+                              2.0 * nherm_host(lp) * nherm_host(lq);
+        const double f_bra = kBraOverheadFlops + 20.0 * nherm_host(lp);
+        double total = 0;
+        for (const FkJengTile &t : bucket[k]) total += t.i1 * (f_bra + f_prim * t.j1);
+        c->jeng_work[k] = 64.0 * total;
+        const double t_max = std::max(kMinTileFlops, kTileShare * total / (8.0 * std::max(c->ncu, 1)));
+        std::vector<FkJengTile> tl;
+        tl.reserve(bucket[k].size());
+        for (const FkJengTile &t : bucket[k]) {
+            const double one = f_bra + f_prim * t.j1;  // one bra primitive pair
+            const int step = (int)std::max(1.0, std::min<double>(t.i1, t_max / one));
+            const int parts = step > 1 || one <= t_max ? 1 : (int)std::min<double>(t.j1, std::ceil(one / t_max));
+            for (int i = 0; i < t.i1; i += step)
+                for (int s = 0; s < parts; ++s) {
+                    FkJengTile u = t;
+                    u.i0 = (unsigned char)i;
+                    u.i1 = (unsigned char)std::min<int>(i + step, t.i1);
+                    u.j0 = (unsigned char)(t.j1 * s / parts);
+                    u.j1 = (unsigned char)(t.j1 * (s + 1) / parts);
+                    tl.push_back(u);
+                }
+        }
+        auto cost = [&](const FkJengTile &t) { return (long long)(t.i1 - t.i0) * (t.j1 - t.j0) * t.ket_count; };
         std::stable_sort(tl.begin(), tl.end(), [&](const FkJengTile &x, const FkJengTile &y) { return cost(x) > cost(y); });
         c->jeng_toff[k] = (int64_t)all.size();
         all.insert(all.end(), tl.begin(), tl.end());
@@ -1668,8 +1701,10 @@ int ensure_dfit(fk_ctx *c)
     return FK_OK;
 }
 
-// J by the J engine into X_J (block per bra pair; see k_jeng_jab).
-int jeng_build(fk_ctx *c, const JKBufs &b, hipStream_t st)
+// J by the J engine into X_J (block per bra pair; see k_jeng_jab), in three
+// parts: D_q of every ket class, J_p of one bucket of bra and ket momenta (any
+// order and stream between the other two), J_ab.
+int jeng_begin(fk_ctx *c, const JKBufs &b, hipStream_t st)
 {
     if (fk_kernels_launch_fill(c->d_jp.p, (long long)c->jp_n, st)) return fail(c, FK_ERR_HIP, "fill kernel launch failed");
     const int nlist = (int)c->ket_list_all.size();
@@ -1685,6 +1720,14 @@ int jeng_build(fk_ctx *c, const JKBufs &b, hipStream_t st)
         if (fk_jeng_launch_dq(c->sh_l[c->pr_sa[p0]], c->sh_l[c->pr_sb[p0]], &a, st))
             return fail(c, FK_ERR_HIP, "J engine: D_q kernel launch failed");
     }
+    return FK_OK;
+}
+
+int jeng_bucket(fk_ctx *c, const JKBufs &b, int k, hipStream_t st)
+{
+    const int64_t nt = c->jeng_toff[k + 1] - c->jeng_toff[k];
+    if (nt <= 0) return FK_OK;
+    const int lp = k / kJengNB, lq = k % kJengNB;
     FkJengArgs a;
     a.pair_ppoff = c->d_pr_ppoff.p; a.pair_npp = c->d_pr_npp.p; a.pair_G = c->d_pr_G.p; a.pp = c->d_pp.p;
     a.jp_off = c->d_jp_off.p; a.jp = c->d_jp.p; a.ppT = c->d_ppT.p; a.groups = c->d_groups.p;
@@ -1692,17 +1735,16 @@ int jeng_build(fk_ctx *c, const JKBufs &b, hipStream_t st)
     a.dq_base = c->d_dq_base.p; a.dq = c->d_dq.p; a.Dsh = b.Dsh; a.ns = c->nshell;
     a.dscreen = c->opts.density_screen && c->opts.tau > 0 ? 1 : 0;
     a.tau = c->opts.tau * c->dscreen_scale;
-    for (int lp = 0; lp < kJengNB; ++lp)
-        for (int lq = 0; lq < kJengNB; ++lq) {
-            const int k = lp * kJengNB + lq;
-            const int64_t nt = c->jeng_toff[k + 1] - c->jeng_toff[k];
-            if (nt <= 0) continue;
-            a.tiles = c->d_jeng_tiles.p + c->jeng_toff[k];
-            a.ntiles = nt;
-            a.rys_tab = c->d_rys.p + rys_staged_offset((lp + lq) / 2 + 1);
-            const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((nt + 3) / 4, 8LL * std::max(c->ncu, 1)));
-            if (fk_jeng_launch_jp(lp, lq, &a, grid, st)) return fail(c, FK_ERR_HIP, "J engine: J_p kernel launch failed");
-        }
+    a.tiles = c->d_jeng_tiles.p + c->jeng_toff[k];
+    a.ntiles = nt;
+    a.rys_tab = c->d_rys.p + rys_staged_offset((lp + lq) / 2 + 1);
+    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((nt + 3) / 4, 8LL * std::max(c->ncu, 1)));
+    if (fk_jeng_launch_jp(lp, lq, &a, grid, st)) return fail(c, FK_ERR_HIP, "J engine: J_p kernel launch failed");
+    return FK_OK;
+}
+
+int jeng_end(fk_ctx *c, const JKBufs &b, hipStream_t st)
+{
     for (int P = 0; P < NPC; ++P) {
         if (c->cls_list[P].empty()) continue;
         FkJengJabArgs j;
@@ -1773,15 +1815,17 @@ int build_jk_impl(fk_ctx *c, const double *D, double *J, double *K, unsigned fla
     if (jeng && (want_rys & FK_WANT_K) && c->opts.tau_k > 0 &&
         fk_kernels_launch_dfit(Dd, c->nbf, c->d_bf_atom.p, c->d_atom_xyz.p, c->dfit_dr, c->d_dfit_bins.p, c->d_dfit.p, st))
         return fail(c, FK_ERR_HIP, "density-bound kernel launch failed");
-    // Several streams: the classes, largest estimated work first, each go to
+    if (jeng && (rcj = jeng_begin(c, b, st))) return rcj;
+    // Several streams: the classes (and with the J engine its J_p buckets, which
+    // only add into J_p), largest estimated work first, each go to
     // the stream with the least work so far, so that the long, latency-bound
     // launches of the small high-L classes run beside the large ones instead
     // of leaving most of the GPU idle.  The classes only add into X with
     // atomics; the other streams fork from and join the caller's.
-    std::vector<hipStream_t> cls_st(c->qclasses.size(), st);
+    std::vector<hipStream_t> cls_st(c->qclasses.size(), st), jp_st(kJengNB * kJengNB, st);
     int nfork = 0;
     const int nst = 1 + std::min((int)c->aux.size(), aux_streams_used(c->qclasses.size(), (int64_t)nn / c->nmol));
-    if (multi && nst > 1 && !c->timed && want_rys && c->qclasses.size() > 1) {
+    if (multi && nst > 1 && !c->timed && (want_rys || jeng) && c->qclasses.size() > 1) {
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         HIPCHK(c, hipStreamIsCapturing(st, &cs));
         if (cs == hipStreamCaptureStatusNone) {
@@ -1800,12 +1844,19 @@ int build_jk_impl(fk_ctx *c, const double *D, double *J, double *K, unsigned fla
                         if (c->qclasses[j].P == c->qclasses[i].P && c->qclasses[j].Q == c->qclasses[i].Q &&
                             c->qclasses[j].prec == 0)
                             wk[i] = wk[j];
+            if (want_rys == 0) std::fill(wk.begin(), wk.end(), 0.0);
+            const size_t ncls = wk.size();
+            if (jeng) {
+                wk.insert(wk.end(), c->jeng_work.begin(), c->jeng_work.end());
+                ord.resize(wk.size());
+                std::iota(ord.begin(), ord.end(), 0);
+            }
             auto work = [&](size_t i) { return wk[i]; };
             std::stable_sort(ord.begin(), ord.end(), [&](size_t x, size_t y) { return work(x) > work(y); });
             std::vector<double> wsum(nst, 0.0);
             for (size_t i : ord) {
                 const int k = (int)(std::min_element(wsum.begin(), wsum.end()) - wsum.begin());
-                cls_st[i] = k == 0 ? st : c->aux[k - 1];
+                (i < ncls ? cls_st[i] : jp_st[i - ncls]) = k == 0 ? st : c->aux[k - 1];
                 wsum[k] += work(i);
             }
             HIPCHK(c, hipEventRecord(c->ev_fork, st));
@@ -1896,11 +1947,14 @@ int build_jk_impl(fk_ctx *c, const double *D, double *J, double *K, unsigned fla
             return fail(c, FK_ERR_HIP, "J/K kernel launch failed for class (%d|%d)", qc.P, qc.Q);
         if (c->timed) HIPCHK(c, hipEventRecord(c->ev[2 * i + 1], st));
     }
-    if (jeng && (rcj = jeng_build(c, b, st))) return rcj;
+    if (jeng)
+        for (int k = 0; k < kJengNB * kJengNB; ++k)
+            if ((rcj = jeng_bucket(c, b, k, jp_st[k]))) return rcj;
     for (int k = 0; k < nfork; ++k) {
         HIPCHK(c, hipEventRecord(c->ev_join[k], c->aux[k]));
         HIPCHK(c, hipStreamWaitEvent(st, c->ev_join[k], 0));
     }
+    if (jeng && (rcj = jeng_end(c, b, st))) return rcj;
     if (fk_kernels_launch_finalize(b.X, b.X + nn, b.xcopy, b.ncopy, c->d_bf_scale.p, &ma, Jd, Kd, st))
         return fail(c, FK_ERR_HIP, "finalize kernel launch failed");
     c->stats_pending = true;

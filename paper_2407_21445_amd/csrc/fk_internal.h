@@ -186,10 +186,12 @@ int fk_kernels_launch_fill(double *p, long long n, void *stream);
 int fk_kernels_debug_host(int P, int Q, const int *pair_ppoff, const int *pair_npp, const double *pair_AB,
                           const double *pp, const int *quartets, int nq, double *out, int engine);
 // ---- J engine (McMurchie-Davidson; paper, "J matrix implementation") ----
-// Work tile of the J_p kernel: one bra pair against up to 64 kets of one
-// primitive-count group (consecutive list positions).
+// Work tile of the J_p kernel: primitive pairs [i0, i1) of one bra pair against
+// up to 64 kets of one primitive-count group (consecutive list positions), of
+// which it sums the primitive pairs [j0, j1).
 struct FkJengTile {
-    int bra, ket_begin, ket_count, grp;
+    int bra, ket_begin, grp;
+    unsigned char ket_count, i0, i1, j0, j1, pad[3];
 };
 // Hermite-contracted ket density D_q and the J_p accumulation.
 struct FkJengArgs {
