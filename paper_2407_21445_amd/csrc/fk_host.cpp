@@ -2737,10 +2737,16 @@ struct ScfWork {
     DevBuf<double> Dlast, dD, Jacc, Kacc;  // incremental builds
     DevBuf<double> Pn, ev, wk;             // canonical orthogonaliser: projector onto the dropped directions
     DevBuf<int> info;
+    DevBuf<double> dots; // DIIS inner products of one vector
+    DevBuf<double> ptr;  // purification on the device: traces and step states
+    DevBuf<int> pst;
     int ndrop = 0;
     std::vector<DevBuf<double>> ringF, ringE;
     ~ScfWork()
     {
+        dev_free(ptr);
+        dev_free(dots);
+        dev_free(pst);
         for (auto *b : {&h, &X, &Xi, &D, &Do, &J, &K, &F, &Fo, &G, &E, &T1, &T2, &T3, &part, &scal, &Dlast, &dD, &Jacc, &Kacc,
                         &Pn, &ev, &wk})
             dev_free(*b);
@@ -2852,6 +2858,30 @@ int scf_purify(ScfWork &w, int nocc, int *steps)
     const int n = w.n;
     double gb[2];
     int rc;
+    if (n <= fk_scf_purify_max_n()) {
+        // small matrices: the steps decide on the device and the host looks
+        // every few launches whether they are done (typically 25 to 35)
+        constexpr int kMax = 301;
+        const int ns = fk_scf_purify_state_ints();
+        if (!w.pst.p && ((rc = dev_upload<int>(w.c, w.pst, nullptr, (size_t)kMax * ns)) ||
+                         (rc = dev_upload<double>(w.c, w.ptr, nullptr, (size_t)fk_scf_purify_trace_doubles(kMax)))))
+            return rc;
+        double *buf[4] = {w.T1.p, w.T2.p, w.T3.p, w.G.p};
+        SCFCHK(w, fk_scf_reduce(w.Fo.p, nullptr, n, 3, w.part.p, w.scal.p, 0, w.st));
+        int done[3] = {0, 0, 0};
+        for (int s = 0; s < kMax && !done[1];) {
+            const int last = std::min(kMax, s == 0 ? 32 : s + 8);
+            SCFCHK(w, fk_scf_purify_steps(w.Fo.p, buf, n, nocc, s, last, w.scal.p, w.ptr.p, w.pst.p, w.st));
+            s = last;
+            HIPCHK(w.c, hipMemcpyAsync(done, w.pst.p + (size_t)(s - 1) * ns, sizeof done, hipMemcpyDeviceToHost, w.st));
+            HIPCHK(w.c, hipStreamSynchronize(w.st));
+        }
+        if (done[1] && done[2] < 0) return fail(w.c, FK_ERR_ARG, "fk_run_scf: degenerate Fock spectrum bounds");
+        if (!done[1]) return fail(w.c, FK_ERR_NOT_CONVERGED, "fk_run_scf: purification did not converge (no gap?)");
+        if (steps) *steps = done[2];
+        SCFCHK(w, fk_scf_lincomb(w.Do.p, buf[2 * (done[2] & 1)], nullptr, nullptr, n, 2.0, 0, 0, 0, w.st));
+        return FK_OK;
+    }
     if ((rc = scf_reduce(w, w.Fo.p, nullptr, 3, gb))) return rc;
     const double lo = gb[0], hi = gb[1];
     if (!(hi > lo)) return fail(w.c, FK_ERR_ARG, "fk_run_scf: degenerate Fock spectrum bounds");
@@ -3000,7 +3030,7 @@ int fk_run_scf(fk_ctx *c, const fk_scf_opts *opts, fk_scf_result *result, double
     for (auto *b : {&w.h, &w.X, &w.Xi, &w.D, &w.Do, &w.J, &w.K, &w.F, &w.Fo, &w.G, &w.E, &w.T1, &w.T2, &w.T3})
         if ((rc = dev_upload<double>(c, *b, nullptr, nn))) return rc;
     if ((rc = dev_upload<double>(c, w.part, nullptr, (size_t)fk_scf_reduce_scratch() + 2))) return rc;
-    if ((rc = dev_upload<double>(c, w.scal, nullptr, 4))) return rc;
+    if ((rc = dev_upload<double>(c, w.scal, nullptr, 4)) || (rc = dev_upload<double>(c, w.dots, nullptr, 32))) return rc;
     w.ringF.resize(std::max(o.diis_n, 1));
     w.ringE.resize(std::max(o.diis_n, 1));
     if (o.diis_n > 0)
@@ -3169,21 +3199,19 @@ int fk_run_scf(fk_ctx *c, const fk_scf_opts *opts, fk_scf_result *result, double
             slot_age.push_back(k);
             HIPCHK(c, hipMemcpyAsync(w.ringF[k].p, w.Fo.p, nn * sizeof(double), hipMemcpyDeviceToDevice, w.st));
             HIPCHK(c, hipMemcpyAsync(w.ringE[k].p, w.E.p, nn * sizeof(double), hipMemcpyDeviceToDevice, w.st));
-            for (int j : slot_age) {
-                double v;
-                if ((rc = scf_reduce(w, w.ringE[k].p, w.ringE[j].p, 0, &v))) return rc;
-                B[(size_t)k * dn + j] = B[(size_t)j * dn + k] = v;
-            }
             const int m = (int)slot_age.size();
+            const double *ev[32], *fv[32];
+            double dots[32];
+            for (int i = 0; i < m; ++i) { ev[i] = w.ringE[slot_age[i]].p; fv[i] = w.ringF[slot_age[i]].p; }
+            SCFCHK(w, fk_scf_dots(w.ringE[k].p, ev, m, n, w.part.p, w.dots.p, w.st));
+            HIPCHK(c, hipMemcpyAsync(dots, w.dots.p, m * sizeof(double), hipMemcpyDeviceToHost, w.st));
+            HIPCHK(c, hipStreamSynchronize(w.st));
+            for (int i = 0; i < m; ++i) B[(size_t)k * dn + slot_age[i]] = B[(size_t)slot_age[i] * dn + k] = dots[i];
             if (m >= 2) {
                 std::vector<double> Bm((size_t)m * m), coef;
                 for (int i = 0; i < m; ++i)
                     for (int j = 0; j < m; ++j) Bm[(size_t)i * m + j] = B[(size_t)slot_age[i] * dn + slot_age[j]];
-                if (diis_solve(Bm, m, coef)) {
-                    SCFCHK(w, fk_scf_lincomb(w.Fo.p, w.ringF[slot_age[0]].p, nullptr, nullptr, n, coef[0], 0, 0, 0, w.st));
-                    for (int i = 1; i < m; ++i)
-                        SCFCHK(w, fk_scf_lincomb(w.Fo.p, w.Fo.p, w.ringF[slot_age[i]].p, nullptr, n, 1.0, coef[i], 0, 0, w.st));
-                }
+                if (diis_solve(Bm, m, coef)) SCFCHK(w, fk_scf_combine(w.Fo.p, fv, coef.data(), m, n, w.st));
             }
         }
         // new density: D' from F', D = X D' X

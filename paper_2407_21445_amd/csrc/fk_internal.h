@@ -256,6 +256,13 @@ int fk_scf_antisym(double *e, const double *G, int n, void *stream);
 int fk_scf_reduce(const double *x, const double *y, int n, int op, double *part, double *out, int slot,
                   void *stream);
 int fk_scf_reduce_scratch();
+int fk_scf_purify_max_n();
+long long fk_scf_purify_trace_doubles(int steps);
+int fk_scf_purify_state_ints();
+int fk_scf_purify_steps(const double *F, double *const *buf, int n, int nocc, int first, int last,
+                        const double *bounds, double *trace, int *state, void *stream);
+int fk_scf_dots(const double *x, const double *const *y, int m, int n, double *part, double *out, void *stream);
+int fk_scf_combine(double *out, const double *const *x, const double *c, int m, int n, void *stream);
 int fk_scf_eig_scale(const double *V, const double *s, double *out, int n, double cutoff, double power, void *stream);
 int fk_scf_eigh(double *A, double *w, double *work, int *info, int n, void *stream);
 }
