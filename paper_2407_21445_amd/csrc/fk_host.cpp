@@ -168,7 +168,9 @@ struct fk_ctx {
     DevBuf<int2> d_tasks;
     DevBuf<int> d_krow_col, d_krow_cnt, d_krow_off, d_krow_fn;
     DevBuf<FkBraBlock> d_blocks;
-    DevBuf<int> d_blk_bra, d_blk_pos;
+    DevBuf<FkBraRec> d_blk_rec;
+    DevBuf<FkKet> d_lst_ket;
+    DevBuf<int2> d_lst_col;
     DevBuf<unsigned long long> d_cnt;
     // J engine (built on first use after fk_build_quartets)
     bool jeng_valid = false;
@@ -291,7 +293,7 @@ void free_device(fk_ctx *c)
     dev_free(c->d_pr_npp); dev_free(c->d_ket); dev_free(c->d_bf_scale); dev_free(c->d_pr_AB);
     dev_free(c->d_pr_G); dev_free(c->d_pp); dev_free(c->d_rys); dev_free(c->d_Ds); dev_free(c->d_Dsh);
     dev_free(c->d_X); dev_free(c->d_Din); dev_free(c->d_Jout); dev_free(c->d_Kout); dev_free(c->d_tiles);
-    dev_free(c->d_cnt); dev_free(c->d_blocks); dev_free(c->d_blk_bra); dev_free(c->d_blk_pos); dev_free(c->d_lst_sa); dev_free(c->d_lst_sb); dev_free(c->d_lst_CD);
+    dev_free(c->d_cnt); dev_free(c->d_blocks); dev_free(c->d_blk_rec); dev_free(c->d_lst_ket); dev_free(c->d_lst_col); dev_free(c->d_lst_npp); dev_free(c->d_lst_sa); dev_free(c->d_lst_sb); dev_free(c->d_lst_CD);
     dev_free(c->d_lst_G); dev_free(c->d_ppT); dev_free(c->d_groups);
     dev_free(c->d_tasks); dev_free(c->d_krow_col); dev_free(c->d_krow_cnt); dev_free(c->d_krow_off); dev_free(c->d_krow_fn);
     dev_free(c->d_jeng_tiles); dev_free(c->d_jp_off); dev_free(c->d_dq_base); dev_free(c->d_pos_grp);
@@ -1291,7 +1293,7 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
                 const int sa0 = c->pr_sa[LP[ord[i0]]];
                 while (i1 < ord.size() && (int)(i1 - i0) < bmax && c->pr_sa[LP[ord[i1]]] == sa0) ++i1;
                 const int blk = (int)c->blocks.size();
-                c->blocks.push_back(FkBraBlock{(int)c->blk_bra.size(), (int)(i1 - i0)});
+                c->blocks.push_back(FkBraBlock{(int)c->blk_bra.size(), (int)(i1 - i0), c->sh_loc[sa0], c->sh_lbf[sa0]});
                 int64_t nppsum = 0;
                 for (size_t x = i0; x < i1; ++x) {
                     c->blk_bra.push_back(LP[ord[x]]);
@@ -1350,7 +1352,8 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
                         else {
                             blk = (int)c->blocks.size();
                             runs[key] = blk;
-                            c->blocks.push_back(FkBraBlock{c->blocks[R.blk].first + key.first, key.second});
+                            c->blocks.push_back(FkBraBlock{c->blocks[R.blk].first + key.first, key.second, c->blocks[R.blk].sa,
+                                                             c->blocks[R.blk].oa});
                             c->blk_nppsum.push_back(nppsum);
                         }
                     }
@@ -1482,8 +1485,22 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
         if ((rc = dev_upload<double>(c, c->d_X, nullptr, 2 * nn * FK_XCD_COPIES))) return rc;
         if ((rc = dev_upload<unsigned long long>(c, c->d_cnt, nullptr, 2 * FK_MAX_QCLASS))) return rc;
         if ((rc = dev_upload(c, c->d_blocks, c->blocks.data(), c->blocks.size()))) return rc;
-        if ((rc = dev_upload(c, c->d_blk_bra, c->blk_bra.data(), c->blk_bra.size()))) return rc;
-        if ((rc = dev_upload(c, c->d_blk_pos, c->blk_pos.data(), c->blk_pos.size()))) return rc;
+        std::vector<FkBraRec> rec(c->blk_bra.size());
+        for (size_t i = 0; i < rec.size(); ++i) {
+            const int p = c->blk_bra[i], sb = c->pr_sb[p];
+            rec[i] = FkBraRec{{c->sh_loc[sb], c->sh_lbf[sb], c->blk_pos[i], c->pr_npp[p], c->pr_G[p]}, c->pr_ppoff[p], p,
+                              {c->pr_AB[3 * p], c->pr_AB[3 * p + 1], c->pr_AB[3 * p + 2]}, {0, 0}};
+        }
+        if ((rc = dev_upload(c, c->d_blk_rec, rec.data(), rec.size()))) return rc;
+        std::vector<FkKet> ket(c->ket_list_all.size());
+        std::vector<int2> col(ket.size());
+        for (size_t q = 0; q < ket.size(); ++q) {
+            const int sc = c->lst_sa[q], sd = c->lst_sb[q];
+            ket[q] = FkKet{c->sh_loc[sc], c->sh_loc[sd], c->sh_lbf[sc], c->sh_lbf[sd]};
+            col[q] = int2{c->krow_col[sc], c->krow_col[sd]};
+        }
+        if ((rc = dev_upload(c, c->d_lst_ket, ket.data(), ket.size()))) return rc;
+        if ((rc = dev_upload(c, c->d_lst_col, col.data(), col.size()))) return rc;
     }
     c->have_quartets = true;
     c->jeng_valid = false;
@@ -1872,22 +1889,13 @@ int build_jk_impl(fk_ctx *c, const double *D, double *J, double *K, unsigned fla
             continue;
         }
         FkJKArgs a;
-        a.sh_bf = c->d_sh_bf.p;
-        a.mol_sh0 = c->d_mol_sh0.p;
         a.mol_nbf = c->d_mol_nbf.p;
         a.mol_nsh = c->d_mol_nsh.p;
         a.mol_base = c->d_mol_base.p;
         a.mol_shbase = c->d_mol_shbase.p;
-        a.pair_sa = c->d_pr_sa.p;
-        a.pair_sb = c->d_pr_sb.p;
-        a.pair_ppoff = c->d_pr_ppoff.p;
-        a.pair_npp = c->d_pr_npp.p;
-        a.pair_AB = c->d_pr_AB.p;
-        a.pair_G = c->d_pr_G.p;
         a.pp = c->d_pp.p;
-        a.ket_list = c->d_ket.p;
-        a.lst_sa = c->d_lst_sa.p;
-        a.lst_sb = c->d_lst_sb.p;
+        a.lst_ket = c->d_lst_ket.p;
+        a.lst_col = c->d_lst_col.p;
         a.lst_npp = c->d_lst_npp.p;
         a.lst_CD = c->d_lst_CD.p;
         a.lst_G = c->d_lst_G.p;
@@ -1899,7 +1907,6 @@ int build_jk_impl(fk_ctx *c, const double *D, double *J, double *K, unsigned fla
         a.tasks = qc.ntask > 0 ? c->d_tasks.p + qc.task_off : nullptr;
         a.ntask = (int)qc.ntask;
         a.krow_ncol = qc.krow_ncol;
-        a.krow_col = c->d_krow_col.p;
         a.krow_cnt = c->d_krow_cnt.p;
         a.krow_off = c->d_krow_off.p;
         a.krow_fn = c->d_krow_fn.p;
@@ -1936,8 +1943,7 @@ int build_jk_impl(fk_ctx *c, const double *D, double *J, double *K, unsigned fla
         a.nw = qc.nw;
         a.krow_nbk = qc.krow_nbk;
         a.blocks = c->d_blocks.p;
-        a.blk_bra = c->d_blk_bra.p;
-        a.blk_pos = c->d_blk_pos.p;
+        a.blk_rec = c->d_blk_rec.p;
         // Enough workgroups for the hardware to fill every CU to its register and
         // LDS limit; the persistent loop covers the rest.
         const int64_t wgs = qc.ntask > 0 ? qc.ntask : (qc.ntile + 3) / 4;

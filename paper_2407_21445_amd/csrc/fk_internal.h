@@ -32,11 +32,29 @@ struct FkTile {
 #define FK_WANT_J 1
 #define FK_WANT_K 2
 
-// Bra block: blk_bra[first .. first + count) are shell-pair indices with the
-// same first shell; blk_pos holds their positions in the sorted pair lists.
+// Bra block: the records [first .. first + count) of blk_rec are shell pairs with
+// the same first shell sa (within its molecule), whose first function is oa.
 struct FkBraBlock {
     int first;
     int count;
+    int sa, oa;
+};
+// Member of a bra block, in one place so that a wave reads it with one scalar
+// load: what the screen needs, then the primitive records and A - B.
+struct FkBraScreen {
+    int sb, ob;    // second shell (within its molecule), its first function
+    int pos, npp;  // position in the sorted pair lists, primitive pairs
+    double G;      // Schwarz factor
+};
+struct FkBraRec {
+    FkBraScreen s;
+    int ppo, bra;  // first primitive record, shell-pair index
+    double AB[3];
+    int pad[2];
+};
+// Ket at a list position: its shells (within the molecule) and their first functions.
+struct FkKet {
+    int sc, sd, oc, od;
 };
 #define FK_MAX_BRA_BLOCK 32
 
@@ -58,23 +76,14 @@ struct FkGroup {
 #endif
 
 struct FkJKArgs {
-    // Shells are numbered within their molecule: a kernel offsets these arrays
-    // by the tile's molecule (FkGroup::mol).
-    const int *sh_bf;        // [nshell] first basis function of each shell, within its molecule
-    const int *mol_sh0;      // [nmol] first shell of each molecule
+    // Shells are numbered within their molecule (FkGroup::mol of a tile).
     const int *mol_nbf;      // [nmol] functions per molecule
     const int *mol_nsh;      // [nmol] shells per molecule
     const long long *mol_base;    // [nmol + 1] offset of each molecule's nbf^2 block in Ds, XJ, XK
     const long long *mol_shbase;  // [nmol + 1] offset of each molecule's nshell^2 block in Dsh
-    const int *pair_sa;      // [npair] first shell (higher l), index within the molecule
-    const int *pair_sb;      // [npair] second shell, index within the molecule
-    const int *pair_ppoff;   // [npair] first primitive pair
-    const int *pair_npp;     // [npair] number of primitive pairs
-    const double *pair_AB;   // [npair * 3] A - B
-    const double *pair_G;    // [npair] Schwarz factor
     const double *pp;        // [nprimpair * FK_NPP_REC]
-    const int *ket_list;     // sorted pair indices (all classes, concatenated)
-    const int *lst_sa, *lst_sb;   // shells (within the molecule) of the pair at each list position
+    const FkKet *lst_ket;    // shells and functions of the pair at each list position
+    const int2 *lst_col;     // its LDS row columns (krow_col of c and d)
     const int *lst_npp;      // its primitive pairs (its group's records hold at least as many)
     const double *lst_CD;    // [3][nlist] A - B of the pair at each list position
     const double *lst_G;     // Schwarz factor at each list position
@@ -84,8 +93,7 @@ struct FkJKArgs {
     const FkTile *tiles;
     int ntiles;
     const FkBraBlock *blocks;
-    const int *blk_bra;      // shell-pair index of each bra of each block
-    const int *blk_pos;      // its position in the sorted pair lists
+    const FkBraRec *blk_rec; // the bras of each block
     const double *Dsh;       // per molecule [nshell_m * nshell_m] max |D| per shell block
     const double *Ds;        // per molecule [nbf_m * nbf_m] component-scaled density
     double *XJ;              // per molecule [nbf_m * nbf_m] unsymmetrised Coulomb accumulator
@@ -123,7 +131,7 @@ struct FkJKArgs {
     int ntask;
     int krow_ncol;           // LDS row length: the class's largest column count over the molecules
     int krow_nbk;            // bras per block the rows are laid out for (the class's bra block)
-    const int *krow_col, *krow_cnt, *krow_off, *krow_fn;
+    const int *krow_cnt, *krow_off, *krow_fn;
 };
 
 // The accumulators X_J, X_K exist once per XCD (CDNA3/4 parts have 8 XCDs,

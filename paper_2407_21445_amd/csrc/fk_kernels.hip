@@ -301,44 +301,102 @@ __device__ __forceinline__ double dmax_args(const FkJKArgs &a, const double *__r
     return dmax_want(Dsh, ns, sa, sb, sc, sd, a.want);
 }
 
-// Screening of the (bra, ket) combinations of a wave and the precision split.
-// A lane's quartet survives the Schwarz bound, the same-class triangle and the
-// density screen G_ab G_cd D_max >= tau.  With the split (tau_fp32 > 0) the
-// wave's surviving quartets of this bra go to the FP32 launch when every one
-// has G_ab G_cd D_max < tau_fp32, else to the FP64 launch: both launches reach
-// the same decision, so each quartet is computed once.  Returns the lanes this
-// launch computes.
-template <typename R>
-__device__ __forceinline__ bool screen_lane(const FkJKArgs &a, bool cand, double gg, const double *__restrict Dsh,
-                                            int ns, int sa, int sb, int sc, int sd)
+// A record at a wave-uniform index, read through the constant address space: a
+// scalar load into SGPRs (none of these tables is written while a kernel reads
+// it).  Vector loads of the same records cost a wave some 640 cycles each, one
+// after the other down the chain tile -> block -> bra -> shells.
+template <class T>
+__device__ __forceinline__ T sload(const T *__restrict p, long long i)
 {
-    bool active = cand && (a.tau <= 0 || gg >= a.tau);
-    double dm = 0.0;
-    if (a.dscreen || a.tau_fp32 > 0) dm = dmax_args(a, Dsh, ns, sa, sb, sc, sd);
-    if (a.dscreen) active = active && gg * dm >= a.tau;
-    if (a.tau_fp32 > 0) {
-        const bool need64 = __ballot(active && gg * dm >= a.tau_fp32) != 0ull;
-        const bool mine = (sizeof(R) == sizeof(double)) ? need64 : !need64;
-        active = active && mine;
-    }
-    return active;
+    static_assert(sizeof(T) % 4 == 0, "whole dwords");
+    const __attribute__((address_space(4))) int *q = (const __attribute__((address_space(4))) int *)(p + i);
+    int w[sizeof(T) / 4];
+#pragma unroll
+    for (int k = 0; k < (int)(sizeof(T) / 4); ++k) w[k] = q[k];
+    T v;
+    __builtin_memcpy(&v, w, sizeof(T));
+    return v;
 }
 
 // Ket pair data at a list position (consecutive lanes: consecutive positions).
 struct KetInfo {
-    int sc, sd;
+    int sc, sd, oc, od;
     double CD[3], G;
 };
 __device__ __forceinline__ KetInfo load_ket(const FkJKArgs &a, int pos)
 {
     KetInfo k;
-    k.sc = a.lst_sa[pos];
-    k.sd = a.lst_sb[pos];
+    const int4 s = *(const int4 *)(a.lst_ket + pos);
+    k.sc = s.x; k.sd = s.y; k.oc = s.z; k.od = s.w;
     k.CD[0] = a.lst_CD[pos];
     k.CD[1] = a.lst_CD[a.nlist + pos];
     k.CD[2] = a.lst_CD[2 * a.nlist + pos];
     k.G = a.lst_G[pos];
     return k;
+}
+
+// Screening of the (bra, ket) combinations of a tile and the precision split.  A
+// lane's quartet survives the same-class triangle (ket position <= bra
+// position), the Schwarz bound and the density screen G_ab G_cd D_max >= tau.
+// With the split (tau_fp32 > 0) the wave's surviving quartets of a bra go to the
+// FP32 launch when every one has G_ab G_cd D_max < tau_fp32, else to the FP64
+// launch: both launches reach the same decision, so each quartet is computed
+// once.  Returns the bras (bits) whose quartet this lane computes; `any`: the
+// bras any lane computes.
+// All bras of the block are screened before the first is computed, four at a
+// time, so that their density maxima are one latency and not one per bra.
+template <typename R>
+__device__ __forceinline__ unsigned screen_block(const FkJKArgs &a, const FkBraBlock &blk, bool same, bool cand, int pos,
+                                                 const KetInfo &K, const double *__restrict Dsh, int ns, unsigned &any)
+{
+    const bool dens = a.dscreen || a.tau_fp32 > 0, kskip = a.ks_shell && a.want == FK_WANT_K;
+    const bool wj = (a.want & FK_WANT_J) != 0, wk = (a.want & FK_WANT_K) != 0;
+    const int sa = blk.sa, sc = K.sc, sd = K.sd;
+    double base = 0.0;
+    if (dens && !kskip) {
+        if (wj) base = Dsh[sc * ns + sd];
+        if (wk) base = fmax(base, fmax(Dsh[sa * ns + sc], Dsh[sa * ns + sd]));
+    }
+    unsigned act = 0u;
+    any = 0u;
+    auto decide = [&](int jb, const FkBraScreen &b, double dm) __attribute__((always_inline)) {
+        const double gg = b.G * K.G;
+        bool active = cand && (!same || pos <= b.pos) && (a.tau <= 0 || gg >= a.tau);
+        if (a.dscreen) active = active && gg * dm >= a.tau;
+        if (a.tau_fp32 > 0) {
+            const bool need64 = __ballot(active && gg * dm >= a.tau_fp32) != 0ull;
+            active = active && (sizeof(R) == sizeof(double) ? need64 : !need64);
+        }
+        any |= __ballot(active) != 0ull ? 1u << jb : 0u;
+        act |= active ? 1u << jb : 0u;
+    };
+    if (dens && kskip) {
+#pragma unroll 1
+        for (int jb = 0; jb < blk.count; ++jb) {
+            const FkBraScreen b = sload(&a.blk_rec[blk.first + jb].s, 0);
+            decide(jb, b, dmax_kskip(a, Dsh, ns, sa, b.sb, sc, sd));
+        }
+        return act;
+    }
+    constexpr int C = 4;
+    for (int j0 = 0; j0 < blk.count; j0 += C) {
+        FkBraScreen b[C];
+        double dm[C];
+#pragma unroll
+        for (int k = 0; k < C; ++k) b[k] = sload(&a.blk_rec[blk.first + min(j0 + k, blk.count - 1)].s, 0);
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            dm[k] = base;
+            if (dens) {
+                if (wk) dm[k] = fmax(dm[k], fmax(Dsh[b[k].sb * ns + sc], Dsh[b[k].sb * ns + sd]));
+                if (wj) dm[k] = fmax(dm[k], sload(Dsh, sa * ns + b[k].sb));
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < C; ++k)
+            if (j0 + k < blk.count) decide(j0 + k, b[k], dm[k]);
+    }
+    return act;
 }
 
 // Primitive pair j of the ket at position r of a group (transposed records).
@@ -353,24 +411,6 @@ __device__ __forceinline__ fk::PrimPair load_ket_pp(const double *__restrict ppT
     p.PA[0] = q[5 * L]; p.PA[1] = q[6 * L]; p.PA[2] = q[7 * L];
     p.K = q[8 * L];
     return p;
-}
-
-struct BraInfo {
-    int sa, sb, ppo, npp;
-    double AB[3], G;
-};
-__device__ __forceinline__ BraInfo load_bra(const FkJKArgs &a, int bra)
-{
-    BraInfo b;
-    b.sa = a.pair_sa[bra];
-    b.sb = a.pair_sb[bra];
-    b.ppo = a.pair_ppoff[bra];
-    b.npp = a.pair_npp[bra];
-    b.AB[0] = a.pair_AB[3 * bra];
-    b.AB[1] = a.pair_AB[3 * bra + 1];
-    b.AB[2] = a.pair_AB[3 * bra + 2];
-    b.G = a.pair_G[bra];
-    return b;
 }
 
 // The bra's primitive records are the same for every lane of the wave: they
@@ -419,7 +459,7 @@ __device__ __forceinline__ void task_loop(const FkJKArgs &a, double *kr, bool ta
     constexpr int NG = NW / SPLIT;
     const int units = tasks ? a.ntask : (a.ntiles + NG - 1) / NG;
     for (int u = blockIdx.x; u < units; u += gridDim.x) {
-        const int2 tk = tasks ? a.tasks[u] : int2{u * NG, min(NG, a.ntiles - u * NG)};
+        const int2 tk = tasks ? sload(a.tasks, u) : int2{u * NG, min(NG, a.ntiles - u * NG)};
         if (tasks) {
             for (int i = threadIdx.x; i < nkr; i += 64 * NW) kr[i] = 0.0;
             __syncthreads();
@@ -429,13 +469,12 @@ __device__ __forceinline__ void task_loop(const FkJKArgs &a, double *kr, bool ta
         __syncthreads();
         // the block's rows to memory: nonzero entries, consecutive threads
         // on consecutive columns of a row
-        const FkTile t0 = a.tiles[tk.x];
-        const int mol = a.groups[t0.grp & ~FK_TILE_SAME].mol;
-        const int n = a.mol_nbf[mol];
-        const int *__restrict shbf = a.sh_bf + a.mol_sh0[mol];
-        const long long xoff = (long long)(blockIdx.x % FK_XCD_COPIES) * a.xcopy + a.mol_base[mol];
-        const FkBraBlock blk = a.blocks[t0.blk];
-        const int oa = shbf[a.pair_sa[a.blk_bra[blk.first]]];
+        const FkTile t0 = sload(a.tiles, tk.x);
+        const int mol = sload(a.groups, t0.grp & ~FK_TILE_SAME).mol;
+        const int n = sload(a.mol_nbf, mol);
+        const long long xoff = (long long)(blockIdx.x % FK_XCD_COPIES) * a.xcopy + sload(a.mol_base, mol);
+        const FkBraBlock blk = sload(a.blocks, t0.blk);
+        const int oa = blk.oa;
         const int cc = a.krow_cnt[4 * mol + LC];
         const int ncm = cc + (LC != LD ? a.krow_cnt[4 * mol + LD] : 0);
         const int *fnc = a.krow_fn + a.krow_off[4 * mol + LC];
@@ -448,7 +487,7 @@ __device__ __forceinline__ void task_loop(const FkJKArgs &a, double *kr, bool ta
                 const int rr = r < blk.count * NB ? r : nbk * NB + (r - blk.count * NB);
                 const double v = kr[rr * ncol + x];
                 if (v == 0.0) continue;
-                const int row = r < blk.count * NB ? shbf[a.pair_sb[a.blk_bra[blk.first + r / NB]]] + r % NB
+                const int row = r < blk.count * NB ? a.blk_rec[blk.first + r / NB].s.ob + r % NB
                                                    : oa + (r - blk.count * NB);
                 const int fn = x < cc ? fnc[x] : fnd[x - cc];
                 atomic_add(&XK[(size_t)row * n + fn], v);
@@ -461,7 +500,7 @@ __device__ __forceinline__ void task_loop(const FkJKArgs &a, double *kr, bool ta
                 const double v = kj[e];
                 if (v == 0.0) continue;
                 const int jb = e / (NA * NB), ab = e % (NA * NB);
-                const int ob = shbf[a.pair_sb[a.blk_bra[blk.first + jb]]];
+                const int ob = a.blk_rec[blk.first + jb].s.ob;
                 atomic_add(&XJ[(size_t)(oa + ab / NB) * n + ob + ab % NB], v);
             }
         }
@@ -742,33 +781,30 @@ __global__ void __launch_bounds__(64 * NW, (LpqBounds<LA, LB, LC, LD, NW>::value
     double *const kr = s_dyn + rys_lds_size(Q::NR) + NW * stg;  // the workgroup's K rows of a block task
     // one tile (t) for this wave
     auto do_tile = [&](int t) __attribute__((always_inline)) {
-        const FkTile tile = a.tiles[t];
+        const FkTile tile = sload(a.tiles, t);
         const bool same = (tile.grp & FK_TILE_SAME) != 0;
-        const FkGroup g = a.groups[tile.grp & ~FK_TILE_SAME];
+        const FkGroup g = sload(a.groups, tile.grp & ~FK_TILE_SAME);
         const int p0 = tile.p0, p1 = tile.p1;
         // the tile's molecule: its blocks of D, D_sh, X_J, X_K and shells
         const int mol = g.mol;
-        const int n = a.mol_nbf[mol], ns = a.mol_nsh[mol];
-        const int *__restrict shbf = a.sh_bf + a.mol_sh0[mol];
-        const double *__restrict Ds = a.Ds + a.mol_base[mol];
-        const double *__restrict Dsh = a.Dsh + a.mol_shbase[mol];
-        const long long xoff = (long long)(blockIdx.x % FK_XCD_COPIES) * a.xcopy + a.mol_base[mol];
+        const int n = sload(a.mol_nbf, mol), ns = sload(a.mol_nsh, mol);
+        const long long mbase = sload(a.mol_base, mol);
+        const double *__restrict Ds = a.Ds + mbase;
+        const double *__restrict Dsh = a.Dsh + sload(a.mol_shbase, mol);
+        const long long xoff = (long long)(blockIdx.x % FK_XCD_COPIES) * a.xcopy + mbase;
         double *XJ = a.XJ + xoff;
         double *XK = a.XK + xoff;
-        const FkBraBlock blk = a.blocks[tile.blk];
+        const FkBraBlock blk = sload(a.blocks, tile.blk);
         const bool inrange = lane < tile.ket_count;
         const int pos = tile.ket_begin + (inrange ? lane : 0);
         const int r = pos - g.begin;
         const KetInfo Kt = load_ket(a, pos);
-        const int sc = Kt.sc, sd = Kt.sd;
-        const int oc = shbf[sc], od = shbf[sd];
-        const int sa = a.pair_sa[a.blk_bra[blk.first]];
-        const int oa = shbf[sa];
+        const int sc = Kt.sc, sd = Kt.sd, oc = Kt.oc, od = Kt.od, sa = blk.sa, oa = blk.oa;
         int colc = 0, cold = 0;
         if (tasks) {
-            const int *kcol = a.krow_col + a.mol_sh0[mol];
-            colc = kcol[sc];
-            cold = kcol[sd] + (LC != LD ? a.krow_cnt[4 * mol + LC] : 0);
+            const int2 kc = a.lst_col[pos];
+            colc = kc.x;
+            cold = kc.y + (LC != LD ? sload(a.krow_cnt, 4 * mol + LC) : 0);
         }
         // D_cd is used with every bra of the block
         double dcd[NC * ND];
@@ -792,28 +828,18 @@ __global__ void __launch_bounds__(64 * NW, (LpqBounds<LA, LB, LC, LD, NW>::value
             using H = fk::HgpClass<LA, LB, LC, LD>;
             constexpr int NACC = ENG == 0 ? NOUT : H::NACC;
             const int nb = blk.count;  // at most NBK: the class reports it as its largest bra block
-            unsigned act = 0u;
             int ppo[NBK], bnpp[NBK];
             R acck[NBK][NACC];
 #pragma unroll
             for (int jb = 0; jb < NBK; ++jb) {
 #pragma unroll
                 for (int o = 0; o < NACC; ++o) acck[jb][o] = (R)0;
-                ppo[jb] = 0;
-                bnpp[jb] = 0;
-                if (jb < nb) {
-                    const int bra = a.blk_bra[blk.first + jb];
-                    const int bpos = a.blk_pos[blk.first + jb];
-                    const bool active = screen_lane<R>(a, inrange && (!same || pos <= bpos), a.pair_G[bra] * Kt.G,
-                                                       Dsh, ns, sa, a.pair_sb[bra], sc, sd);
-                    ppo[jb] = __builtin_amdgcn_readfirstlane(a.pair_ppoff[bra]);
-                    bnpp[jb] = __builtin_amdgcn_readfirstlane(a.pair_npp[bra]);
-                    const int nact = __popcll(__ballot(active));
-                    cq += p0 == 0 ? nact : 0;
-                    if (nact) cp += (unsigned long long)bnpp[jb] * ket_prims(g, a.lst_npp, pos, p0, p1, active, nact);
-                    if (active) act |= 1u << jb;
-                }
+                const FkBraRec B = sload(a.blk_rec, blk.first + min(jb, nb - 1));
+                ppo[jb] = B.ppo;
+                bnpp[jb] = B.s.npp;
             }
+            unsigned any_bra;
+            const unsigned act = screen_block<R>(a, blk, same, inrange, pos, Kt, Dsh, ns, any_bra);
             if (act) {
                 fk::PrimPair qn = load_ket_pp(a.ppT, g, p0, r);
                 for (int j = p0; j < p1; ++j) {
@@ -822,7 +848,7 @@ __global__ void __launch_bounds__(64 * NW, (LpqBounds<LA, LB, LC, LD, NW>::value
 #pragma unroll
                     for (int jb = 0; jb < NBK; ++jb) {
                         if (jb < nb && ((act >> jb) & 1u)) {
-                            const fk_const_ptr ab = (fk_const_ptr)(a.pair_AB + 3 * a.blk_bra[blk.first + jb]);
+                            const fk_const_ptr ab = (fk_const_ptr)a.blk_rec[blk.first + jb].AB;
                             const double AB[3] = {ab[0], ab[1], ab[2]};
                             if constexpr (ENG == 0) {
                                 constexpr bool PAIR = NOUT <= FK_LPQ_PAIR_NOUT;
@@ -848,9 +874,8 @@ __global__ void __launch_bounds__(64 * NW, (LpqBounds<LA, LB, LC, LD, NW>::value
             // digestion, one bra at a time: the block's accumulators move down
             // one slot per bra, so the loop body reads slot 0 only
             for (int jb = 0; jb < nb; ++jb) {
-                const int bra = a.blk_bra[blk.first + jb];
-                const int bpos = a.blk_pos[blk.first + jb];
-                const int sb = a.pair_sb[bra];
+                const FkBraRec B = sload(a.blk_rec, blk.first + jb);
+                const double AB[3] = {B.AB[0], B.AB[1], B.AB[2]};
                 const bool active = ((act >> jb) & 1u) != 0u;
                 R acc[NOUT];
                 if constexpr (ENG == 0) {
@@ -860,7 +885,6 @@ __global__ void __launch_bounds__(64 * NW, (LpqBounds<LA, LB, LC, LD, NW>::value
 #pragma unroll
                     for (int o = 0; o < NOUT; ++o) acc[o] = (R)0;
                     if (active) {
-                        const double AB[3] = {a.pair_AB[3 * bra], a.pair_AB[3 * bra + 1], a.pair_AB[3 * bra + 2]};
                         fk::hgp_hrr<LA, LB, LC, LD, R>(acck[0], AB, Kt.CD, acc);
                     }
                 }
@@ -868,29 +892,28 @@ __global__ void __launch_bounds__(64 * NW, (LpqBounds<LA, LB, LC, LD, NW>::value
                 for (int k = 0; k + 1 < NBK; ++k)
 #pragma unroll
                     for (int o = 0; o < NACC; ++o) acck[k][o] = acck[k + 1][o];
-                if (__ballot(active) == 0ull) continue;
-                lpq_digest<LA, LB, LC, LD, R>(acc, active, same && pos == bpos, sa, sb, sc, sd, oa, shbf[sb], oc,
+                if (!((any_bra >> jb) & 1u)) continue;
+                const int nact = __popcll(__ballot(active));
+                cq += p0 == 0 ? nact : 0;
+                cp += (unsigned long long)B.s.npp * ket_prims(g, a.lst_npp, pos, p0, p1, active, nact);
+                lpq_digest<LA, LB, LC, LD, R>(acc, active, same && pos == B.s.pos, sa, B.s.sb, sc, sd, oa, B.s.ob, oc,
                                               od, n, Ds, dcd, kac, kad, jcd, XJ, XK, s_stage, lane, wj, wk, any,
                                               tasks, kr + jb * NB * a.krow_ncol, a.krow_ncol, colc, cold,
                                               kr + (nbk * NB + NA) * a.krow_ncol + jb * NA * NB);
             }
         } else
-        for (int jb = 0; jb < blk.count; ++jb) {
-            const int bra = a.blk_bra[blk.first + jb];
-            const int bpos = a.blk_pos[blk.first + jb];
-            const BraInfo B = load_bra(a, bra);
-            const int sb = B.sb;
-            // Schwarz bound, same-class triangle (ket position <= bra position)
-            // and density screen for this (bra, ket)
-            const bool active = screen_lane<R>(a, inrange && (!same || pos <= bpos), B.G * Kt.G, Dsh, ns, sa, sb, sc, sd);
-            const unsigned long long mask = __ballot(active);
-            if (mask == 0ull) continue;
-            const int nact = __popcll(mask);
+        {
+        unsigned any_bra;
+        const unsigned act = screen_block<R>(a, blk, same, inrange, pos, Kt, Dsh, ns, any_bra);
+        for (; any_bra; any_bra &= any_bra - 1) {
+            const int jb = __ffs((int)any_bra) - 1;
+            const FkBraRec B = sload(a.blk_rec, blk.first + jb);
+            const double AB[3] = {B.AB[0], B.AB[1], B.AB[2]};
+            const bool active = ((act >> jb) & 1u) != 0u;
+            const int ppo = B.ppo, bnpp = B.s.npp;
+            const int nact = __popcll(__ballot(active));
             cq += p0 == 0 ? nact : 0;
-            cp += (unsigned long long)B.npp * ket_prims(g, a.lst_npp, pos, p0, p1, active, nact);
-
-            const int ppo = __builtin_amdgcn_readfirstlane(B.ppo);
-            const int bnpp = __builtin_amdgcn_readfirstlane(B.npp);
+            cp += (unsigned long long)bnpp * ket_prims(g, a.lst_npp, pos, p0, p1, active, nact);
             R acc[NOUT];
 #pragma unroll
             for (int o = 0; o < NOUT; ++o) acc[o] = (R)0;
@@ -908,11 +931,11 @@ __global__ void __launch_bounds__(64 * NW, (LpqBounds<LA, LB, LC, LD, NW>::value
                         if constexpr (PAIR)
                             for (; i + 1 < bnpp; i += 2) {
                                 const fk::PrimPair p0 = sload_pp(a.pp, ppo + i), p1 = sload_pp(a.pp, ppo + i + 1);
-                                fk::rys_prim_all<LA, LB, LC, LD, R, true>(s_tab, p0, q, B.AB, Kt.CD, acc);
-                                fk::rys_prim_all<LA, LB, LC, LD, R, true>(s_tab, p1, q, B.AB, Kt.CD, acc);
+                                fk::rys_prim_all<LA, LB, LC, LD, R, true>(s_tab, p0, q, AB, Kt.CD, acc);
+                                fk::rys_prim_all<LA, LB, LC, LD, R, true>(s_tab, p1, q, AB, Kt.CD, acc);
                             }
                         for (; i < bnpp; ++i)
-                            fk::rys_prim_all<LA, LB, LC, LD, R, PAIR>(s_tab, sload_pp(a.pp, ppo + i), q, B.AB, Kt.CD,
+                            fk::rys_prim_all<LA, LB, LC, LD, R, PAIR>(s_tab, sload_pp(a.pp, ppo + i), q, AB, Kt.CD,
                                                                       acc);
                     }
                 }
@@ -931,14 +954,15 @@ __global__ void __launch_bounds__(64 * NW, (LpqBounds<LA, LB, LC, LD, NW>::value
                         for (int i = 0; i < bnpp; ++i)
                             fk::hgp_prim<LA, LB, LC, LD, R>(s_tab, sload_pp(a.pp, ppo + i), q, acce);
                     }
-                    fk::hgp_hrr<LA, LB, LC, LD, R>(acce, B.AB, Kt.CD, acc);
+                    fk::hgp_hrr<LA, LB, LC, LD, R>(acce, AB, Kt.CD, acc);
                 }
             }
-            const bool diag = same && pos == bpos;
-            lpq_digest<LA, LB, LC, LD, R>(acc, active, diag, sa, sb, sc, sd, oa, shbf[sb], oc, od, n, Ds, dcd, kac,
+            const bool diag = same && pos == B.s.pos;
+            lpq_digest<LA, LB, LC, LD, R>(acc, active, diag, sa, B.s.sb, sc, sd, oa, B.s.ob, oc, od, n, Ds, dcd, kac,
                                           kad, jcd, XJ, XK, s_stage, lane, wj, wk, any,
                                           tasks, kr + jb * NB * a.krow_ncol, a.krow_ncol, colc, cold,
                                           kr + (nbk * NB + NA) * a.krow_ncol + jb * NA * NB);
+        }
         }
         // block sums: a lane without work holds zeros, which are not added
         if (__ballot(any) != 0ull) {
@@ -1062,27 +1086,25 @@ __global__ void __launch_bounds__(FK_BLOCK, (TpqMinBlocks<LA, LB, LC, LD>::value
     double *const kr = s_dyn + rys_lds_size(Q::NR) + FK_WAVES * TSh::RED_TASK;
     // one tile (t) for this wave
     auto do_tile = [&](int t) __attribute__((always_inline)) {
-        const FkTile tile = a.tiles[t];
+        const FkTile tile = sload(a.tiles, t);
         const bool same = (tile.grp & FK_TILE_SAME) != 0;
-        const FkGroup g = a.groups[tile.grp & ~FK_TILE_SAME];
+        const FkGroup g = sload(a.groups, tile.grp & ~FK_TILE_SAME);
         const int p0 = tile.p0, p1 = tile.p1;
         // the tile's molecule: its blocks of D, D_sh, X_J, X_K and shells
         const int mol = g.mol;
-        const int n = a.mol_nbf[mol], ns = a.mol_nsh[mol];
-        const int *__restrict shbf = a.sh_bf + a.mol_sh0[mol];
-        const int *kcol = a.krow_col + a.mol_sh0[mol];
+        const int n = sload(a.mol_nbf, mol), ns = sload(a.mol_nsh, mol);
+        const long long mbase = sload(a.mol_base, mol);
         const int cold0 = tasks && LC != LD ? a.krow_cnt[4 * mol + LC] : 0;
         // X_J[a, b] of each bra: the wave's own sums, or the task's
         double *s_jab = tasks ? kr + (nbk * NB + NA) * ncol : s_team + QPW * NV;
         double *kra = kr + (nbk * NB + ia) * ncol;
-        const double *__restrict Ds = a.Ds + a.mol_base[mol];
-        const double *__restrict Dsh = a.Dsh + a.mol_shbase[mol];
-        const long long xoff = (long long)(blockIdx.x % FK_XCD_COPIES) * a.xcopy + a.mol_base[mol];
+        const double *__restrict Ds = a.Ds + mbase;
+        const double *__restrict Dsh = a.Dsh + sload(a.mol_shbase, mol);
+        const long long xoff = (long long)(blockIdx.x % FK_XCD_COPIES) * a.xcopy + mbase;
         double *XJ = a.XJ + xoff;
         double *XK = a.XK + xoff;
-        const FkBraBlock blk = a.blocks[tile.blk];
-        const int sa = a.pair_sa[a.blk_bra[blk.first]];
-        const int oa = shbf[sa];
+        const FkBraBlock blk = sload(a.blocks, tile.blk);
+        const int sa = blk.sa, oa = blk.oa;
         const size_t ra = (size_t)(oa + ia) * n;
         if (!tasks) {
             wave_sync_lds();
@@ -1095,9 +1117,9 @@ __global__ void __launch_bounds__(FK_BLOCK, (TpqMinBlocks<LA, LB, LC, LD>::value
             const int pos = tile.ket_begin + (tin ? k0 + slot : 0);
             const int r = pos - g.begin;
             const KetInfo Kt = load_ket(a, pos);
-            const int sc = Kt.sc, sd = Kt.sd;
-            const int oc = shbf[sc], od = shbf[sd];
-            const int colc = tasks ? kcol[sc] : 0, cold = tasks ? kcol[sd] + cold0 : 0;
+            const int sc = Kt.sc, sd = Kt.sd, oc = Kt.oc, od = Kt.od;
+            const int2 kc = tasks ? a.lst_col[pos] : int2{0, 0};
+            const int colc = kc.x, cold = kc.y + cold0;
             double kac[NC], kad[ND], jcd[NC * ND];
 #pragma unroll
             for (int ic = 0; ic < NC; ++ic) kac[ic] = 0.0;
@@ -1107,19 +1129,17 @@ __global__ void __launch_bounds__(FK_BLOCK, (TpqMinBlocks<LA, LB, LC, LD>::value
             for (int o = 0; o < NC * ND; ++o) jcd[o] = 0.0;
             bool any = false;
 
-            for (int jb = 0; jb < blk.count; ++jb) {
-                const int bra = a.blk_bra[blk.first + jb];
-                const int bpos = a.blk_pos[blk.first + jb];
-                const BraInfo B = load_bra(a, bra);
-                const int sb = B.sb;
-                const bool active = screen_lane<R>(a, tin && (!same || pos <= bpos), B.G * Kt.G, Dsh, ns, sa, sb, sc, sd);
-                const unsigned long long mask = __ballot(active);
-                if (mask == 0ull) continue;
-                const int nact = __popcll(mask) / TS;
+            unsigned any_bra;
+            const unsigned act = screen_block<R>(a, blk, same, tin, pos, Kt, Dsh, ns, any_bra);
+            for (; any_bra; any_bra &= any_bra - 1) {
+                const int jb = __ffs((int)any_bra) - 1;
+                const FkBraRec B = sload(a.blk_rec, blk.first + jb);
+                const double AB[3] = {B.AB[0], B.AB[1], B.AB[2]};
+                const bool active = ((act >> jb) & 1u) != 0u;
+                const int ppo = B.ppo, bnpp = B.s.npp;
+                const int nact = __popcll(__ballot(active)) / TS;
                 cq += p0 == 0 ? nact : 0;
-                cp += (unsigned long long)B.npp * ket_prims(g, a.lst_npp, pos, p0, p1, active && comp == 0, nact);
-                const int ppo = __builtin_amdgcn_readfirstlane(B.ppo);
-                const int bnpp = __builtin_amdgcn_readfirstlane(B.npp);
+                cp += (unsigned long long)bnpp * ket_prims(g, a.lst_npp, pos, p0, p1, active && comp == 0, nact);
                 R acc[NOL];
 #pragma unroll
                 for (int o = 0; o < NOL; ++o) acc[o] = (R)0;
@@ -1129,13 +1149,13 @@ __global__ void __launch_bounds__(FK_BLOCK, (TpqMinBlocks<LA, LB, LC, LD>::value
                         const fk::PrimPair q = qn;
                         if (j + 1 < p1) qn = load_ket_pp(a.ppT, g, j + 1, r);
                         for (int i = 0; i < bnpp; ++i)
-                            fk::rys_prim_team<LA, LB, LC, LD, MODE, R>(s_tab, sload_pp(a.pp, ppo + i), q, B.AB, Kt.CD,
+                            fk::rys_prim_team<LA, LB, LC, LD, MODE, R>(s_tab, sload_pp(a.pp, ppo + i), q, AB, Kt.CD,
                                                                       ax, bx, acc);
                     }
                 }
-                const bool diag = same && pos == bpos;
-                const double fac = (sa == sb ? 0.5 : 1.0) * (sc == sd ? 0.5 : 1.0) * (diag ? 0.5 : 1.0);
-                const int ob = shbf[sb];
+                const bool diag = same && pos == B.s.pos;
+                const double fac = (sa == B.s.sb ? 0.5 : 1.0) * (sc == sd ? 0.5 : 1.0) * (diag ? 0.5 : 1.0);
+                const int ob = B.s.ob;
                 // X_K[b, c] and X_K[b, d] for this bra: team sums, or added to the
                 // task's rows
                 double *const sbc = tasks ? kr + jb * NB * ncol + colc : tsum;
@@ -1231,7 +1251,7 @@ __global__ void __launch_bounds__(FK_BLOCK, (TpqMinBlocks<LA, LB, LC, LD>::value
         if (tasks) return;
         for (int x = lane; x < blk.count * NA * NB; x += 64) {
             const int jb = x / (NA * NB), ab = x % (NA * NB);
-            const int ob = shbf[a.pair_sb[a.blk_bra[blk.first + jb]]];
+            const int ob = a.blk_rec[blk.first + jb].s.ob;
             const double v = s_jab[x];
             if (v != 0.0) atomic_add(&XJ[(size_t)(oa + ab / NB) * n + ob + ab % NB], 2.0 * v);
         }
@@ -1293,38 +1313,36 @@ __global__ void __launch_bounds__(FK_BLOCK) k_jk_wpq(FkJKArgs a)
     double *const kr = s_dyn + rys_lds_size(Q::NR);  // the workgroup's rows of a block task
     // one tile (t) for this group of waves
     auto do_tile = [&](int t) __attribute__((always_inline)) {
-        const FkTile tile = a.tiles[t];
-        // team and wave kernels get blocks of one bra: the tile's kets are
-        // exactly that bra's Schwarz prefix (and same-class triangle)
-        const int bra = a.blk_bra[a.blocks[tile.blk].first];
+        const FkTile tile = sload(a.tiles, t);
+        // wave kernels get blocks of one bra: the tile's kets are exactly that
+        // bra's Schwarz prefix (and same-class triangle)
+        const FkBraBlock blk = sload(a.blocks, tile.blk);
+        const FkBraRec B = sload(a.blk_rec, blk.first);
+        const double AB[3] = {B.AB[0], B.AB[1], B.AB[2]};
         const bool same = (tile.grp & FK_TILE_SAME) != 0;
-        const FkGroup g = a.groups[tile.grp & ~FK_TILE_SAME];
+        const FkGroup g = sload(a.groups, tile.grp & ~FK_TILE_SAME);
         const int p0 = tile.p0, p1 = tile.p1;
         // the tile's molecule: its blocks of D, D_sh, X_J, X_K and shells
         const int mol = g.mol;
-        const int n = a.mol_nbf[mol], ns = a.mol_nsh[mol];
-        const int *__restrict shbf = a.sh_bf + a.mol_sh0[mol];
-        const double *__restrict Ds = a.Ds + a.mol_base[mol];
-        const double *__restrict Dsh = a.Dsh + a.mol_shbase[mol];
-        const long long xoff = (long long)(blockIdx.x % FK_XCD_COPIES) * a.xcopy + a.mol_base[mol];
+        const int n = sload(a.mol_nbf, mol), ns = sload(a.mol_nsh, mol);
+        const long long mbase = sload(a.mol_base, mol);
+        const double *__restrict Ds = a.Ds + mbase;
+        const double *__restrict Dsh = a.Dsh + sload(a.mol_shbase, mol);
+        const long long xoff = (long long)(blockIdx.x % FK_XCD_COPIES) * a.xcopy + mbase;
         double *XJ = a.XJ + xoff;
         double *XK = a.XK + xoff;
-        const BraInfo B = load_bra(a, bra);
-        const int sa = B.sa, sb = B.sb;
-        const int oa = shbf[sa], ob = shbf[sb];
+        const int sa = blk.sa, sb = B.s.sb, oa = blk.oa, ob = B.s.ob;
         unsigned long long live;
         {
             const bool in = lane < tile.ket_count;
             const KetInfo K0 = load_ket(a, tile.ket_begin + (in ? lane : 0));
             bool ok = in;
-            if (a.dscreen) ok = ok && (B.G * K0.G * dmax_args(a, Dsh, ns, sa, sb, K0.sc, K0.sd) >= a.tau);
+            if (a.dscreen) ok = ok && (B.s.G * K0.G * dmax_args(a, Dsh, ns, sa, sb, K0.sc, K0.sd) >= a.tau);
             live = __ballot(ok);
         }
         if (live == 0ull) return;
-        const int *kcol = a.krow_col + a.mol_sh0[mol];
         const int cold0 = tasks && LC != LD ? a.krow_cnt[4 * mol + LC] : 0;
-        const int ppo = __builtin_amdgcn_readfirstlane(B.ppo);
-        const int bnpp = __builtin_amdgcn_readfirstlane(B.npp);
+        const int ppo = B.ppo, bnpp = B.s.npp;
         while (live) {
             const int k = __ffsll((long long)live) - 1;
             live &= live - 1;
@@ -1334,7 +1352,7 @@ __global__ void __launch_bounds__(FK_BLOCK) k_jk_wpq(FkJKArgs a)
             const int r = pos - g.begin;
             if (half == 0) {
                 cq += p0 == 0 ? 1 : 0;
-                cp += (unsigned long long)B.npp * max(min(a.lst_npp[pos], p1) - p0, 0);
+                cp += (unsigned long long)bnpp * max(min(a.lst_npp[pos], p1) - p0, 0);
             }
             double acc[ITEMS][NCD];
 #pragma unroll
@@ -1347,13 +1365,14 @@ __global__ void __launch_bounds__(FK_BLOCK) k_jk_wpq(FkJKArgs a)
                     const fk::PrimPair p = sload_pp(a.pp, ppo + i);
 #pragma unroll
                     for (int it = 0; it < ITEMS; ++it)
-                        if (ival[it]) fk::rys_prim_bra_comp<LA, LB, LC, LD>(s_tab, p, q, B.AB, Kt.CD, iax[it], ibx[it], acc[it]);
+                        if (ival[it]) fk::rys_prim_bra_comp<LA, LB, LC, LD>(s_tab, p, q, AB, Kt.CD, iax[it], ibx[it], acc[it]);
                 }
             }
-            const bool diag = same && a.ket_list[pos] == bra;
+            const bool diag = same && pos == B.s.pos;
             const double fac = (sa == sb ? 0.5 : 1.0) * (sc == sd ? 0.5 : 1.0) * (diag ? 0.5 : 1.0);
-            const int oc = shbf[sc], od = shbf[sd];
-            const int colc = tasks ? kcol[sc] : 0, cold = tasks ? kcol[sd] + cold0 : 0;
+            const int oc = Kt.oc, od = Kt.od;
+            const int2 kc = tasks ? a.lst_col[pos] : int2{0, 0};
+            const int colc = kc.x, cold = kc.y + cold0;
             double jcd[NCD];
 #pragma unroll
             for (int o = 0; o < NCD; ++o) jcd[o] = 0.0;
