@@ -143,21 +143,6 @@ struct QuartetSetup {
     double PQ[3];
 };
 
-// 1/sqrt(x) for x > 0: on the device the hardware estimate refined by two
-// Newton steps y <- y + y (1 - x y^2)/2 (each doubles the correct bits); on the
-// host the library functions.
-FK_HD double fk_rsqrt(double x)
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    double y = __builtin_amdgcn_rsq(x);
-    y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
-    y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
-    return y;
-#else
-    return 1.0 / sqrt(x);
-#endif
-}
-
 // One reciprocal square root serves the quartet: with r = (zeta + eta)^(-1/2),
 // 1/(zeta + eta) = r^2 and, since each pair's K carries sqrt(zeta),
 // K_P K_Q r = K_P K_Q sqrt(zeta eta / (zeta + eta)) (the sqrt(rho) of the
@@ -165,7 +150,7 @@ FK_HD double fk_rsqrt(double x)
 FK_HD QuartetSetup quartet_setup(const PrimPair &p, const PrimPair &q)
 {
     QuartetSetup s;
-    const double r = fk_rsqrt(p.zeta + q.zeta);
+    const double r = rys_rsqrt(p.zeta + q.zeta);
     s.inv = r * r;
     s.PQ[0] = p.P[0] - q.P[0];
     s.PQ[1] = p.P[1] - q.P[1];
@@ -177,7 +162,6 @@ FK_HD QuartetSetup quartet_setup(const PrimPair &p, const PrimPair &q)
     return s;
 }
 
-// Adds the primitive quartet [ab|cd] to acc[NA][NB][NC][ND] (all components).
 // Adds the primitive quartet [ab|cd] to acc[NA][NB][NC][ND] (all components).
 // The set-up (T, prefactor) and the roots and weights are FP64; the 2-D
 // recurrences, transfers and products run in R (double, or float for the

@@ -318,6 +318,16 @@ __device__ __forceinline__ T sload(const T *__restrict p, long long i)
     return v;
 }
 
+// The kernel's arguments (its only parameter), to be read again from here on:
+// the compiler otherwise loads all of them at the kernel's start and keeps them
+// over every loop, more scalars than there are SGPRs.
+__device__ __forceinline__ const FkJKArgs &fresh_args()
+{
+    unsigned long long p = (unsigned long long)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const FkJKArgs *)(const __attribute__((address_space(4))) FkJKArgs *)p;
+}
+
 // Ket pair data at a list position (consecutive lanes: consecutive positions).
 struct KetInfo {
     int sc, sd, oc, od;
@@ -638,8 +648,9 @@ __device__ __forceinline__ void lpq_digest(R *acc, bool active, bool diag, int s
 // Digestion: X_J[a, b_j] is reduced over the wave per bra; X_K[b_j, c],
 // X_K[b_j, d] go to memory per bra; X_K[a, c], X_K[a, d] and X_J[c, d] do not
 // depend on b_j and are summed in registers over the whole block first.
-// Waves per SIMD the compiler must fit in registers (one workgroup of four
-// waves places one per SIMD).  Five lane-per-quartet classes run faster at two
+// Waves per SIMD the compiler must fit in registers; classes of more than two
+// get no more, so that the scheduler spends the registers left over on loads in
+// flight.  Five lane-per-quartet classes run faster at two
 // waves per SIMD with some bytes spilled per lane than at one wave without
 // spills (their register demand is just above half of the file); the others
 // keep the compiler's own choice (measured: C20H42, (fs|ss) on the organic
@@ -653,7 +664,7 @@ struct LpqMinBlocks<0, 0, 0, 0> {
     static constexpr int value = 4;
 };
 template <>
-struct LpqMinBlocks<1, 0, 0, 0> {  // 166 VGPRs, no spill; (H2O)64 34.2 ms, 41.3 at 171 (two waves)
+struct LpqMinBlocks<1, 0, 0, 0> {  // 148 VGPRs; (H2O)64 34.2 ms, 41.3 at two waves
     static constexpr int value = 3;
 };
 template <>
@@ -745,17 +756,13 @@ template <> struct LpqWide<2, 0, 1, 0> { static constexpr bool value = true; };
 template <> struct LpqWide<2, 1, 0, 0> { static constexpr bool value = true; };
 template <> struct LpqWide<2, 1, 1, 0> { static constexpr bool value = true; };
 
-// workgroups per CU the launch bounds ask for with NW waves per workgroup (the
-// same waves per SIMD as LpqMinBlocks workgroups of four waves)
-template <int LA, int LB, int LC, int LD, int NW>
-struct LpqBounds {
-    static constexpr int value = (LpqMinBlocks<LA, LB, LC, LD>::value * FK_WAVES + NW - 1) / NW;
-};
-
 // ENG: the integral engine, 0 Rys quadrature, 1 HGP with early contraction;
 // NW: waves per workgroup
 template <int LA, int LB, int LC, int LD, typename R = double, int ENG = 0, int NW = FK_WAVES>
-__global__ void __launch_bounds__(64 * NW, (LpqBounds<LA, LB, LC, LD, NW>::value)) k_jk_lpq(FkJKArgs a)
+__global__ void __launch_bounds__(64 * NW)
+    __attribute__((amdgpu_waves_per_eu(LpqMinBlocks<LA, LB, LC, LD>::value,
+                                       (LpqMinBlocks<LA, LB, LC, LD>::value > 2 ? LpqMinBlocks<LA, LB, LC, LD>::value : 2))))
+    k_jk_lpq(FkJKArgs a)
 {
     using Q = fk::QClass<LA, LB, LC, LD>;
     constexpr int NA = Q::NA, NB = Q::NB, NC = Q::NC, ND = Q::ND, NOUT = Q::NOUT;
@@ -781,6 +788,7 @@ __global__ void __launch_bounds__(64 * NW, (LpqBounds<LA, LB, LC, LD, NW>::value
     double *const kr = s_dyn + rys_lds_size(Q::NR) + NW * stg;  // the workgroup's K rows of a block task
     // one tile (t) for this wave
     auto do_tile = [&](int t) __attribute__((always_inline)) {
+        const FkJKArgs &a = fresh_args();
         const FkTile tile = sload(a.tiles, t);
         const bool same = (tile.grp & FK_TILE_SAME) != 0;
         const FkGroup g = sload(a.groups, tile.grp & ~FK_TILE_SAME);
@@ -1086,6 +1094,7 @@ __global__ void __launch_bounds__(FK_BLOCK, (TpqMinBlocks<LA, LB, LC, LD>::value
     double *const kr = s_dyn + rys_lds_size(Q::NR) + FK_WAVES * TSh::RED_TASK;
     // one tile (t) for this wave
     auto do_tile = [&](int t) __attribute__((always_inline)) {
+        const FkJKArgs &a = fresh_args();
         const FkTile tile = sload(a.tiles, t);
         const bool same = (tile.grp & FK_TILE_SAME) != 0;
         const FkGroup g = sload(a.groups, tile.grp & ~FK_TILE_SAME);
@@ -1313,6 +1322,7 @@ __global__ void __launch_bounds__(FK_BLOCK) k_jk_wpq(FkJKArgs a)
     double *const kr = s_dyn + rys_lds_size(Q::NR);  // the workgroup's rows of a block task
     // one tile (t) for this group of waves
     auto do_tile = [&](int t) __attribute__((always_inline)) {
+        const FkJKArgs &a = fresh_args();
         const FkTile tile = sload(a.tiles, t);
         // wave kernels get blocks of one bra: the tile's kets are exactly that
         // bra's Schwarz prefix (and same-class triangle)

@@ -29,15 +29,18 @@ struct GHConst {
     double y2[28], w[28];
 };
 
-// 1/sqrt(x) for x > 0: on the device the hardware estimate refined by two
-// Newton steps y <- y (3 - x y^2)/2 (each doubles the correct bits).
+// 1/sqrt(x) for x > 0: on the host the library functions; on the device the
+// hardware estimate y (some 25 bits) and one step of third order: with
+// e = 1 - x y^2, 1/sqrt(x) = y (1 - e)^(-1/2) = y (1 + e/2 + 3 e^2/8 + O(e^3)),
+// five operations and a chain of four where two Newton steps take seven or
+// eight and a chain of six.  What is left out is below 2^-70; the result is
+// within one unit in the last place, as after two Newton steps.
 FK_HD double rys_rsqrt(double x)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
-    double y = __builtin_amdgcn_rsq(x);
-    y = y * fma(-0.5 * x * y, y, 1.5);
-    y = y * fma(-0.5 * x * y, y, 1.5);
-    return y;
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
 #else
     return 1.0 / sqrt(x);
 #endif
@@ -71,6 +74,21 @@ static_assert(rys_table_nint[1] == (int)(RYS_TSWITCH_1 * RYS_UNI_INVH) &&
               rys_table_nint[RYS_UNI_NMAX] == (int)(RYS_TSWITCH_4 * RYS_UNI_INVH) &&
               rys_table_nint[RYS_UNI_NMAX + 1] == RYS_NINT, "table layout");
 
+// The values of one interval's coefficients as the kernels use them: read before
+// the first is used.  The compiler otherwise reads two, waits for them, uses them
+// and reads the next two, one LDS latency after the other down the recurrence.
+template <int M>
+FK_HD void rys_read(const double *__restrict c, int step, double *__restrict v)
+{
+#pragma unroll
+    for (int k = 0; k < M; ++k) v[k] = c[k * step];
+#if defined(__HIP_DEVICE_COMPILE__)
+    static_assert(M == 10, "operands of the statement below");
+    asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7]),
+                      "+v"(v[8]), "+v"(v[9]));
+#endif
+}
+
 // Evaluate the n-point rule at T.  `tab` points at the n-point segment of the
 // table ([interval][coefficient][function], intervals rys_stride(n) apart);
 // gy2/gw at the n-point Gauss-Hermite data (y_i^2 and h_i) for the region
@@ -78,8 +96,8 @@ static_assert(rys_table_nint[1] == (int)(RYS_TSWITCH_1 * RYS_UNI_INVH) &&
 // evaluates the weights only (enough when L = 0).
 //
 // Uniform grid (small n), BRANCHLESS: both rules are evaluated -- a lane
-// beyond the switch reads interval 0, which every such lane shares (one LDS
-// broadcast) -- and the lane's rule selected, so that the code of a primitive
+// beyond the switch reads the last interval, which every such lane shares (one
+// LDS broadcast) -- and the lane's rule selected, so that the code of a primitive
 // quartet is one basic block the compiler can interleave with the next one's
 // (at the cost of both results being live at once).  Otherwise the two rules
 // are separate branches, so a wave whose lanes all lie beyond the switch
@@ -93,23 +111,28 @@ FK_HD void rys_roots_from(double T, const double *__restrict tab, const double *
     static_assert(RYS_NREG == 4 && RYS_REG1_T0 == 16.0 && RYS_REG1_INVH == 1.0 && RYS_REG3_BASE == 56,
                   "closed-form region selection assumes the generated four-region layout");
     if constexpr (N <= RYS_UNI_NMAX && BRANCHLESS) {
+        // every lane beyond the switch reads the end of the last interval
         const bool in_tab = T < rys_tswitch(N);
-        const double y = (in_tab ? T : 0.0) * RYS_UNI_INVH;
+        constexpr double ylast = rys_table_nint[N] * (1.0 - 0x1p-53);
+        const double y = fmin(T * RYS_UNI_INVH, ylast);
         const int iv = (int)y;
         const double x = fma(2.0, y - (double)iv, -1.0);
         const double *c = tab + iv * rys_stride(N);
-        const double sT = rys_rsqrt(in_tab ? 1.0 : T);
+        const double sT = rys_rsqrt(T);  // not used below the switch, where it may be anything (T = 0)
         const double rT = sT * sT;
 #pragma unroll
         for (int i = 0; i < N; ++i) {
-            double vw = c[RYS_DEG * NF + 2 * i + 1];
+            double cw[RYS_DEG + 1], cu[RYS_DEG + 1];
+            rys_read<RYS_DEG + 1>(c + 2 * i + 1, NF, cw);
+            double vw = cw[RYS_DEG];
 #pragma unroll
-            for (int k = RYS_DEG - 1; k >= 0; --k) vw = vw * x + c[k * NF + 2 * i + 1];
+            for (int k = RYS_DEG - 1; k >= 0; --k) vw = vw * x + cw[k];
             w[i] = in_tab ? vw : rys_gh_w[gh_offset(N) + i] * sT;
             if constexpr (NEED_U) {
-                double vu = c[RYS_DEG * NF + 2 * i];
+                rys_read<RYS_DEG + 1>(c + 2 * i, NF, cu);
+                double vu = cu[RYS_DEG];
 #pragma unroll
-                for (int k = RYS_DEG - 1; k >= 0; --k) vu = vu * x + c[k * NF + 2 * i];
+                for (int k = RYS_DEG - 1; k >= 0; --k) vu = vu * x + cu[k];
                 u[i] = in_tab ? vu : rys_gh_y2[gh_offset(N) + i] * rT;
             }
         }
@@ -134,14 +157,17 @@ FK_HD void rys_roots_from(double T, const double *__restrict tab, const double *
         const double *c = tab + iv * rys_stride(N);
 #pragma unroll
         for (int i = 0; i < N; ++i) {
-            double vw = c[RYS_DEG * NF + 2 * i + 1];
+            double cw[RYS_DEG + 1], cu[RYS_DEG + 1];
+            rys_read<RYS_DEG + 1>(c + 2 * i + 1, NF, cw);
+            double vw = cw[RYS_DEG];
 #pragma unroll
-            for (int k = RYS_DEG - 1; k >= 0; --k) vw = vw * x + c[k * NF + 2 * i + 1];
+            for (int k = RYS_DEG - 1; k >= 0; --k) vw = vw * x + cw[k];
             w[i] = vw;
             if constexpr (NEED_U) {
-                double vu = c[RYS_DEG * NF + 2 * i];
+                rys_read<RYS_DEG + 1>(c + 2 * i, NF, cu);
+                double vu = cu[RYS_DEG];
 #pragma unroll
-                for (int k = RYS_DEG - 1; k >= 0; --k) vu = vu * x + c[k * NF + 2 * i];
+                for (int k = RYS_DEG - 1; k >= 0; --k) vu = vu * x + cu[k];
                 u[i] = vu;
             }
         }
@@ -218,11 +244,14 @@ FK_HD void rys_root_at(const RysAt<N> &a, int r, double &u, double &w)
     w = a.gh[N + r] * a.sT;
     if (a.any_tab) {
         const double *c = a.c + 2 * r;
-        double vu = c[RYS_DEG * NF], vw = c[RYS_DEG * NF + 1];
+        double cu[RYS_DEG + 1], cw[RYS_DEG + 1];
+        fk::rys_read<RYS_DEG + 1>(c, NF, cu);
+        fk::rys_read<RYS_DEG + 1>(c + 1, NF, cw);
+        double vu = cu[RYS_DEG], vw = cw[RYS_DEG];
 #pragma unroll
         for (int k = RYS_DEG - 1; k >= 0; --k) {
-            vu = vu * a.x + c[k * NF];
-            vw = vw * a.x + c[k * NF + 1];
+            vu = vu * a.x + cu[k];
+            vw = vw * a.x + cw[k];
         }
         u = a.in_tab ? vu : u;
         w = a.in_tab ? vw : w;
