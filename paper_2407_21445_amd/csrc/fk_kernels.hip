@@ -423,6 +423,20 @@ __device__ __forceinline__ fk::PrimPair load_ket_pp(const double *__restrict ppT
     return p;
 }
 
+// The same for a wave-uniform position.
+__device__ __forceinline__ fk::PrimPair sload_ket_pp(const double *__restrict ppT, const FkGroup &g, int j, int r)
+{
+    const long long q = g.base + (long long)j * FK_NFLD * g.len + r;
+    const int L = g.len;
+    fk::PrimPair p;
+    p.zeta = sload(ppT, q);
+    p.oo2z = sload(ppT, q + L);
+    p.P[0] = sload(ppT, q + 2 * L); p.P[1] = sload(ppT, q + 3 * L); p.P[2] = sload(ppT, q + 4 * L);
+    p.PA[0] = sload(ppT, q + 5 * L); p.PA[1] = sload(ppT, q + 6 * L); p.PA[2] = sload(ppT, q + 7 * L);
+    p.K = sload(ppT, q + 8 * L);
+    return p;
+}
+
 // The bra's primitive records are the same for every lane of the wave: they
 // are read through the constant address space, which the compiler serves with
 // scalar loads into SGPRs (no LDS traffic and no VGPRs for them; the records
@@ -518,6 +532,12 @@ __device__ __forceinline__ void task_loop(const FkJKArgs &a, double *kr, bool ta
     }
 }
 
+// Largest NOUT whose density loads are kept together in front of the digestion
+// (larger classes have no registers for them).
+#ifndef FK_LPQ_LOADS_NOUT
+#define FK_LPQ_LOADS_NOUT 27
+#endif
+
 // Digestion of one bra's contracted quartets with the lane's ket (paper,
 // "Optimised GPU Implementation": the six Fock blocks of a quartet): scales the
 // integrals by the coincidence factors, forms X_J[a, b] (reduced over the wave
@@ -540,6 +560,26 @@ __device__ __forceinline__ void lpq_digest(R *acc, bool active, bool diag, int s
     double jab[NA * NB];
 #pragma unroll
     for (int o = 0; o < NA * NB; ++o) jab[o] = 0.0;
+    // the density blocks of X_K, all on their way before the first is used (D_ab
+    // is the same for every lane: scalar loads)
+    double dbc[NB * NC], dbd[NB * ND], dac[NA * NC], dad[NA * ND];
+    if (active && wk) {
+#pragma unroll
+        for (int ib = 0; ib < NB; ++ib) {
+#pragma unroll
+            for (int ic = 0; ic < NC; ++ic) dbc[ib * NC + ic] = Ds[(size_t)(ob + ib) * n + oc + ic];
+#pragma unroll
+            for (int id = 0; id < ND; ++id) dbd[ib * ND + id] = Ds[(size_t)(ob + ib) * n + od + id];
+        }
+#pragma unroll
+        for (int ia = 0; ia < NA; ++ia) {
+#pragma unroll
+            for (int id = 0; id < ND; ++id) dad[ia * ND + id] = Ds[(size_t)(oa + ia) * n + od + id];
+#pragma unroll
+            for (int ic = 0; ic < NC; ++ic) dac[ia * NC + ic] = Ds[(size_t)(oa + ia) * n + oc + ic];
+        }
+        if constexpr (NOUT <= FK_LPQ_LOADS_NOUT) __builtin_amdgcn_sched_barrier(0);
+    }
     if (active) {
         any = true;
 #pragma unroll
@@ -550,7 +590,7 @@ __device__ __forceinline__ void lpq_digest(R *acc, bool active, bool diag, int s
 #pragma unroll
         for (int ia = 0; ia < NA; ++ia)
 #pragma unroll
-            for (int ib = 0; ib < NB; ++ib) dab[ia * NB + ib] = Ds[(size_t)(oa + ia) * n + ob + ib];
+            for (int ib = 0; ib < NB; ++ib) dab[ia * NB + ib] = sload(Ds, (long long)(oa + ia) * n + ob + ib);
         // X_J[a, b] partial (reduced over the wave below); X_J[c, d] block sum
 #pragma unroll
         for (int ab = 0; ab < NA * NB; ++ab)
@@ -566,14 +606,6 @@ __device__ __forceinline__ void lpq_digest(R *acc, bool active, bool diag, int s
 #pragma unroll
     for (int o = 0; o < NB * ND; ++o) kbd[o] = 0.0;
     if (active && wk) {
-        double dbc[NB * NC], dbd[NB * ND];
-#pragma unroll
-        for (int ib = 0; ib < NB; ++ib) {
-#pragma unroll
-            for (int ic = 0; ic < NC; ++ic) dbc[ib * NC + ic] = Ds[(size_t)(ob + ib) * n + oc + ic];
-#pragma unroll
-            for (int id = 0; id < ND; ++id) dbd[ib * ND + id] = Ds[(size_t)(ob + ib) * n + od + id];
-        }
         // X_K[a, c] += v D_bd and X_K[a, d] += v D_bc (block sums)
 #pragma unroll
         for (int ia = 0; ia < NA; ++ia)
@@ -597,7 +629,7 @@ __device__ __forceinline__ void lpq_digest(R *acc, bool active, bool diag, int s
                 for (int ia = 0; ia < NA; ++ia)
 #pragma unroll
                     for (int id = 0; id < ND; ++id)
-                        s += acc[((ia * NB + ib) * NC + ic) * ND + id] * Ds[(size_t)(oa + ia) * n + od + id];
+                        s += acc[((ia * NB + ib) * NC + ic) * ND + id] * dad[ia * ND + id];
                 kbc[ib * NC + ic] = s;
             }
 #pragma unroll
@@ -607,7 +639,7 @@ __device__ __forceinline__ void lpq_digest(R *acc, bool active, bool diag, int s
                 for (int ia = 0; ia < NA; ++ia)
 #pragma unroll
                     for (int ic = 0; ic < NC; ++ic)
-                        s += acc[((ia * NB + ib) * NC + ic) * ND + id] * Ds[(size_t)(oa + ia) * n + oc + ic];
+                        s += acc[((ia * NB + ib) * NC + ic) * ND + id] * dac[ia * NC + ic];
                 kbd[ib * ND + id] = s;
             }
         }
@@ -1027,6 +1059,15 @@ struct TeamShape {
 };
 
 
+// Doubles of D a team kernel reads together in its digestion, and the largest
+// NC ND whose D_cd stays in registers for a whole round.
+#ifndef FK_TPQ_LOADS
+#define FK_TPQ_LOADS 40
+#endif
+#ifndef FK_TPQ_CDREG
+#define FK_TPQ_CDREG 18
+#endif
+
 // Waves per SIMD the compiler must fit in registers (as for the lane-per-quartet
 // kernels): team classes whose demand is just above half of the file run
 // faster at two waves with some bytes spilled (measured: the d classes on
@@ -1090,6 +1131,8 @@ __global__ void __launch_bounds__(FK_BLOCK, (TpqMinBlocks<LA, LB, LC, LD>::value
     double *tsum = s_team + (lane_ok ? slot : 0) * nvs;
     unsigned long long cq = 0, cp = 0;
 
+    constexpr bool CDREG = NC * ND <= FK_TPQ_CDREG;
+    constexpr int LG0 = FK_TPQ_LOADS / (1 + NC + ND), LG = LG0 < 1 ? 1 : LG0 > NBL ? NBL : LG0;
     // the workgroup's rows of a block task
     double *const kr = s_dyn + rys_lds_size(Q::NR) + FK_WAVES * TSh::RED_TASK;
     // one tile (t) for this wave
@@ -1129,11 +1172,25 @@ __global__ void __launch_bounds__(FK_BLOCK, (TpqMinBlocks<LA, LB, LC, LD>::value
             const int sc = Kt.sc, sd = Kt.sd, oc = Kt.oc, od = Kt.od;
             const int2 kc = tasks ? a.lst_col[pos] : int2{0, 0};
             const int colc = kc.x, cold = kc.y + cold0;
-            double kac[NC], kad[ND], jcd[NC * ND];
+            // what the round's quartets share, read before the bra loop: the
+            // ket's first primitive pair, D_ac and D_ad of the lane's a, D_cd
+            // where there are registers for it
+            const fk::PrimPair q0 = load_ket_pp(a.ppT, g, p0, r);
+            double kac[NC], kad[ND], jcd[NC * ND], dac[NC], dad[ND], dcd[CDREG ? NC * ND : 1];
 #pragma unroll
-            for (int ic = 0; ic < NC; ++ic) kac[ic] = 0.0;
+            for (int ic = 0; ic < NC; ++ic) {
+                kac[ic] = 0.0;
+                dac[ic] = Ds[ra + oc + ic];
+            }
 #pragma unroll
-            for (int id = 0; id < ND; ++id) kad[id] = 0.0;
+            for (int id = 0; id < ND; ++id) {
+                kad[id] = 0.0;
+                dad[id] = Ds[ra + od + id];
+            }
+            if constexpr (CDREG) {
+#pragma unroll
+                for (int o = 0; o < NC * ND; ++o) dcd[o] = Ds[(size_t)(oc + o / ND) * n + od + o % ND];
+            }
 #pragma unroll
             for (int o = 0; o < NC * ND; ++o) jcd[o] = 0.0;
             bool any = false;
@@ -1153,7 +1210,7 @@ __global__ void __launch_bounds__(FK_BLOCK, (TpqMinBlocks<LA, LB, LC, LD>::value
 #pragma unroll
                 for (int o = 0; o < NOL; ++o) acc[o] = (R)0;
                 if (active) {
-                    fk::PrimPair qn = load_ket_pp(a.ppT, g, p0, r);
+                    fk::PrimPair qn = q0;
                     for (int j = p0; j < p1; ++j) {
                         const fk::PrimPair q = qn;
                         if (j + 1 < p1) qn = load_ket_pp(a.ppT, g, j + 1, r);
@@ -1177,20 +1234,34 @@ __global__ void __launch_bounds__(FK_BLOCK, (TpqMinBlocks<LA, LB, LC, LD>::value
                 }
                 if (active) {
                     any = true;
+                    // D_ab, D_bc and D_bd of LG of the lane's components of b at a
+                    // time, all requested before the first is used
+                    double dab[NBL], dbc[NBL * NC], dbd[NBL * ND];
 #pragma unroll
                     for (int jj = 0; jj < NBL; ++jj) {
                         const int ib = (MODE == 1) ? jj : ib0;
-                        const size_t rb = (size_t)(ob + ib) * n;
+                        if (jj % LG == 0) {
+#pragma unroll
+                            for (int k = jj; k < jj + LG && k < NBL; ++k) {
+                                const int ibk = (MODE == 1) ? k : ib0;
+                                const double *Db = Ds + (size_t)(ob + ibk) * n;
+                                dab[k] = Ds[ra + ob + ibk];
+#pragma unroll
+                                for (int ic = 0; ic < NC; ++ic) dbc[k * NC + ic] = Db[oc + ic];
+#pragma unroll
+                                for (int id = 0; id < ND; ++id) dbd[k * ND + id] = Db[od + id];
+                            }
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
                         if (wj) {
-                            const double dab = Ds[ra + ob + ib];
                             double sj = 0.0;
 #pragma unroll
                             for (int ic = 0; ic < NC; ++ic)
 #pragma unroll
                                 for (int id = 0; id < ND; ++id) {
                                     const double v = fac * acc[(jj * NC + ic) * ND + id];
-                                    sj += v * Ds[(size_t)(oc + ic) * n + od + id];
-                                    jcd[ic * ND + id] += v * dab;
+                                    sj += v * (CDREG ? dcd[CDREG ? ic * ND + id : 0] : Ds[(size_t)(oc + ic) * n + od + id]);
+                                    jcd[ic * ND + id] += v * dab[jj];
                                 }
                             lds_add(&s_jab[jb * NA * NB + ia * NB + ib], tasks ? 2.0 * sj : sj);
                         }
@@ -1201,9 +1272,9 @@ __global__ void __launch_bounds__(FK_BLOCK, (TpqMinBlocks<LA, LB, LC, LD>::value
 #pragma unroll
                                 for (int id = 0; id < ND; ++id) {
                                     const double v = fac * acc[(jj * NC + ic) * ND + id];
-                                    kac[ic] += v * Ds[rb + od + id];
-                                    kad[id] += v * Ds[rb + oc + ic];
-                                    kbc += v * Ds[ra + od + id];
+                                    kac[ic] += v * dbd[jj * ND + id];
+                                    kad[id] += v * dbc[jj * NC + ic];
+                                    kbc += v * dad[id];
                                 }
                                 lds_add(&sbc[ib * wbc + ic], kbc);
                             }
@@ -1212,7 +1283,7 @@ __global__ void __launch_bounds__(FK_BLOCK, (TpqMinBlocks<LA, LB, LC, LD>::value
                                 double kbd = 0.0;
 #pragma unroll
                                 for (int ic = 0; ic < NC; ++ic)
-                                    kbd += fac * acc[(jj * NC + ic) * ND + id] * Ds[ra + oc + ic];
+                                    kbd += fac * acc[(jj * NC + ic) * ND + id] * dac[ic];
                                 lds_add(&sbd[ib * wbd + id], kbd);
                             }
                         }
@@ -1357,12 +1428,14 @@ __global__ void __launch_bounds__(FK_BLOCK) k_jk_wpq(FkJKArgs a)
             const int k = __ffsll((long long)live) - 1;
             live &= live - 1;
             const int pos = tile.ket_begin + k;
-            const KetInfo Kt = load_ket(a, pos);
+            // one quartet per wave: the ket's data are scalars
+            const FkKet Kt = sload(a.lst_ket, pos);
+            const double CD[3] = {sload(a.lst_CD, pos), sload(a.lst_CD, a.nlist + pos), sload(a.lst_CD, 2 * a.nlist + pos)};
             const int sc = Kt.sc, sd = Kt.sd;
             const int r = pos - g.begin;
             if (half == 0) {
                 cq += p0 == 0 ? 1 : 0;
-                cp += (unsigned long long)bnpp * max(min(a.lst_npp[pos], p1) - p0, 0);
+                cp += (unsigned long long)bnpp * max(min(sload(a.lst_npp, pos), p1) - p0, 0);
             }
             double acc[ITEMS][NCD];
 #pragma unroll
@@ -1370,18 +1443,18 @@ __global__ void __launch_bounds__(FK_BLOCK) k_jk_wpq(FkJKArgs a)
 #pragma unroll
                 for (int o = 0; o < NCD; ++o) acc[it][o] = 0.0;
             for (int j = p0; j < p1; ++j) {
-                const fk::PrimPair q = load_ket_pp(a.ppT, g, j, r);
+                const fk::PrimPair q = sload_ket_pp(a.ppT, g, j, r);
                 for (int i = 0; i < bnpp; ++i) {
                     const fk::PrimPair p = sload_pp(a.pp, ppo + i);
 #pragma unroll
                     for (int it = 0; it < ITEMS; ++it)
-                        if (ival[it]) fk::rys_prim_bra_comp<LA, LB, LC, LD>(s_tab, p, q, AB, Kt.CD, iax[it], ibx[it], acc[it]);
+                        if (ival[it]) fk::rys_prim_bra_comp<LA, LB, LC, LD>(s_tab, p, q, AB, CD, iax[it], ibx[it], acc[it]);
                 }
             }
             const bool diag = same && pos == B.s.pos;
             const double fac = (sa == sb ? 0.5 : 1.0) * (sc == sd ? 0.5 : 1.0) * (diag ? 0.5 : 1.0);
             const int oc = Kt.oc, od = Kt.od;
-            const int2 kc = tasks ? a.lst_col[pos] : int2{0, 0};
+            const int2 kc = tasks ? sload(a.lst_col, pos) : int2{0, 0};
             const int colc = kc.x, cold = kc.y + cold0;
             double jcd[NCD];
 #pragma unroll
