@@ -59,8 +59,12 @@ inline int aux_streams_used(size_t nclass, int64_t nmat)
 // build; C20H42 9.0, 8.1, 8.0 and 8.0; (H2O)9 cc-pVDZ-type 3.9, 3.3, 3.3 and
 // 3.7; 19.6, 8.2 and 10.1 with whole tiles).  The least matters for the smallest
 // calls: (H2O)4 / STO-3G takes 0.12 ms with 3000-4000, 0.13 with 6000, 0.20
-// with 12000 and 0.70 with whole tiles.
-constexpr double kTileShare = 2.0, kMinTileFlops = 4000.0;
+// with 12000 and 0.70 with whole tiles.  No tile exceeds kMaxTileFlops: beside
+// that much work a further pass costs little, and where the screen drops most
+// of the quartets the class's share is far more than a wave really gets
+// (exchange of 21 waters 22.6 ms without the limit, 21.1 at 2e5, 19.9 at 1e5,
+// 19.2 at 5e4; C20H42 6.63, 6.63, 6.62, 6.70; (H2O)64 168.0, 167.9, 167.6, 173.8).
+constexpr double kTileShare = 2.0, kMinTileFlops = 4000.0, kMaxTileFlops = 1e5;
 // the fixed part of a bra's pass over a round of kets (lists, screen, flushes)
 constexpr double kBraOverheadFlops = 600.0;
 // groups of kets (fk_build_quartets): (H2O)9 cc-pVDZ-type 3.2 ms per build
@@ -1321,10 +1325,11 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
             // A tile is one wave's serial work.  Where a class has few tiles, whole
             // blocks against deeply contracted kets would leave most of the chip
             // waiting for a handful of waves, so a tile's serial work is bounded
-            // (kTileShare, kMinTileFlops): first the block is cut into runs of bras (each
+            // (kTileShare, kMinTileFlops, kMaxTileFlops): first the block is cut into runs of bras (each
             // a block of its own), then a single bra's tile over the kets'
             // primitive pairs.  Large classes keep their whole blocks.
-            const double t_max = std::max(kMinTileFlops, kTileShare * serial_total / (8.0 * (c->ncu > 0 ? c->ncu : 256)));
+            const double share = kTileShare * serial_total / (8.0 * (c->ncu > 0 ? c->ncu : 256));
+            const double t_max = std::max(kMinTileFlops, std::min(kMaxTileFlops, share));
             std::map<std::pair<int, int>, int> runs;  // runs of the present block: (first, count) -> block
             int runs_blk = -1;
             for (const Reach &R : reach) {
