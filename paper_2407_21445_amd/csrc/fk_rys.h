@@ -77,6 +77,9 @@ static_assert(rys_table_nint[1] == (int)(RYS_TSWITCH_1 * RYS_UNI_INVH) &&
 // The values of one interval's coefficients as the kernels use them: read before
 // the first is used.  The compiler otherwise reads two, waits for them, uses them
 // and reads the next two, one LDS latency after the other down the recurrence.
+// rys_read2 reads a root's u and w, which lie side by side, in one go (C20H42
+// 6.63 -> 6.53 ms, exchange of 21 waters 19.9 -> 19.45 against one after the
+// other).
 template <int M>
 FK_HD void rys_read(const double *__restrict c, int step, double *__restrict v)
 {
@@ -86,6 +89,22 @@ FK_HD void rys_read(const double *__restrict c, int step, double *__restrict v)
     static_assert(M == 10, "operands of the statement below");
     asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7]),
                       "+v"(v[8]), "+v"(v[9]));
+#endif
+}
+
+template <int M>
+FK_HD void rys_read2(const double *__restrict c, int step, double *__restrict u, double *__restrict w)
+{
+#pragma unroll
+    for (int k = 0; k < M; ++k) {
+        u[k] = c[k * step];
+        w[k] = c[k * step + 1];
+    }
+#if defined(__HIP_DEVICE_COMPILE__)
+    static_assert(M == 10, "operands of the statement below");
+    asm volatile("" : "+v"(u[0]), "+v"(u[1]), "+v"(u[2]), "+v"(u[3]), "+v"(u[4]), "+v"(u[5]), "+v"(u[6]), "+v"(u[7]),
+                      "+v"(u[8]), "+v"(u[9]), "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]), "+v"(w[4]), "+v"(w[5]),
+                      "+v"(w[6]), "+v"(w[7]), "+v"(w[8]), "+v"(w[9]));
 #endif
 }
 
@@ -123,13 +142,13 @@ FK_HD void rys_roots_from(double T, const double *__restrict tab, const double *
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             double cw[RYS_DEG + 1], cu[RYS_DEG + 1];
-            rys_read<RYS_DEG + 1>(c + 2 * i + 1, NF, cw);
+            if constexpr (NEED_U) rys_read2<RYS_DEG + 1>(c + 2 * i, NF, cu, cw);
+            else rys_read<RYS_DEG + 1>(c + 2 * i + 1, NF, cw);
             double vw = cw[RYS_DEG];
 #pragma unroll
             for (int k = RYS_DEG - 1; k >= 0; --k) vw = vw * x + cw[k];
             w[i] = in_tab ? vw : rys_gh_w[gh_offset(N) + i] * sT;
             if constexpr (NEED_U) {
-                rys_read<RYS_DEG + 1>(c + 2 * i, NF, cu);
                 double vu = cu[RYS_DEG];
 #pragma unroll
                 for (int k = RYS_DEG - 1; k >= 0; --k) vu = vu * x + cu[k];
@@ -158,13 +177,13 @@ FK_HD void rys_roots_from(double T, const double *__restrict tab, const double *
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             double cw[RYS_DEG + 1], cu[RYS_DEG + 1];
-            rys_read<RYS_DEG + 1>(c + 2 * i + 1, NF, cw);
+            if constexpr (NEED_U) rys_read2<RYS_DEG + 1>(c + 2 * i, NF, cu, cw);
+            else rys_read<RYS_DEG + 1>(c + 2 * i + 1, NF, cw);
             double vw = cw[RYS_DEG];
 #pragma unroll
             for (int k = RYS_DEG - 1; k >= 0; --k) vw = vw * x + cw[k];
             w[i] = vw;
             if constexpr (NEED_U) {
-                rys_read<RYS_DEG + 1>(c + 2 * i, NF, cu);
                 double vu = cu[RYS_DEG];
 #pragma unroll
                 for (int k = RYS_DEG - 1; k >= 0; --k) vu = vu * x + cu[k];
@@ -245,8 +264,7 @@ FK_HD void rys_root_at(const RysAt<N> &a, int r, double &u, double &w)
     if (a.any_tab) {
         const double *c = a.c + 2 * r;
         double cu[RYS_DEG + 1], cw[RYS_DEG + 1];
-        fk::rys_read<RYS_DEG + 1>(c, NF, cu);
-        fk::rys_read<RYS_DEG + 1>(c + 1, NF, cw);
+        fk::rys_read2<RYS_DEG + 1>(c, NF, cu, cw);
         double vu = cu[RYS_DEG], vw = cw[RYS_DEG];
 #pragma unroll
         for (int k = RYS_DEG - 1; k >= 0; --k) {
