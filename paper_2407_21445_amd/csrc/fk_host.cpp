@@ -170,7 +170,7 @@ struct fk_ctx {
     DevBuf<FkGroup> d_groups;
     DevBuf<FkTile> d_tiles;
     DevBuf<int2> d_tasks;
-    DevBuf<int> d_krow_col, d_krow_cnt, d_krow_off, d_krow_fn;
+    DevBuf<int> d_krow_cnt, d_krow_off, d_krow_fn;
     DevBuf<FkBraBlock> d_blocks;
     DevBuf<FkBraRec> d_blk_rec;
     DevBuf<FkKet> d_lst_ket;
@@ -299,7 +299,7 @@ void free_device(fk_ctx *c)
     dev_free(c->d_X); dev_free(c->d_Din); dev_free(c->d_Jout); dev_free(c->d_Kout); dev_free(c->d_tiles);
     dev_free(c->d_cnt); dev_free(c->d_blocks); dev_free(c->d_blk_rec); dev_free(c->d_lst_ket); dev_free(c->d_lst_col); dev_free(c->d_lst_npp); dev_free(c->d_lst_sa); dev_free(c->d_lst_sb); dev_free(c->d_lst_CD);
     dev_free(c->d_lst_G); dev_free(c->d_ppT); dev_free(c->d_groups);
-    dev_free(c->d_tasks); dev_free(c->d_krow_col); dev_free(c->d_krow_cnt); dev_free(c->d_krow_off); dev_free(c->d_krow_fn);
+    dev_free(c->d_tasks); dev_free(c->d_krow_cnt); dev_free(c->d_krow_off); dev_free(c->d_krow_fn);
     dev_free(c->d_jeng_tiles); dev_free(c->d_jp_off); dev_free(c->d_dq_base); dev_free(c->d_pos_grp);
     dev_free(c->d_jp); dev_free(c->d_dq);
     dev_free(c->d_bf_atom); dev_free(c->d_atom_xyz); dev_free(c->d_ks_shell); dev_free(c->d_dfit); dev_free(c->d_dfit_bins);
@@ -1070,9 +1070,9 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
         // from one group and step through its largest count together (shorter
         // kets' records are padded with K = 0), so a run takes in the next
         // smaller count while that keeps lanes from idling: down to kGroupFar of
-        // the first count while the run is shorter than kGroupLen, then down to
-        // kGroupNear of it while it is shorter than kGroupLong.  Pruning leaves nearly every count
-        // from 1 to 81 in a small molecule, each with few pairs.
+        // the first count while the run is shorter than kGroupLen.  Pruning
+        // leaves nearly every count from 1 to 81 in a small molecule, each with
+        // few pairs.
         for (size_t i = 0; i < L.size();) {
             size_t j = i;
             const int mi = c->sh_mol[c->pr_sa[L[i]]], top = c->pr_npp[L[i]];
@@ -1275,8 +1275,9 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
             };
             // bra blocks, their quartet counts and, per ket group, the kets their
             // bras reach (the union of the bras' prefixes)
-            struct Reach { int i0, i1, blk, gi; };
+            struct Reach { int i0, i1, blk, gi; size_t cnt0; };
             std::vector<Reach> reach;
+            std::vector<int> reach_cnt;  // bra_reach of each bra of each entry, from cnt0 on
             // kets [0, cnt) of group gi that bra position pb takes
             auto bra_reach = [&](int pb, size_t gi) {
                 const auto &g = c->cls_groups[Q][gi];
@@ -1311,14 +1312,17 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
                     if (c->sh_mol[c->pr_sa[LQ[g.first]]] != bmol) continue;  // kets of the bra's molecule only
                     const int gnpp = c->groups[c->cls_group0[Q] + gi].npp;
                     int hi = 0;
+                    const size_t cnt0 = reach_cnt.size();
                     for (size_t x = i0; x < i1; ++x) {
                         const int cnt = bra_reach(ord[x], gi);
+                        reach_cnt.push_back(cnt);
                         hi = std::max(hi, cnt);
                         qc.nquartet += cnt;
                         qc.nprim += c->pr_npp[LP[ord[x]]] * (npp_before[g.first + cnt] - npp_before[g.first]);
                         serial_total += rounds_of(cnt) * (f_bra + f_prim * c->pr_npp[LP[ord[x]]] * gnpp);
                     }
-                    if (hi > 0) reach.push_back(Reach{(int)i0, (int)i1, blk, (int)gi});
+                    if (hi > 0) reach.push_back(Reach{(int)i0, (int)i1, blk, (int)gi, cnt0});
+                    else reach_cnt.resize(cnt0);
                 }
                 i0 = i1;
             }
@@ -1347,7 +1351,7 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
                         if (x1 > x0 && full_rounds * (cost1 + add) > t_max) break;
                         cost1 += add;
                         nppsum += np;
-                        hi = std::max(hi, bra_reach(ord[x1], R.gi));
+                        hi = std::max(hi, reach_cnt[R.cnt0 + (x1 - R.i0)]);
                     }
                     int blk = R.blk;
                     if (hi > 0 && (x0 > R.i0 || x1 < R.i1)) {
@@ -1480,7 +1484,6 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
         if ((rc = dev_upload(c, c->d_groups, c->groups.data(), c->groups.size()))) return rc;
         if ((rc = dev_upload(c, c->d_tiles, c->tiles.data(), c->tiles.size()))) return rc;
         if ((rc = dev_upload(c, c->d_tasks, c->tasks.data(), c->tasks.size()))) return rc;
-        if ((rc = dev_upload(c, c->d_krow_col, c->krow_col.data(), c->krow_col.size()))) return rc;
         if ((rc = dev_upload(c, c->d_krow_cnt, c->krow_cnt.data(), c->krow_cnt.size()))) return rc;
         if ((rc = dev_upload(c, c->d_krow_off, c->krow_off.data(), c->krow_off.size()))) return rc;
         if ((rc = dev_upload(c, c->d_krow_fn, c->krow_fn.data(), c->krow_fn.size()))) return rc;

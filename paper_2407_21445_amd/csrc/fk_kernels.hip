@@ -696,7 +696,7 @@ struct LpqMinBlocks<0, 0, 0, 0> {
     static constexpr int value = 4;
 };
 template <>
-struct LpqMinBlocks<1, 0, 0, 0> {  // 148 VGPRs; (H2O)64 34.2 ms, 41.3 at two waves
+struct LpqMinBlocks<1, 0, 0, 0> {  // 168 VGPRs, no spill; (H2O)64 29.3 ms (34.2 against 41.3 at two waves when it was set)
     static constexpr int value = 3;
 };
 template <>
@@ -739,6 +739,7 @@ struct LpqMinBlocks<3, 0, 0, 0> {
 // VGPRs, two waves; 49.1 and 45.2 ms without block tasks); (ss|ss) (HGP)
 // 19.7 ms at 4 with block tasks (four workgroups per CU fit their LDS)
 // against 23.2 ms at 8, where the rows would halve the workgroups per CU.
+// The kernels have become faster since: (ps|ss) 29.3 ms, (ss|ss) (Rys) 15.4.
 template <int LA, int LB, int LC, int LD>
 struct LpqKetOuter {
     static constexpr int value = 0;
