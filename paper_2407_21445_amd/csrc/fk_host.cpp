@@ -63,8 +63,16 @@ inline int aux_streams_used(size_t nclass, int64_t nmat)
 // that much work a further pass costs little, and where the screen drops most
 // of the quartets the class's share is far more than a wave really gets
 // (exchange of 21 waters 22.6 ms without the limit, 21.1 at 2e5, 19.9 at 1e5,
-// 19.2 at 5e4; C20H42 6.63, 6.63, 6.62, 6.70; (H2O)64 168.0, 167.9, 167.6, 173.8).
-constexpr double kTileShare = 2.0, kMinTileFlops = 4000.0, kMaxTileFlops = 1e5;
+// 19.2 at 5e4; (H2O)64 168.0, 167.9, 167.6, 173.8; all with blocks of 8 bras).
+constexpr double kTileShare = 2.0, kMinTileFlops = 4000.0, kMaxTileFlops = 7e4;
+// Bras per tile unless the options or the class's schedule say otherwise: the
+// more, the fewer block sums reach memory; the limit on a tile's work cuts the
+// blocks that would be long.  With limits of 1e5 and 8, 16, 32 bras: (H2O)64
+// 166.7, 164.0, 160.4 ms, C20H42 6.53, 6.44, 6.41, batch of five organic
+// molecules 6.96, 6.81, 6.60, exchange of 21 waters 19.4, 19.6, 19.7.  With 32
+// bras and limits of 1e5, 7e4, 5e4: (H2O)64 161.0, 162.6, 164.1, exchange of 21
+// waters 19.6, 18.8, 18.6, C20H42 6.40, 6.42, 6.50.
+constexpr int kBraBlock = 32;
 // the fixed part of a bra's pass over a round of kets (lists, screen, flushes)
 constexpr double kBraOverheadFlops = 600.0;
 // groups of kets (fk_build_quartets): (H2O)9 cc-pVDZ-type 3.2 ms per build
@@ -1160,7 +1168,7 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
     }
     c->tasks.clear();
     // 4. tiles per quartet class (P >= Q): bra blocks from class P, kets from class Q
-    const int bra_block = opts.bra_block > 0 ? std::min(opts.bra_block, FK_MAX_BRA_BLOCK) : 8;
+    const int bra_block = opts.bra_block > 0 ? std::min(opts.bra_block, FK_MAX_BRA_BLOCK) : kBraBlock;
     c->tiles.clear();
     c->blocks.clear();
     c->blk_bra.clear();
@@ -2381,7 +2389,7 @@ int fk_autotune(fk_ctx *c, const double *D, unsigned flags, int reps, void *stre
             const auto &sc = c->sched[q.P * NPC + q.Q];
             rep->la[i] = q.info.la; rep->lb[i] = q.info.lb; rep->lc[i] = q.info.lc; rep->ld[i] = q.info.ld;
             rep->precision[i] = q.prec ? 32 : 64;
-            rep->bra_block[i] = std::max(1, std::min(sc.bb > 0 ? sc.bb : (opts.bra_block > 0 ? opts.bra_block : 8), q.info.bra_block));
+            rep->bra_block[i] = std::max(1, std::min(sc.bb > 0 ? sc.bb : (opts.bra_block > 0 ? opts.bra_block : kBraBlock), q.info.bra_block));
             rep->kets_per_tile[i] = q.info.wave_per_quartet == 0 ? 64 : (sc.kt > 0 ? sc.kt : 2 * (q.info.wave_per_quartet == 3 ? 1 : 64 / std::max(1, q.info.team_size)));
             rep->grid_fraction[i] = sc.gf;
             rep->engine[i] = q.engine;
@@ -2391,7 +2399,7 @@ int fk_autotune(fk_ctx *c, const double *D, unsigned flags, int reps, void *stre
             const fk_ctx::ClassSched sc0 = s0 == start.end() ? fk_ctx::ClassSched{} : s0->second;
             // compare the schedules in effect (a candidate equal to the default is no change)
             auto eff_bb = [&](const fk_ctx::ClassSched &x) {
-                return std::max(1, std::min(x.bb > 0 ? x.bb : (opts.bra_block > 0 ? opts.bra_block : 8), q.info.bra_block));
+                return std::max(1, std::min(x.bb > 0 ? x.bb : (opts.bra_block > 0 ? opts.bra_block : kBraBlock), q.info.bra_block));
             };
             auto eff_kt = [&](const fk_ctx::ClassSched &x) {
                 if (q.info.wave_per_quartet == 0) return 64;
