@@ -778,3 +778,24 @@ def test_team_and_wave_kernels_with_and_without_rows(fk, torch):
     Jt, Kt = oracle.jk(t, E)
     assert np.max(np.abs(J.cpu().numpy() - np.concatenate([Jo.ravel(), Jt.ravel()]))) <= 1e-10
     assert np.max(np.abs(K.cpu().numpy() - np.concatenate([Ko.ravel(), Kt.ravel()]))) <= 1e-10
+
+
+@pytest.mark.parametrize("bra_block", [2, 4, 5, 32])
+def test_bra_blocks_keep_the_screen(fk, torch, bra_block):
+    """The bras of a block are screened together, four at a time: with blocks of
+    any size the same quartets survive the Schwarz bound, the triangle and the
+    density screen as with one bra per tile, and J and K agree within 1e-11
+    (summation order only) -- J and K, K alone, and K beside the J engine with
+    its K-block skip (one bra at a time)."""
+    s = wl.water_sys(3, "ccpvdz-type")
+    D = torch.tensor(_core_D(s), device="cuda")
+    for kw, only, jeng in (({}, None, False), ({}, "K", False), ({"tau_k": 1e-6}, None, True)):
+        res = []
+        for bb in (1, bra_block):
+            c = fk.FockJK(0).set_system(s).build_quartets(tau=1e-8, tau_prim=0.0, bra_block=bb, **kw)
+            J, K = torch.zeros_like(D), torch.zeros_like(D)
+            c.build_jk(D, J, K, only=only, j_engine=jeng, sync=True)
+            res.append((J.cpu().numpy(), K.cpu().numpy(), c.stats()["quartets"]))
+        assert res[0][2] == res[1][2] and res[0][2] > 0
+        assert np.max(np.abs(res[0][0] - res[1][0])) <= 1e-11
+        assert np.max(np.abs(res[0][1] - res[1][1])) <= 1e-11
