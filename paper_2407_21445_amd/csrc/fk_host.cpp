@@ -505,9 +505,29 @@ void prune_primitives(fk_ctx *c, double tau_prim)
     c->pp.swap(npp_new);
 }
 
-// Every index a J/K kernel dereferences, checked on the host before upload:
-// tiles -> pairs, groups and list positions; groups -> transposed records;
-// pairs -> shells and primitive records; shells -> basis-function offsets.
+// The positions of `key` by descending key, equal keys in their present order:
+// byte-wise radix passes, skipping bytes that all keys share (a class's tiles
+// by cost are three passes).  A comparison sort of the tiles, whose every
+// comparison looks up two blocks, took 1.1 of the 9.4 ms that the lists of
+// (H2O)6 / 6-31G*-type take without a device.
+void order_descending(const std::vector<uint64_t> &key, std::vector<int> &ord)
+{
+    const size_t n = key.size();
+    ord.resize(n);
+    std::iota(ord.begin(), ord.end(), 0);
+    uint64_t differ = 0;
+    for (uint64_t k : key) differ |= k ^ key[0];
+    std::vector<int> next(n);
+    for (int shift = 0; shift < 64 && (differ >> shift) != 0; shift += 8) {
+        if (((differ >> shift) & 255) == 0) continue;
+        size_t at[257] = {0};
+        for (uint64_t k : key) ++at[255 - ((k >> shift) & 255) + 1];
+        for (int b = 0; b < 256; ++b) at[b + 1] += at[b];
+        for (int i : ord) next[at[255 - ((key[i] >> shift) & 255)]++] = i;
+        ord.swap(next);
+    }
+}
+
 // XCD-aware order of a lane-per-quartet class's work.  Workgroup g runs on
 // XCD g mod 8, whose L2 (4 MB) serves only that XCD.  The class's bra blocks
 // are cut into eight regions of equal cost by recursive bisection of the
@@ -609,6 +629,10 @@ void order_for_xcds(fk_ctx *c, const QuartetClass &q)
     }
 }
 
+// Every index a J/K kernel dereferences, checked on the host before upload:
+// tiles -> pairs, groups and list positions; groups -> transposed records;
+// pairs -> shells and primitive records; shells -> basis-function offsets.
+// What all tiles of a block, a group or a class share is checked once there.
 int validate_lists(fk_ctx *c)
 {
     const int npair = (int)c->pr_sa.size();
@@ -628,11 +652,17 @@ int validate_lists(fk_ctx *c)
         if (G.begin < 0 || G.len < 1 || G.begin + G.len > nl || G.npp < 1 ||
             G.base < 0 || G.base + (long long)G.npp * FK_NFLD * G.len > (long long)c->ppT.size())
             return fail(c, FK_ERR_STATE, "internal: group %zu is inconsistent", g);
-        for (int r = 0; r < G.len; ++r)
-            if (c->pr_npp[c->ket_list_all[G.begin + r]] > G.npp || c->lst_npp[G.begin + r] != c->pr_npp[c->ket_list_all[G.begin + r]])
+        for (int r = 0; r < G.len; ++r) {
+            const int p = c->ket_list_all[G.begin + r];
+            if (c->pr_npp[p] > G.npp || c->lst_npp[G.begin + r] != c->pr_npp[p])
                 return fail(c, FK_ERR_STATE, "internal: group %zu holds fewer primitives than a pair", g);
+            if (c->lst_sa[G.begin + r] != c->pr_sa[p] || c->lst_sb[G.begin + r] != c->pr_sb[p] ||
+                c->sh_mol[c->pr_sa[p]] != G.mol || c->sh_mol[c->pr_sb[p]] != G.mol)
+                return fail(c, FK_ERR_STATE, "internal: group %zu mixes molecules or pairs", g);
+        }
     }
     if (c->blk_pos.size() != c->blk_bra.size()) return fail(c, FK_ERR_STATE, "internal: bra block arrays differ in size");
+    std::vector<int> blk_npp(c->blocks.size(), 0);  // the largest count of a block's bras
     for (size_t b = 0; b < c->blocks.size(); ++b) {
         const FkBraBlock &B = c->blocks[b];
         if (B.first < 0 || B.count < 1 || B.count > FK_MAX_BRA_BLOCK || (size_t)B.first + B.count > c->blk_bra.size())
@@ -642,22 +672,22 @@ int validate_lists(fk_ctx *c)
             if (p < 0 || p >= npair || q < 0 || q >= nl || c->ket_list_all[q] != p ||
                 c->pr_sa[p] != c->pr_sa[c->blk_bra[B.first]] || c->pr_cls[p] != c->pr_cls[c->blk_bra[B.first]])
                 return fail(c, FK_ERR_STATE, "internal: bra block %zu member %d is inconsistent", b, j);
+            blk_npp[b] = std::max(blk_npp[b], c->pr_npp[p]);
         }
     }
     for (const QuartetClass &qc : c->qclasses) {
         for (int64_t t = qc.tile_off; t < qc.tile_off + qc.ntile; ++t) {
             const FkTile &T = c->tiles[t];
             const int gid = T.grp & ~FK_TILE_SAME;
-            if (T.blk < 0 || T.blk >= (int)c->blocks.size() || gid < 0 || gid >= (int)c->groups.size() ||
+            if (T.blk < 0 || T.blk >= (int)c->blocks.size() || gid < c->cls_group0[qc.Q] || gid >= c->cls_group0[qc.Q + 1] ||
                 T.ket_count < 1 || T.ket_count > 64 || T.p0 >= T.p1 || T.p1 > c->groups[gid].npp)
                 return fail(c, FK_ERR_STATE, "internal: tile %lld is inconsistent", (long long)t);
             const FkBraBlock &B = c->blocks[T.blk];
             if (B.count > qc.info.bra_block)
                 return fail(c, FK_ERR_STATE, "internal: tile %lld has %d bras, its class kernel takes %d",
                             (long long)t, B.count, qc.info.bra_block);
-            for (int j = 0; j < B.count; ++j)
-                if (c->pr_npp[c->blk_bra[B.first + j]] * FK_NFLD > qc.bra_slot || c->pr_cls[c->blk_bra[B.first + j]] != qc.P)
-                    return fail(c, FK_ERR_STATE, "internal: tile %lld bra %d does not fit its class", (long long)t, j);
+            if (blk_npp[T.blk] * FK_NFLD > qc.bra_slot || c->pr_cls[c->blk_bra[B.first]] != qc.P)
+                return fail(c, FK_ERR_STATE, "internal: tile %lld has bras that do not fit its class", (long long)t);
             const FkGroup &G = c->groups[gid];
             if (T.ket_begin < G.begin || T.ket_begin + T.ket_count > G.begin + G.len)
                 return fail(c, FK_ERR_STATE, "internal: tile %lld leaves its group", (long long)t);
@@ -669,8 +699,18 @@ int validate_lists(fk_ctx *c)
         // bra block; every ket's columns lie inside the LDS rows
         if (qc.task_off < 0 || qc.task_off + qc.ntask > (int64_t)c->tasks.size() || qc.krow_ncol < 1 || qc.krow_nbk < 1)
             return fail(c, FK_ERR_STATE, "internal: block tasks of class (%d|%d)", qc.P, qc.Q);
-        int64_t next = 0;
         const int lc = qc.info.lc, ld = qc.info.ld, nc = (lc + 1) * (lc + 2) / 2, nd = (ld + 1) * (ld + 2) / 2;
+        for (int q = c->ket_off[qc.Q]; q < c->ket_off[qc.Q + 1]; ++q) {
+            const int sc = c->lst_sa[q], sd = c->lst_sb[q], m = c->sh_mol[sc];
+            const int cc = c->krow_cnt[4 * m + lc];
+            const int ncm = cc + (lc != ld ? c->krow_cnt[4 * m + ld] : 0);
+            const int xc = c->krow_col[sc], xd = c->krow_col[sd] + (lc != ld ? cc : 0);
+            if (ncm > qc.krow_ncol) return fail(c, FK_ERR_STATE, "internal: block task columns exceed the rows");
+            if (c->sh_l[sc] != lc || c->sh_l[sd] != ld || c->sh_mol[sd] != m ||
+                xc < 0 || xc + nc > cc || xd < (lc != ld ? cc : 0) || xd + nd > ncm)
+                return fail(c, FK_ERR_STATE, "internal: list position %d has columns outside the rows", q);
+        }
+        int64_t next = 0;
         for (int64_t k = qc.task_off; k < qc.task_off + qc.ntask; ++k) {
             const int2 T = c->tasks[k];
             if (T.x != next || T.y < 1 || T.x + T.y > qc.ntile)
@@ -679,21 +719,9 @@ int validate_lists(fk_ctx *c)
             const int blk = c->tiles[qc.tile_off + T.x].blk;
             if (c->blocks[blk].count > qc.krow_nbk)
                 return fail(c, FK_ERR_STATE, "internal: block task %lld has more bras than its rows", (long long)k);
-            for (int i = T.x; i < T.x + T.y; ++i) {
-                const FkTile &tt = c->tiles[qc.tile_off + i];
-                if (tt.blk != blk) return fail(c, FK_ERR_STATE, "internal: block task %lld mixes bra blocks", (long long)k);
-                const int m = c->groups[tt.grp & ~FK_TILE_SAME].mol;
-                const int cc = c->krow_cnt[4 * m + lc];
-                const int ncm = cc + (lc != ld ? c->krow_cnt[4 * m + ld] : 0);
-                if (ncm > qc.krow_ncol) return fail(c, FK_ERR_STATE, "internal: block task columns exceed the rows");
-                for (int q = tt.ket_begin; q < tt.ket_begin + tt.ket_count; ++q) {
-                    const int sc = c->lst_sa[q], sd = c->lst_sb[q];
-                    const int xc = c->krow_col[sc], xd = c->krow_col[sd] + (lc != ld ? cc : 0);
-                    if (c->sh_l[sc] != lc || c->sh_l[sd] != ld || c->sh_mol[sc] != m || c->sh_mol[sd] != m ||
-                        xc < 0 || xc + nc > cc || xd < (lc != ld ? cc : 0) || xd + nd > ncm)
-                        return fail(c, FK_ERR_STATE, "internal: list position %d has columns outside the rows", q);
-                }
-            }
+            for (int i = T.x; i < T.x + T.y; ++i)
+                if (c->tiles[qc.tile_off + i].blk != blk)
+                    return fail(c, FK_ERR_STATE, "internal: block task %lld mixes bra blocks", (long long)k);
         }
         if (next != qc.ntile) return fail(c, FK_ERR_STATE, "internal: block tasks do not cover class (%d|%d)", qc.P, qc.Q);
     }
@@ -1225,6 +1253,16 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
             qc.krow_ncol = 0;
             qc.nw = 4;
             const int kind = qc.info.wave_per_quartet;
+            // workgroups per CU of the class's launch with this much LDS and nw
+            // waves (0: none fit), asked of the runtime once
+            std::map<std::pair<int, int>, int> wgs_cu;
+            auto wgs_per_cu = [&](int lds, int nw) {
+                const auto it = wgs_cu.find({lds, nw});
+                if (it != wgs_cu.end()) return it->second;
+                int nb = 0;
+                if (fk_kernels_max_blocks(P, Q, lds, qc.engine, kind, nw, &nb) != 0) nb = 0;
+                return wgs_cu[{lds, nw}] = nb;
+            };
             const bool may_task = kind != 0 || ((qc.info.ket_outer > 0 || qc.info.wide > 0) &&
                                                 (sch.bt < 0 ? qc.info.ket_outer > 0 : sch.bt != 0));
             if (may_task && opts.block_tasks == 0) {
@@ -1238,9 +1276,7 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
                     const int lds = fk_kernels_jk_lds_bytes(P, Q, qc.bra_slot, nc, kind, nbk, nw);
                     if (lds < 0 || lds > (nw == 4 && kind == 0 ? kKrowLdsMax : kKrowLdsMaxWide)) return 0;
                     if (!dev) return nw;
-                    int nb = 0;
-                    if (fk_kernels_max_blocks(P, Q, lds, qc.engine, kind, nw, &nb) != 0) return 0;
-                    return nb * nw;
+                    return wgs_per_cu(lds, nw) * nw;
                 };
                 const int w0 = dev ? waves_cu(4, bmax, 0) : 1;
                 if (ncol > 0 && w0 > 0) {
@@ -1342,10 +1378,9 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
             // primitive pairs.  Large classes keep their whole blocks.
             const double share = kTileShare * serial_total / (8.0 * (c->ncu > 0 ? c->ncu : 256));
             const double t_max = std::max(kMinTileFlops, std::min(kMaxTileFlops, share));
-            std::map<std::pair<int, int>, int> runs;  // runs of the present block: (first, count) -> block
-            int runs_blk = -1;
+            // runs of the present block by (first, count): the block they were cut from, and their own
+            std::vector<std::pair<int, int>> runs((size_t)bmax * (bmax + 1), {-1, -1});
             for (const Reach &R : reach) {
-                if (R.blk != runs_blk) { runs.clear(); runs_blk = R.blk; }
                 const auto &g = c->cls_groups[Q][R.gi];
                 const int gnpp = c->groups[c->cls_group0[Q] + R.gi].npp;
                 const int full_rounds = rounds_of(std::min(tile_kets, g.second - g.first));
@@ -1363,16 +1398,15 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
                     }
                     int blk = R.blk;
                     if (hi > 0 && (x0 > R.i0 || x1 < R.i1)) {
-                        const auto key = std::make_pair(x0 - R.i0, x1 - x0);
-                        const auto it = runs.find(key);
-                        if (it != runs.end()) blk = it->second;
-                        else {
-                            blk = (int)c->blocks.size();
-                            runs[key] = blk;
-                            c->blocks.push_back(FkBraBlock{c->blocks[R.blk].first + key.first, key.second, c->blocks[R.blk].sa,
-                                                             c->blocks[R.blk].oa});
+                        const int first = x0 - R.i0, count = x1 - x0;
+                        auto &run = runs[(size_t)first * (bmax + 1) + count];
+                        if (run.first != R.blk) {
+                            run = {R.blk, (int)c->blocks.size()};
+                            const FkBraBlock whole = c->blocks[R.blk];
+                            c->blocks.push_back(FkBraBlock{whole.first + first, count, whole.sa, whole.oa});
                             c->blk_nppsum.push_back(nppsum);
                         }
+                        blk = run.second;
                     }
                     int kets = tile_kets, parts = 1;
                     if (x1 - x0 == 1 && full_rounds * cost1 > t_max) {
@@ -1401,56 +1435,65 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
             }
             if (tl.empty()) continue;
             // most expensive tiles first (bra primitives x ket primitives x kets)
-            auto cost = [&](const FkTile &t) { return c->blk_nppsum[t.blk] * (t.p1 - t.p0) * t.ket_count; };
-            std::stable_sort(tl.begin(), tl.end(), [&](const FkTile &x, const FkTile &y) { return cost(x) > cost(y); });
+            std::vector<uint64_t> key(tl.size());  // cost of each tile
+            for (size_t t = 0; t < tl.size(); ++t)
+                key[t] = (uint64_t)(c->blk_nppsum[tl[t].blk] * (tl[t].p1 - tl[t].p0) * tl[t].ket_count);
+            std::vector<int> tord;
+            order_descending(key, tord);
             // block tasks: the tiles of one bra block, cut into chunks that share
             // the block's tiles round-robin (each a similar mix of costs),
             // largest chunks first; the class's tiles are stored in task order
             qc.ntask = 0;
+            qc.tile_off = (int64_t)c->tiles.size();
+            qc.ntile = (int64_t)tl.size();
             if (qc.krow_ncol > 0) {
-                std::stable_sort(tl.begin(), tl.end(), [](const FkTile &x, const FkTile &y) { return x.blk < y.blk; });
+                // the tiles block by block, by cost within a block
+                std::vector<uint64_t> bkey(tl.size());
+                for (size_t t = 0; t < tl.size(); ++t) bkey[t] = ~(uint64_t)tl[tord[t]].blk;
+                std::vector<int> bord;
+                order_descending(bkey, bord);
+                for (int &t : bord) t = tord[t];
+                tord.swap(bord);
                 // the fewest tiles a chunk is cut to: team and wave classes have few
                 // tiles, and their rows are cheap beside them (8, 12, 16, 24: organic
                 // molecule of 324 functions 14.1, 13.7, 13.7, 13.7 ms, batch of five
                 // 6.64, 6.62, 6.84, 7.12, C6H14 0.98, 1.00, 1.04, 1.05)
                 const int64_t least = kind != 0 ? 12 : 16;
                 const int64_t ch = std::max<int64_t>(least, std::min<int64_t>(256, (int64_t)tl.size() / 4096));
-                std::vector<std::vector<FkTile>> chunks;
-                std::vector<double> ccost;
+                struct Chunk { size_t begin, end, step; };  // every step-th position of tord
+                std::vector<Chunk> chunks;
+                std::vector<uint64_t> ccost;
                 for (size_t i = 0; i < tl.size();) {
                     size_t j = i;
-                    while (j < tl.size() && tl[j].blk == tl[i].blk) ++j;
+                    const FkTile &t0 = tl[tord[i]];
+                    int64_t parts = 0;
+                    for (; j < tl.size() && tl[tord[j]].blk == t0.blk; ++j) parts += tl[tord[j]].p1 - tl[tord[j]].p0;
                     const int64_t len = (int64_t)(j - i);
                     // chunks no longer than ch tiles, nor than twice the longest
                     // tile's time for the four or eight waves of the workgroup
-                    double serial = 0;
-                    for (size_t k = i; k < j; ++k)
-                        serial += c->blocks[tl[k].blk].count * f_bra + f_prim * c->blk_nppsum[tl[k].blk] * (tl[k].p1 - tl[k].p0);
+                    const double serial = len * (c->blocks[t0.blk].count * f_bra) + f_prim * c->blk_nppsum[t0.blk] * parts;
                     const int64_t nch = std::min<int64_t>((len + qc.nw - 1) / qc.nw,
                                                           std::max<int64_t>((len + ch - 1) / ch, (int64_t)(serial / (2 * qc.nw * t_max))));
-                    const size_t c0 = chunks.size();
-                    chunks.resize(c0 + nch);
-                    ccost.resize(c0 + nch, 0.0);
-                    for (int64_t k = 0; k < len; ++k) {
-                        chunks[c0 + k % nch].push_back(tl[i + k]);
-                        ccost[c0 + k % nch] += (double)cost(tl[i + k]);
+                    for (int64_t k = 0; k < nch; ++k) {
+                        uint64_t sum = 0;
+                        for (size_t x = i + k; x < j; x += nch) sum += key[tord[x]];
+                        chunks.push_back(Chunk{i + k, j, (size_t)nch});
+                        ccost.push_back(sum);
                     }
                     i = j;
                 }
-                std::vector<int> ord_c(chunks.size());
-                std::iota(ord_c.begin(), ord_c.end(), 0);
-                std::stable_sort(ord_c.begin(), ord_c.end(), [&](int x, int y) { return ccost[x] > ccost[y]; });
+                std::vector<int> ord_c;
+                order_descending(ccost, ord_c);
                 qc.task_off = (int64_t)c->tasks.size();
-                tl.clear();
                 for (int k : ord_c) {
-                    c->tasks.push_back(int2{(int)tl.size(), (int)chunks[k].size()});
-                    tl.insert(tl.end(), chunks[k].begin(), chunks[k].end());
+                    const int first = (int)((int64_t)c->tiles.size() - qc.tile_off);
+                    for (size_t x = chunks[k].begin; x < chunks[k].end; x += chunks[k].step) c->tiles.push_back(tl[tord[x]]);
+                    c->tasks.push_back(int2{first, (int)((int64_t)c->tiles.size() - qc.tile_off) - first});
                 }
                 qc.ntask = (int64_t)chunks.size();
+            } else {
+                for (int t : tord) c->tiles.push_back(tl[t]);
             }
-            qc.tile_off = (int64_t)c->tiles.size();
-            qc.ntile = (int64_t)tl.size();
-            c->tiles.insert(c->tiles.end(), tl.begin(), tl.end());
             c->flops_schwarz += qc.nprim * qc.flops_prim() + qc.nquartet * qc.flops_quartet();
             c->nq_schwarz += qc.nquartet;
             for (int k = 0; k < (split ? 2 : 1); ++k) {
@@ -1463,11 +1506,9 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
                 }
                 q.blocks_per_cu = 1;
                 if (dev) {
-                    int nb = 0;
                     const int lds = fk_kernels_jk_lds_bytes(P, Q, q.bra_slot, q.ntask > 0 ? q.krow_ncol : 0,
                                                             q.info.wave_per_quartet, q.krow_nbk, q.nw);
-                    if (fk_kernels_max_blocks(P, Q, lds, q.engine, q.info.wave_per_quartet, q.nw, &nb) == 0 && nb > 0)
-                        q.blocks_per_cu = nb;
+                    if (const int nb = wgs_per_cu(lds, q.nw)) q.blocks_per_cu = nb;
                 }
                 if ((int)c->qclasses.size() >= FK_MAX_QCLASS)
                     return fail(c, FK_ERR_STATE, "internal: more class launches than FK_MAX_QCLASS");
@@ -1486,10 +1527,6 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
                 c->ev_join.push_back(e);
             }
         }
-        if ((rc = dev_upload(c, c->d_pr_G, c->pr_G.data(), c->pr_G.size()))) return rc;
-        if ((rc = dev_upload(c, c->d_ket, c->ket_list_all.data(), c->ket_list_all.size()))) return rc;
-        if ((rc = dev_upload(c, c->d_lst_sa, c->lst_sa_loc.data(), c->lst_sa_loc.size()))) return rc;
-        if ((rc = dev_upload(c, c->d_lst_sb, c->lst_sb_loc.data(), c->lst_sb_loc.size()))) return rc;
         if ((rc = dev_upload(c, c->d_lst_npp, c->lst_npp.data(), c->lst_npp.size()))) return rc;
         if ((rc = dev_upload(c, c->d_lst_CD, c->lst_CD.data(), c->lst_CD.size()))) return rc;
         if ((rc = dev_upload(c, c->d_lst_G, c->lst_G.data(), c->lst_G.size()))) return rc;
@@ -1687,7 +1724,11 @@ int ensure_jeng(fk_ctx *c)
     }
     c->jeng_toff[kJengNB * kJengNB] = (int64_t)all.size();
     int rc;
-    if ((rc = dev_upload(c, c->d_jeng_tiles, all.data(), all.size())) || (rc = dev_upload(c, c->d_jp_off, jp_off.data(), jp_off.size())) ||
+    if ((rc = dev_upload(c, c->d_pr_G, c->pr_G.data(), c->pr_G.size())) ||
+        (rc = dev_upload(c, c->d_ket, c->ket_list_all.data(), c->ket_list_all.size())) ||
+        (rc = dev_upload(c, c->d_lst_sa, c->lst_sa_loc.data(), c->lst_sa_loc.size())) ||
+        (rc = dev_upload(c, c->d_lst_sb, c->lst_sb_loc.data(), c->lst_sb_loc.size())) ||
+        (rc = dev_upload(c, c->d_jeng_tiles, all.data(), all.size())) || (rc = dev_upload(c, c->d_jp_off, jp_off.data(), jp_off.size())) ||
         (rc = dev_upload(c, c->d_dq_base, dq_base.data(), dq_base.size())) ||
         (rc = dev_upload(c, c->d_pos_grp, pos_grp.data(), pos_grp.size())) ||
         (rc = dev_upload<double>(c, c->d_jp, nullptr, (size_t)std::max<long long>(njp, 1))) ||

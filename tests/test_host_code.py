@@ -1,0 +1,164 @@
+"""The library's host code from inside, without a GPU: a driver includes
+fk_host.cpp, is linked with the kernel objects of the last build, and runs one
+check per process.  Contexts have no device (device -1) unless a check replaces
+the HIP calls it makes by its own."""
+import glob
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PKG = os.path.join(ROOT, "paper_2407_21445_amd")
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+DRIVER = r'''
+#include "fk_host.cpp"
+
+#include <random>
+
+#define CHECK(x)                                                          \
+    do {                                                                  \
+        if (!(x)) { std::printf("%s:%d: %s\n", __FILE__, __LINE__, #x); return 1; } \
+    } while (0)
+
+// order_descending against a stable comparison sort
+static int check_order()
+{
+    std::mt19937_64 rng(5);
+    const uint64_t tops[] = {0, 1, 255, 256, 65535, 1 << 20, ~0ull};
+    for (size_t n : {0, 1, 2, 3, 64, 1000, 4097})
+        for (uint64_t top : tops)
+            for (uint64_t base : {(uint64_t)0, (uint64_t)77 << 32}) {
+                std::vector<uint64_t> key(n);
+                for (auto &k : key) k = base + (top == ~0ull ? rng() : rng() % (top + 1));
+                std::vector<int> got, want(n);
+                order_descending(key, got);
+                std::iota(want.begin(), want.end(), 0);
+                std::stable_sort(want.begin(), want.end(), [&](int x, int y) { return key[x] > key[y]; });
+                CHECK(got == want);
+            }
+    return 0;
+}
+
+// s, p and d shells on eight atoms, mixed contraction; two molecules
+static int small_system(fk_ctx **ctx)
+{
+    CHECK(fk_create(ctx, -1) == FK_OK);
+    const int na = 8;
+    std::vector<int> Z(na, 6), atom, l, np;
+    std::vector<double> xyz, ex, co;
+    for (int a = 0; a < na; ++a) {
+        xyz.insert(xyz.end(), {2.5 * (a % 4) + (a / 4) * 60.0, 0.3 * a, 0.7 * (a % 2)});
+        for (int s = 0; s < 3; ++s) {
+            atom.push_back(a); l.push_back(s); np.push_back(3 - s);
+            for (int k = 0; k < 3 - s; ++k) { ex.push_back(8.0 / (1 + 3 * k + s)); co.push_back(0.3 + 0.2 * k); }
+        }
+    }
+    CHECK(fk_set_geometry(*ctx, na, Z.data(), xyz.data(), 0) == FK_OK);
+    CHECK(fk_set_basis(*ctx, (int)l.size(), atom.data(), l.data(), np.data(), ex.data(), co.data()) == FK_OK);
+    const int mol[na] = {0, 0, 0, 0, 1, 1, 1, 1};
+    CHECK(fk_set_molecules(*ctx, 2, mol) == FK_OK);
+    CHECK(fk_build_quartets(*ctx, nullptr) == FK_OK);
+    return 0;
+}
+
+// every kind of inconsistency is found
+static int check_validation()
+{
+    fk_ctx *c = nullptr;
+    if (small_system(&c)) return 1;
+    CHECK(validate_lists(c) == FK_OK);
+    const QuartetClass *task = nullptr;
+    for (const auto &q : c->qclasses)
+        if (q.ntask > 1 && !task) task = &q;
+    CHECK(task);
+    int bad = 0;
+#define BREAK(lvalue, value)                                              \
+    do {                                                                  \
+        const auto keep = lvalue;                                         \
+        lvalue = value;                                                   \
+        if (validate_lists(c) == FK_OK) { std::printf("not found: %s = %s\n", #lvalue, #value); ++bad; } \
+        lvalue = keep;                                                    \
+    } while (0)
+    for (size_t t : {(size_t)0, c->tiles.size() / 2, c->tiles.size() - 1}) {
+        FkTile &T = c->tiles[t];
+        const int gid = T.grp & ~FK_TILE_SAME;
+        BREAK(T.blk, -1);
+        BREAK(T.blk, (int)c->blocks.size());
+        BREAK(T.grp, (int)c->groups.size());
+        BREAK(T.grp, gid == 0 ? (int)c->groups.size() - 1 : 0);  // a group of another class, or of other kets
+        BREAK(T.ket_count, 0);
+        BREAK(T.ket_count, 65);
+        BREAK(T.p0, T.p1);
+        BREAK(T.p1, (unsigned char)(c->groups[gid].npp + 1));
+        BREAK(T.ket_begin, c->groups[gid].begin - 1);
+        BREAK(T.ket_begin, c->groups[gid].begin + c->groups[gid].len);
+    }
+    const size_t b = c->blocks.size() / 2;
+    BREAK(c->blocks[b].first, -1);
+    BREAK(c->blocks[b].count, FK_MAX_BRA_BLOCK + 1);
+    BREAK(c->blk_bra[c->blocks[b].first], -1);
+    BREAK(c->blk_pos[c->blocks[b].first], c->blk_pos[c->blocks[b].first] + 1);
+    FkGroup &G = c->groups[c->groups.size() / 2];
+    BREAK(G.npp, G.npp_min - 1);
+    BREAK(G.base, (long long)c->ppT.size());
+    BREAK(G.mol, 1 - G.mol);
+    BREAK(c->lst_npp[G.begin], c->lst_npp[G.begin] + 1);
+    BREAK(c->lst_sa[G.begin], c->lst_sa[G.begin] == 0 ? 1 : 0);
+    const int p = c->ket_list_all[G.begin];
+    BREAK(c->ket_list_all[G.begin], (int)c->pr_sa.size());
+    BREAK(c->pr_npp[p], FK_MAX_K * FK_MAX_K + 1);
+    BREAK(c->pr_sb[p], c->nshell);
+    BREAK(c->pr_G[p], std::nan(""));
+    BREAK(c->pr_ppoff[p], -1);
+    QuartetClass &q = const_cast<QuartetClass &>(*task);
+    BREAK(q.bra_slot, 1);
+    BREAK(q.krow_ncol, 1);
+    BREAK(q.krow_nbk, 0);
+    BREAK(c->tasks[q.task_off].y, c->tasks[q.task_off].y + 1);
+    BREAK(c->tasks[q.task_off + 1].x, 0);
+    BREAK(c->krow_col[c->lst_sa[c->ket_off[q.Q]]], 1 << 20);
+    CHECK(bad == 0);
+    CHECK(validate_lists(c) == FK_OK);
+    fk_destroy(c);
+    return 0;
+}
+
+int main(int argc, char **argv)
+{
+    const std::string what = argc > 1 ? argv[1] : "";
+    const int rc = what == "order" ? check_order() : what == "validation" ? check_validation() : 2;
+    std::printf("%s %s\n", what.c_str(), rc == 0 ? "passed" : "failed");
+    return rc;
+}
+'''
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    objs = [o for o in sorted(glob.glob(os.path.join(PKG, "_build", "*.o"))) if os.path.basename(o) != "fk_host.o"]
+    if not os.path.exists(HIPCC) or len(objs) < 14:
+        pytest.skip("needs hipcc and the kernel objects of a build")
+    d = tmp_path_factory.mktemp("driver")
+    src, obj, exe = (str(d / x) for x in ("driver.cpp", "driver.o", "driver"))
+    with open(src, "w") as f:
+        f.write(DRIVER)
+    for cmd in ([HIPCC, "-x", "hip", "-O1", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
+                 "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-DFK_BUILD_MAXL=3", "-Wno-unused-function", "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(PKG, "csrc"),
+                 "-c", src, "-o", obj],
+                [HIPCC, "--offload-arch=gfx950", "-o", exe, obj] + objs +
+                ["-L/opt/rocm/lib", "-Wl,-rpath,/opt/rocm/lib", "-lrocsolver", "-lrocblas"]):
+        r = subprocess.run(cmd, capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr[-4000:]
+    return exe
+
+
+@pytest.mark.parametrize("what", ["order", "validation"])
+def test_host_code(driver, what):
+    """order: the radix order of tiles and chunks equals a stable sort by
+    descending key.  validation: each inconsistency planted in the lists (tiles,
+    blocks, groups, list positions, pairs, block tasks and their columns) is
+    found before anything is uploaded."""
+    r = subprocess.run([driver, what], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and f"{what} passed" in r.stdout, (r.stdout + r.stderr)[-4000:]
