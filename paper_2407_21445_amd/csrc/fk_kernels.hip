@@ -1538,6 +1538,35 @@ __global__ void __launch_bounds__(FK_BLOCK) k_jk_wpq(FkJKArgs a)
 }
 
 // -------------------------------------------------------------- debug ----
+// The ket's primitive pairs in order, f(record) of each, the next one's record on
+// its way while this one's quartet is formed; with PAIR two at a time, straight-line
+// code that the compiler interleaves.  The Schwarz factors of a pair of nine
+// primitives per shell are 6561 primitive quartets one after the other in one
+// lane: the lists of one water cc-pVDZ-type take 3.7 ms, 4.9 with one primitive
+// quartet at a time and its record read in place.
+template <bool PAIR, class F>
+__device__ __forceinline__ void each_ket_prim(const FkDebugArgs &a, int ket, F &&f)
+{
+    const int n = a.pair_npp[ket], o = a.pair_ppoff[ket];
+    fk::PrimPair q0 = load_pp(a.pp, o), q1 = q0;
+    int j = 0;
+    if constexpr (PAIR) {
+        q1 = load_pp(a.pp, o + min(1, n - 1));
+        for (; j + 1 < n; j += 2) {
+            const fk::PrimPair p0 = q0, p1 = q1;
+            q0 = load_pp(a.pp, o + min(j + 2, n - 1));
+            q1 = load_pp(a.pp, o + min(j + 3, n - 1));
+            f(p0);
+            f(p1);
+        }
+    }
+    for (; j < n; ++j) {
+        const fk::PrimPair p = q0;
+        if (j + 1 < n) q0 = load_pp(a.pp, o + j + 1);
+        f(p);
+    }
+}
+
 // Raw contracted integrals of listed quartets (canonical orientation), one
 // lane per quartet (small classes) or one wave per quartet (large classes).
 template <int LA, int LB, int LC, int LD>
@@ -1556,8 +1585,10 @@ __global__ void __launch_bounds__(FK_BLOCK) k_debug_lpq(FkDebugArgs a)
     for (int o = 0; o < Q::NOUT; ++o) acc[o] = 0.0;
     for (int i = 0; i < a.pair_npp[bra]; ++i) {
         const fk::PrimPair p = load_pp(a.pp, a.pair_ppoff[bra] + i);
-        for (int j = 0; j < a.pair_npp[ket]; ++j)
-            fk::rys_prim_all<LA, LB, LC, LD>(s_tab, p, load_pp(a.pp, a.pair_ppoff[ket] + j), AB, CD, acc);
+        constexpr bool PAIR = Q::NOUT <= FK_LPQ_PAIR_NOUT;
+        each_ket_prim<PAIR>(a, ket, [&](const fk::PrimPair &q) __attribute__((always_inline)) {
+            fk::rys_prim_all<LA, LB, LC, LD, double, PAIR>(s_tab, p, q, AB, CD, acc);
+        });
     }
 #pragma unroll
     for (int o = 0; o < Q::NOUT; ++o) a.out[(size_t)q * Q::NOUT + o] = acc[o];
@@ -1585,9 +1616,9 @@ __global__ void __launch_bounds__(FK_BLOCK) k_debug_wpq(FkDebugArgs a)
         for (int o = 0; o < NCD; ++o) acc[o] = 0.0;
         for (int i = 0; i < a.pair_npp[bra]; ++i) {
             const fk::PrimPair p = load_pp(a.pp, a.pair_ppoff[bra] + i);
-            for (int j = 0; j < a.pair_npp[ket]; ++j)
-                fk::rys_prim_bra_comp<LA, LB, LC, LD>(s_tab, p, load_pp(a.pp, a.pair_ppoff[ket] + j), AB, CD, ax, bx,
-                                                      acc);
+            each_ket_prim<false>(a, ket, [&](const fk::PrimPair &q) __attribute__((always_inline)) {
+                fk::rys_prim_bra_comp<LA, LB, LC, LD>(s_tab, p, q, AB, CD, ax, bx, acc);
+            });
         }
 #pragma unroll
         for (int o = 0; o < NCD; ++o) a.out[(size_t)q * Q::NOUT + it * NCD + o] = acc[o];
@@ -1620,8 +1651,9 @@ __global__ void __launch_bounds__(FK_BLOCK) k_debug_tpq(FkDebugArgs a)
     for (int o = 0; o < NBL * NC * ND; ++o) acc[o] = 0.0;
     for (int i = 0; i < a.pair_npp[bra]; ++i) {
         const fk::PrimPair p = load_pp(a.pp, a.pair_ppoff[bra] + i);
-        for (int j = 0; j < a.pair_npp[ket]; ++j)
-            fk::rys_prim_team<LA, LB, LC, LD, MODE>(s_tab, p, load_pp(a.pp, a.pair_ppoff[ket] + j), AB, CD, ax, bx, acc);
+        each_ket_prim<false>(a, ket, [&](const fk::PrimPair &q) __attribute__((always_inline)) {
+            fk::rys_prim_team<LA, LB, LC, LD, MODE>(s_tab, p, q, AB, CD, ax, bx, acc);
+        });
     }
 #pragma unroll
     for (int jb = 0; jb < NBL; ++jb) {
@@ -1650,8 +1682,9 @@ __global__ void __launch_bounds__(FK_BLOCK) k_debug_hgp(FkDebugArgs a)
     for (int o = 0; o < H::NACC; ++o) acce[o] = 0.0;
     for (int i = 0; i < a.pair_npp[bra]; ++i) {
         const fk::PrimPair p = load_pp(a.pp, a.pair_ppoff[bra] + i);
-        for (int j = 0; j < a.pair_npp[ket]; ++j)
-            fk::hgp_prim<LA, LB, LC, LD>(s_tab, p, load_pp(a.pp, a.pair_ppoff[ket] + j), acce);
+        each_ket_prim<false>(a, ket, [&](const fk::PrimPair &q) __attribute__((always_inline)) {
+            fk::hgp_prim<LA, LB, LC, LD>(s_tab, p, q, acce);
+        });
     }
     double out[Q::NOUT];
     fk::hgp_hrr<LA, LB, LC, LD>(acce, AB, CD, out);

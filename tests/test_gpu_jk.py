@@ -12,7 +12,7 @@ import pytest
 import oracle
 from oracle.scf import core_guess, orthogonalizer
 from synth import workloads as wl
-from test_oracle import _rand_sys
+from test_oracle import _rand_sys, _sys
 
 pytestmark = pytest.mark.gpu
 
@@ -65,6 +65,27 @@ def test_device_eri_every_class_and_orientation(fk, torch):
     qs.append([15, 15, 3, 3])
     dev = c.debug_eri(qs, on_device=True)
     host = c.debug_eri(qs, on_device=False)
+    for q, a, h in zip(qs, dev, host):
+        b = oracle.eri_quartet(s, *q)
+        scale = max(1.0, float(np.max(np.abs(b))))
+        assert np.max(np.abs(a - b)) <= 1e-12 * scale, q
+        assert np.max(np.abs(a - h)) <= 1e-13 * scale, q
+
+
+@pytest.mark.parametrize("k", [1, 2, 3, 9])
+def test_device_eri_contraction_depths(fk, torch, k):
+    """Raw (ab|cd) on the device with k primitives in every shell: the ket's
+    1, 4, 9 or 81 primitive pairs (an odd count ends with a single one) are
+    read ahead and, for s and p shells, taken two at a time.  Same bounds as
+    for every class above: the oracle within 1e-12 and the same code on the
+    host within 1e-13 of max(1, |ERI|max)."""
+    rng = np.random.default_rng(50 + k)
+    shells = [{"atom": a, "l": l, "exps": list(rng.uniform(0.2, 3.0, size=k)), "coefs": list(rng.uniform(0.3, 1.0, size=k))}
+              for a in range(2) for l in range(3)]
+    s = _sys(rng.uniform(-1.5, 1.5, size=(2, 3)), shells)
+    c = fk.FockJK(0).set_system(s).build_quartets(tau=0.0)
+    qs = [[0, 0, 0, 0], [3, 0, 3, 0], [1, 0, 3, 0], [1, 3, 4, 0], [4, 1, 4, 1], [2, 0, 3, 0], [2, 4, 5, 1]]
+    dev, host = c.debug_eri(qs, on_device=True), c.debug_eri(qs, on_device=False)
     for q, a, h in zip(qs, dev, host):
         b = oracle.eri_quartet(s, *q)
         scale = max(1.0, float(np.max(np.abs(b))))
