@@ -19,6 +19,10 @@
 // and J = X_J + X_J^T, K = X_K + X_K^T.
 #include <hip/hip_runtime.h>
 
+#include <map>
+#include <mutex>
+#include <utility>
+
 #include "fk_internal.h"
 #include "fk_eri.h"
 #include "fk_hgp.h"
@@ -1798,11 +1802,7 @@ struct Disp {
             if constexpr (WIDE) {
                 if (a->nw == 2 * FK_WAVES) {
                     const void *kw = jk_kernel(low, 0, 0, a->nw);
-                    static int raised_w[2] = {0, 0};
-                    if (lds > 65536 && lds > raised_w[low]) {
-                        if (hipFuncSetAttribute(kw, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess) return -3;
-                        raised_w[low] = lds;
-                    }
+                    if (fk_kernels_raise_lds(kw, lds)) return -3;
                     if (low)
                         hipLaunchKernelGGL((k_jk_lpq<LA, LB, LC, LD, float, 0, 2 * FK_WAVES>), dim3(grid),
                                            dim3(128 * FK_WAVES), lds, st, *a);
@@ -1816,11 +1816,7 @@ struct Disp {
                 if (a->kind == 1) {
                     if (eng != 0) return -2;
                     const void *kt = jk_kernel(low, 0, 1);
-                    static int raised_t[2] = {0, 0};
-                    if (lds > 65536 && lds > raised_t[low]) {
-                        if (hipFuncSetAttribute(kt, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess) return -3;
-                        raised_t[low] = lds;
-                    }
+                    if (fk_kernels_raise_lds(kt, lds)) return -3;
                     if (low) hipLaunchKernelGGL((k_jk_tpq<LA, LB, LC, LD, 1, float>), dim3(grid), dim3(FK_BLOCK), lds, st, *a);
                     else hipLaunchKernelGGL((k_jk_tpq<LA, LB, LC, LD, 1, double>), dim3(grid), dim3(FK_BLOCK), lds, st, *a);
                     return hipGetLastError() == hipSuccess ? 0 : -3;
@@ -1829,11 +1825,7 @@ struct Disp {
             if (low && KIND == 3) return -2;  // f-f bras: FP64 only
             if (eng != 0 && !HGP) return -2;  // HGP only for the classes it is built for
             const void *k = jk_kernel(low, eng);
-            static int raised[2][2] = {{0, 0}, {0, 0}};
-            if (lds > 65536 && lds > raised[low][eng]) {
-                if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess) return -3;
-                raised[low][eng] = lds;
-            }
+            if (fk_kernels_raise_lds(k, lds)) return -3;
             if constexpr (HGP) {
                 if (eng == 1) {
                     if (low) hipLaunchKernelGGL((k_jk_lpq<LA, LB, LC, LD, float, 1>), dim3(grid), dim3(FK_BLOCK), lds, st, *a);
@@ -2486,14 +2478,31 @@ int fk_kernels_jk_lds_bytes(int P, int Q, int bra_slot, int krow_ncol, int kind,
     return -1;
 }
 
+// Lets launches of `kernel` on the present device take `bytes` of dynamic LDS
+// (above 64 KB a kernel has to be told).  The limit is the kernel's, not the
+// context's: it only ever rises, so that the lists of one context, which ask
+// for what their rows need, do not take it from another that is in use.
+int fk_kernels_raise_lds(const void *kernel, int bytes)
+{
+    if (bytes <= 65536) return 0;
+    static std::mutex mutex;
+    static std::map<std::pair<int, const void *>, int> limit;  // by device and kernel
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return -3;
+    std::lock_guard<std::mutex> lock(mutex);
+    int &l = limit[{dev, kernel}];
+    if (bytes <= l) return 0;
+    if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) return -3;
+    l = bytes;
+    return 0;
+}
+
 int fk_kernels_max_blocks(int P, int Q, int dyn_lds_bytes, int engine, int kind, int nw, int *blocks_per_cu)
 {
     const void *k = kern_of(P, Q, engine, kind, nw);
     if (!k) return -2;
     int nb = 0;
-    if (dyn_lds_bytes > 65536 &&
-        hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_lds_bytes) != hipSuccess)
-        return -3;
+    if (fk_kernels_raise_lds(k, dyn_lds_bytes)) return -3;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k, 64 * nw, dyn_lds_bytes) != hipSuccess) return -3;
     *blocks_per_cu = nb;
     return 0;

@@ -820,3 +820,21 @@ def test_bra_blocks_keep_the_screen(fk, torch, bra_block):
         assert res[0][2] == res[1][2] and res[0][2] > 0
         assert np.max(np.abs(res[0][0] - res[1][0])) <= 1e-11
         assert np.max(np.abs(res[0][1] - res[1][1])) <= 1e-11
+
+
+def test_contexts_with_rows_of_different_lengths(fk, torch):
+    """Two live contexts whose block tasks take different amounts of LDS of the
+    same kernels (C14H30 and C6H14, p and d shells): building and running the
+    smaller one between two builds of the larger leaves the larger one's J and K
+    as they were (summation order only, 1e-11)."""
+    def ctx(n):
+        s = wl.alkane_sys(n, "6-31gs-type")
+        c = fk.FockJK(0).set_system(s).build_quartets(tau=1e-10, tau_prim=1e-12)
+        return c, torch.tensor(_rand_D(s["nbf"], 90 + n), device="cuda")
+    a, Da = ctx(14)
+    J0, K0 = [x.clone() for x in a.build_jk(Da, sync=True)]
+    b, Db = ctx(6)
+    b.build_jk(Db, sync=True)
+    J1, K1 = a.build_jk(Da, sync=True)
+    scale = max(1.0, float(J0.abs().max()))
+    assert float((J1 - J0).abs().max()) <= 1e-11 * scale and float((K1 - K0).abs().max()) <= 1e-11 * scale

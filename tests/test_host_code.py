@@ -1,7 +1,7 @@
 """The library's host code from inside, without a GPU: a driver includes
 fk_host.cpp, is linked with the kernel objects of the last build, and runs one
-check per process.  Contexts have no device (device -1) unless a check replaces
-the HIP calls it makes by its own."""
+check per process.  Contexts have no device (device -1); where a check needs a
+HIP call, the driver's own stands in for the runtime's."""
 import glob
 import os
 import subprocess
@@ -125,10 +125,76 @@ static int check_validation()
     return 0;
 }
 
+// The runtime's part in a launch: the LDS limit each kernel was last given, per
+// device, and whether a launch kept to it.
+static int g_dev = 0, g_refused = 0, g_launched = 0;
+static std::map<std::pair<int, const void *>, int> g_limit;
+extern "C" hipError_t hipGetDevice(int *d) { *d = g_dev; return hipSuccess; }
+extern "C" hipError_t hipGetLastError() { return hipSuccess; }
+extern "C" hipError_t hipFuncSetAttribute(const void *k, hipFuncAttribute, int v)
+{
+    g_limit[{g_dev, k}] = v;
+    return hipSuccess;
+}
+extern "C" hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, int, size_t)
+{
+    *n = 1;
+    return hipSuccess;
+}
+static size_t g_lds;
+extern "C" hipError_t __hipPushCallConfiguration(dim3, dim3, size_t lds, hipStream_t)
+{
+    g_lds = lds;
+    return hipSuccess;
+}
+extern "C" hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, hipStream_t *st)
+{
+    *grid = *block = dim3(1);
+    *lds = g_lds;
+    *st = nullptr;
+    return hipSuccess;
+}
+extern "C" hipError_t hipLaunchKernel(const void *k, dim3, dim3, void **, size_t lds, hipStream_t)
+{
+    ++g_launched;
+    if (lds > 65536 && (int)lds > g_limit[{g_dev, k}]) ++g_refused;
+    return hipSuccess;
+}
+
+// two contexts that use one kernel with rows of different lengths, on two devices
+static int check_lds()
+{
+    const int P = pair_class(1, 1);
+    auto probe = [&](int ncol) {
+        int nb = 0;
+        const int lds = fk_kernels_jk_lds_bytes(P, P, 0, ncol, 1, 8, 4);
+        if (lds <= 65536 || lds > 160 * 1024) std::printf("%d columns take %d bytes\n", ncol, lds);
+        return fk_kernels_max_blocks(P, P, lds, 0, 1, 4, &nb) == 0 && nb == 1 && lds > 65536 && lds <= 160 * 1024;
+    };
+    auto launch = [&](int ncol) {
+        FkJKArgs a;
+        std::memset((void *)&a, 0, sizeof a);
+        a.kind = 1; a.nw = 4; a.ntask = 1; a.krow_ncol = ncol; a.krow_nbk = 8;
+        return fk_kernels_launch_jk(P, P, &a, 1, nullptr) == 0;
+    };
+    FkClassInfo info;
+    CHECK(fk_kernels_class_info(P, P, &info) == 0 && info.wave_per_quartet == 1);
+    for (g_dev = 0; g_dev < 2; ++g_dev) {
+        CHECK(probe(440) && launch(440));
+        CHECK(probe(300) && launch(300));
+        CHECK(launch(440));
+        CHECK(probe(480) && launch(440) && launch(480));
+    }
+    std::printf("%d launches, %d beyond their limit\n", g_launched, g_refused);
+    CHECK(g_launched == 10 && g_refused == 0);
+    return 0;
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
-    const int rc = what == "order" ? check_order() : what == "validation" ? check_validation() : 2;
+    const int rc = what == "order" ? check_order() : what == "validation" ? check_validation() :
+                   what == "lds" ? check_lds() : 2;
     std::printf("%s %s\n", what.c_str(), rc == 0 ? "passed" : "failed");
     return rc;
 }
@@ -154,11 +220,12 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["order", "validation"])
+@pytest.mark.parametrize("what", ["order", "validation", "lds"])
 def test_host_code(driver, what):
     """order: the radix order of tiles and chunks equals a stable sort by
     descending key.  validation: each inconsistency planted in the lists (tiles,
     blocks, groups, list positions, pairs, block tasks and their columns) is
-    found before anything is uploaded."""
+    found before anything is uploaded.  lds: a context that asks for less dynamic
+    LDS of a kernel does not take it from one that launches with more."""
     r = subprocess.run([driver, what], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and f"{what} passed" in r.stdout, (r.stdout + r.stderr)[-4000:]
