@@ -86,8 +86,8 @@ __device__ __forceinline__ fk::PrimPair load_pp(const double *__restrict pp, int
 // still carries: a lane keeps one half and adds its partner's copies of it, so
 // N values take N/2 + N/4 + ... exchanges instead of 6 N, and the sums end up
 // spread over lanes, which add them to memory with one instruction.  `idx` is
-// the value whose sum this lane returns, `own` is set in one lane per value
-// (idx may reach past N - 1 in lanes without a value: those own none).
+// the value whose sum this lane returns, `own` is set in exactly one lane per
+// value (wave_sums_owner).
 // Exchanges: half-wave and row swaps (v_permlane32_swap, v_permlane16_swap),
 // then DPP within 16 lanes.  X_J[a, b] of a bra has 1 to 18 values in the lane
 // kernels, once per bra and tile: (H2O)64 217 -> 206 ms per build, C20H42 7.7 ->
@@ -134,23 +134,39 @@ __device__ __forceinline__ double sum_halves(double x, double y, int lane)
         return keep + lane_xor<O>(send);
     }
 }
+// The value whose sum a lane of wave_sums<n> returns, and whether it is the lane
+// to add it: a half that got only the padding of an odd count holds none, and of
+// two lanes that share one value the lower one does.
+__host__ __device__ __forceinline__ constexpr bool wave_sums_owner(int n, int lane, int &idx)
+{
+    int slots = n, have = n;  // values a lane carries, padding included; real ones among them
+    bool own = true;
+    idx = 0;
+    for (int o = 32; o > 0; o >>= 1) {
+        const bool up = (lane & o) != 0;
+        if (slots > 1) {
+            const int h = (slots + 1) / 2;
+            idx += up ? h : 0;
+            have = up ? have - h : (have < h ? have : h);
+            slots = h;
+        } else if (up) {
+            own = false;
+        }
+    }
+    return own && have > 0;
+}
 template <int N, int O = 32>
 __device__ __forceinline__ double wave_sums(double *v, int lane, int &idx, bool &own)
 {
-    if constexpr (O == 32) {
-        idx = 0;
-        own = true;
-    }
+    if constexpr (O == 32) own = wave_sums_owner(N, lane, idx);
     if constexpr (N > 1) {
         constexpr int H = (N + 1) / 2;
 #pragma unroll
         for (int i = 0; i < H; ++i) v[i] = sum_halves<O>(v[i], i + H < N ? v[i + H] : 0.0, lane);
-        if (lane & O) idx += H;
         if constexpr (O > 1) return wave_sums<H, O / 2>(v, lane, idx, own);
         else return v[0];
     } else {
         v[0] = sum_halves<O>(v[0], v[0], lane);
-        if (lane & O) own = false;
         if constexpr (O > 1) return wave_sums<1, O / 2>(v, lane, idx, own);
         else return v[0];
     }
@@ -669,7 +685,7 @@ __device__ __forceinline__ void lpq_digest(R *acc, bool active, bool diag, int s
         int ab;
         bool own;
         const double s = 2.0 * wave_sums<NA * NB>(jab, lane, ab, own);
-        if (own && ab < NA * NB) {
+        if (own) {
             if (tasks) lds_add(&kr_jab[ab], s);
             else atomic_add(&XJ[(size_t)(oa + ab / NB) * n + ob + ab % NB], s);
         }
@@ -1524,11 +1540,11 @@ __global__ void __launch_bounds__(FK_BLOCK) k_jk_wpq(FkJKArgs a)
                 int o;
                 bool own;
                 double s = 2.0 * wave_sums<N0>(jcd, lane, o, own);
-                if (own && o < N0) atomic_add(&XJ[(size_t)(oc + o / ND) * n + od + o % ND], s);
+                if (own) atomic_add(&XJ[(size_t)(oc + o / ND) * n + od + o % ND], s);
                 if constexpr (N1 > 0) {
                     s = 2.0 * wave_sums<N1>(jcd + N0, lane, o, own);
                     o += N0;
-                    if (own && o < NCD) atomic_add(&XJ[(size_t)(oc + o / ND) * n + od + o % ND], s);
+                    if (own) atomic_add(&XJ[(size_t)(oc + o / ND) * n + od + o % ND], s);
                 }
             }
         }
@@ -2134,7 +2150,7 @@ __global__ void __launch_bounds__(FK_BLOCK) k_jeng_jp(FkJengArgs a)
             int h;
             bool own;
             const double sum = wave_sums<NHP>(jp, lane, h, own);
-            if (own && h < NHP && sum != 0.0) atomic_add(&a.jp[jo + (long long)i * NHP + h], sum);
+            if (own && sum != 0.0) atomic_add(&a.jp[jo + (long long)i * NHP + h], sum);
         }
     }
 }
@@ -2476,6 +2492,12 @@ int fk_kernels_jk_lds_bytes(int P, int Q, int bra_slot, int krow_ncol, int kind,
 {
     FK_SWITCH_P(P, lds(Q, bra_slot, krow_ncol, kind, nbk, nw))
     return -1;
+}
+
+int fk_kernels_debug_wave_sums_owner(int n, int lane)
+{
+    int idx = 0;
+    return n >= 1 && n <= FK_WAVE_SUMS_MAX && lane >= 0 && lane < 64 && wave_sums_owner(n, lane, idx) ? idx : -1;
 }
 
 // Lets launches of `kernel` on the present device take `bytes` of dynamic LDS

@@ -657,3 +657,12 @@ def test_cut_tiles_keep_the_quartets(name):
     one.check_indices()
     assert a.info()["nquartet_schwarz"] == one.info()["nquartet_schwarz"]
     assert a.info()["flops_schwarz"] == pytest.approx(one.info()["flops_schwarz"], rel=1e-14)
+
+
+# --------------------------------------------------------- wave sums: one adder per value
+@pytest.mark.parametrize("n", [1, 2, 3, 5, 6, 9, 10, 18, 20, 35, 36, 64])
+def test_wave_sums_have_one_owner(n):
+    """Each of n values summed over a wave is added to memory by exactly one lane
+    (lanes that got only the padding of an odd half add nothing)."""
+    owners = [fk._lib.fk_kernels_debug_wave_sums_owner(n, lane) for lane in range(64)]
+    assert sorted(o for o in owners if o >= 0) == list(range(n))
