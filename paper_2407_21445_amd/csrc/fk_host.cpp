@@ -2931,8 +2931,8 @@ int scf_purify(ScfWork &w, int nocc, int *steps)
         // every few launches whether they are done (typically 25 to 35)
         constexpr int kMax = 301;
         const int ns = fk_scf_purify_state_ints();
-        if (!w.pst.p && ((rc = dev_upload<int>(w.c, w.pst, nullptr, (size_t)kMax * ns)) ||
-                         (rc = dev_upload<double>(w.c, w.ptr, nullptr, (size_t)fk_scf_purify_trace_doubles(kMax)))))
+        if ((rc = dev_upload<int>(w.c, w.pst, nullptr, (size_t)kMax * ns)) ||
+            (rc = dev_upload<double>(w.c, w.ptr, nullptr, (size_t)fk_scf_purify_trace_doubles(kMax))))
             return rc;
         double *buf[4] = {w.T1.p, w.T2.p, w.T3.p, w.G.p};
         SCFCHK(w, fk_scf_reduce(w.Fo.p, nullptr, n, 3, w.part.p, w.scal.p, 0, w.st));

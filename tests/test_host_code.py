@@ -13,6 +13,16 @@ PKG = os.path.join(ROOT, "paper_2407_21445_amd")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 DRIVER = r'''
+extern "C" {
+int test_purify_steps(const double *, double *const *, int, int, int, int, const double *, double *, int *, void *);
+int test_reduce(const double *, const double *, int, int, double *, double *, int, void *);
+int test_lincomb(double *, const double *, const double *, const double *, int, double, double, double, double, void *);
+}
+#include <hip/hip_runtime.h>
+#include "fk_internal.h"
+#define fk_scf_purify_steps test_purify_steps
+#define fk_scf_reduce test_reduce
+#define fk_scf_lincomb test_lincomb
 #include "fk_host.cpp"
 
 #include <random>
@@ -190,11 +200,64 @@ static int check_lds()
     return 0;
 }
 
+// Purification buffers: the second allocation fails once; the next purification
+// must not run without it.
+static int g_mallocs = 0, g_fail_at = 0, g_null_trace = 0, g_purified = 0;
+extern "C" hipError_t hipMalloc(void **p, size_t n)
+{
+    *p = nullptr;
+    if (++g_mallocs == g_fail_at) return hipErrorOutOfMemory;
+    *p = std::calloc(1, n);
+    return hipSuccess;
+}
+extern "C" hipError_t hipFree(void *p)
+{
+    std::free(p);
+    return hipSuccess;
+}
+extern "C" hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+extern "C" hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t)
+{
+    std::memcpy(d, s, n);
+    return hipSuccess;
+}
+// stands in for the step kernels: done at once, one step
+int test_purify_steps(const double *, double *const *, int, int, int, int last, const double *, double *trace, int *state,
+                      void *)
+{
+    ++g_purified;
+    if (!trace || !state) ++g_null_trace;
+    if (state) { state[3 * (last - 1) + 1] = 1; state[3 * (last - 1) + 2] = 0; }
+    return 0;
+}
+int test_reduce(const double *, const double *, int, int, double *, double *, int, void *) { return 0; }
+int test_lincomb(double *, const double *, const double *, const double *, int, double, double, double, double, void *)
+{
+    return 0;
+}
+
+static int check_purify()
+{
+    for (int fail_at = 1; fail_at <= 2; ++fail_at) {
+        fk_ctx c;
+        ScfWork w;
+        w.c = &c;
+        w.n = 4;
+        g_mallocs = 0;
+        g_fail_at = fail_at;
+        g_purified = 0;
+        CHECK(scf_purify(w, 1, nullptr) == FK_ERR_OOM && g_purified == 0);
+        g_fail_at = 0;
+        CHECK(scf_purify(w, 1, nullptr) == FK_OK && g_purified == 1 && g_null_trace == 0);
+    }
+    return 0;
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     const int rc = what == "order" ? check_order() : what == "validation" ? check_validation() :
-                   what == "lds" ? check_lds() : 2;
+                   what == "lds" ? check_lds() : what == "purify" ? check_purify() : 2;
     std::printf("%s %s\n", what.c_str(), rc == 0 ? "passed" : "failed");
     return rc;
 }
@@ -220,12 +283,13 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["order", "validation", "lds"])
+@pytest.mark.parametrize("what", ["order", "validation", "lds", "purify"])
 def test_host_code(driver, what):
     """order: the radix order of tiles and chunks equals a stable sort by
     descending key.  validation: each inconsistency planted in the lists (tiles,
     blocks, groups, list positions, pairs, block tasks and their columns) is
     found before anything is uploaded.  lds: a context that asks for less dynamic
-    LDS of a kernel does not take it from one that launches with more."""
+    LDS of a kernel does not take it from one that launches with more.  purify:
+    after a failed allocation the next purification allocates what is missing."""
     r = subprocess.run([driver, what], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and f"{what} passed" in r.stdout, (r.stdout + r.stderr)[-4000:]
