@@ -459,3 +459,81 @@ def test_core_guess_projector_matches_diagonalisation(fk, sys_):
     X = U / np.sqrt(w) @ U.T
     C = X @ np.linalg.eigh(X @ (T + V) @ X)[1][:, : s["nelec"] // 2]
     assert np.max(np.abs(D - 2.0 * C @ C.T)) <= 1e-9
+
+
+def _hhhe(h1, h2, he, more=()):
+    """Two H and one He with STO-3G-type shells (and shells `more`), four electrons: He's pair and one of H-H."""
+    ex = {1: [3.42525091, 0.62391373, 0.16885540], 2: [6.36242139, 1.15892300, 0.31364979]}
+    Z = [1, 1, 2]
+    return wl.flatten({"Z": np.array(Z, dtype=np.int32), "xyz": np.array([h1, h2, he], dtype=np.float64), "charge": 0,
+                       "name": "HHHe"},
+                      [{"atom": a, "l": 0, "exps": ex[z], "coefs": [0.15432897, 0.53532814, 0.44463454]} for a, z in enumerate(Z)] +
+                      list(more))
+
+
+def _purification_steps(F, nocc):
+    """Steps of the trace-correcting purification of F by its rule in numpy."""
+    off = np.abs(F).sum(1) - np.abs(np.diag(F))
+    lo, hi = np.min(np.diag(F) - off), np.max(np.diag(F) + off)
+    P, extra = (hi * np.eye(len(F)) - F) / (hi - lo), -1
+    for it in range(300):
+        Q = P @ P
+        t1, t2 = np.trace(P), np.trace(Q)
+        if extra < 0 and abs(t1 - t2) < 1e-11:
+            extra = 2
+        if extra == 0:
+            return it
+        extra -= extra > 0
+        P = Q if abs(t2 - nocc) < abs(2 * t1 - t2 - nocc) else 2 * P - Q
+    return None
+
+
+@pytest.mark.parametrize("R,at_least", [(4.0, 0), (10.0, 32), (11.0, 38), (12.0, 42)])
+def test_core_guess_projector_with_small_gaps(fk, R, at_least):
+    """Two H atoms R bohr apart beside He: the gap between their two
+    combinations shrinks from 9e-2 to 3e-6 hartree and the purification's steps
+    pass 32, 40 and nearly 48, between which the host looks at the steps' state.
+    The projector errs by rounding of order n eps |F| / gap; held to 100 times
+    n eps |F| / gap."""
+    s = _hhhe([0, -R / 2, 0], [0, R / 2, 0], [6.0, 0, 0])
+    c = fk.FockJK(0).set_system(s).build_quartets(tau=1e-10)
+    D = c.run_scf(max_iter=0)["D"]
+    S, T, V, _ = c.one_electron()
+    w, U = np.linalg.eigh(S)
+    X = U / np.sqrt(w) @ U.T
+    F = X @ (T + V) @ X
+    e, W = np.linalg.eigh(F)
+    assert _purification_steps(F, 2) >= at_least
+    C = X @ W[:, :2]
+    tol = 100 * len(F) * np.finfo(float).eps * np.max(np.abs(e)) / (e[2] - e[1])
+    assert np.max(np.abs(D - 2.0 * C @ C.T)) <= tol
+
+
+def test_purification_without_a_gap_ends(fk):
+    """Two H atoms so far apart that they share their level to the last bit (the
+    coordinates are powers of two, so each one's integrals round alike) with one
+    pair between them: no projector exists, and the purification ends by its
+    limit of steps.  He's second shell puts a level above theirs, so that they do
+    not lie at the spectrum's bound.  The context then serves a system that has a gap."""
+    B = 2.0 ** 60
+    c = fk.FockJK(0).set_system(_hhhe([-B, 0, 0], [B, 0, 0], [0, 0, 0],
+                                      [{"atom": 2, "l": 0, "exps": [0.6], "coefs": [1.0]}])).build_quartets(tau=1e-10)
+    _, T, V, _ = c.one_electron()
+    h = T + V
+    assert h[0, 0] == h[1, 1] and np.all(h[:2, 2:] == 0.0) and h[0, 1] == 0.0
+    r = c.run_scf()
+    assert r["converged"] == 0 and r["iterations"] == 0
+    assert b"did not converge" in fk._lib.fk_last_error(c._ctx)
+    c.set_system(wl.h2_sto3g()).build_quartets(tau=0.0)
+    assert c.run_scf()["converged"] == 1
+
+
+def test_one_function_has_no_spectrum_bounds(fk):
+    """One basis function: both bounds of the spectrum coincide and the purification
+    refuses them (as it did with its steps decided on the host)."""
+    he = wl.flatten({"Z": np.array([2], dtype=np.int32), "xyz": np.zeros((1, 3)), "charge": 0, "name": "He"},
+                    [{"atom": 0, "l": 0, "exps": [6.36, 1.16, 0.31], "coefs": [0.15, 0.54, 0.44]}])
+    c = fk.FockJK(0).set_system(he).build_quartets(tau=0.0)
+    with pytest.raises(fk.FockJKError) as e:
+        c.run_scf()
+    assert e.value.code == fk.FK_ERR_ARG and "degenerate" in str(e.value)
