@@ -838,3 +838,52 @@ def test_contexts_with_rows_of_different_lengths(fk, torch):
     J1, K1 = a.build_jk(Da, sync=True)
     scale = max(1.0, float(J0.abs().max()))
     assert float((J1 - J0).abs().max()) <= 1e-11 * scale and float((K1 - K0).abs().max()) <= 1e-11 * scale
+
+
+def _split_counts(st):
+    n = {(p, team): 0 for p in (32, 64) for team in (False, True)}
+    for x in st["classes"]:
+        n[x["precision"], x["team_size"] > 1] += x["quartets"]
+    return n
+
+
+@pytest.mark.parametrize("n,tau_prim", [(2, 0.0), (3, 1e-12)])
+def test_cut_tiles_and_padded_groups_in_the_split(fk, torch, n, tau_prim):
+    """The precision split over tiles cut along the kets' primitive pairs and
+    groups of mixed primitive counts: the FP64 and the FP32 launch walk the same
+    tiles and must decide alike, so that together they count every quartet once.
+    An FP32 quartet is below tau_fp32 / D_max in size and errs by some 2^-19 of
+    it (recurrences of a few dozen FP32 operations); it adds at most four times
+    to an element, so J and K are held to 4 N tau_fp32 2^-19 for its N quartets
+    (plus 1e-9 where primitive pairs are pruned) -- a lost quartet of a thousandth
+    of tau_fp32 would show in the counts."""
+    s = wl.water_sys(n, "ccpvdz-type")
+    D = _rand_D(s["nbf"], 80 + n)
+    tau32 = 1e-3
+    J, K, c = _gpu_jk(fk, torch, s, D, tau=0.0, tau_prim=tau_prim, tau_fp32=tau32)
+    Jo, Ko = oracle.jk(s, D)
+    cnt = _split_counts(c.stats())
+    ns = len(s["sh_nprim"])
+    npair = ns * (ns + 1) // 2
+    assert sum(cnt.values()) == npair * (npair + 1) // 2
+    n32 = cnt[32, False] + cnt[32, True]
+    assert n32 > 0 and cnt[64, False] > 0
+    tol = 4 * n32 * tau32 * 2.0 ** -19 + 1e-9
+    assert np.max(np.abs(J - Jo)) <= tol and np.max(np.abs(K - Ko)) <= tol
+
+
+@pytest.mark.parametrize("block_tasks", [True, False])
+def test_team_kernels_in_the_split(fk, torch, block_tasks):
+    """Every class up to (ff|ff) with the precision split, the team kernels with
+    and without rows in LDS, on atoms far enough apart that lane and team classes
+    have quartets on both sides: counts and bounds as above."""
+    s = _rand_sys(43, lmax=3, natom=4, kmax=2)
+    s["xyz"] = np.asarray(s["xyz"]) * 4.0
+    D = _rand_D(s["nbf"], 81)
+    tau32 = 1e-4
+    J, K, c = _gpu_jk(fk, torch, s, D, tau=0.0, tau_fp32=tau32, block_tasks=block_tasks)
+    Jo, Ko = oracle.jk(s, D)
+    cnt = _split_counts(c.stats())
+    assert sum(cnt.values()) == 136 * 137 // 2 and min(cnt.values()) > 0, cnt
+    tol = 4 * (cnt[32, False] + cnt[32, True]) * tau32 * 2.0 ** -19
+    assert np.max(np.abs(J - Jo)) <= tol and np.max(np.abs(K - Ko)) <= tol
