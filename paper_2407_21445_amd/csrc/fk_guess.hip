@@ -93,7 +93,9 @@ __global__ void __launch_bounds__(64 * NW) k_mm(const float *__restrict A, int l
     __shared__ float bpart[NW][2][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int i = lane & 15, g = lane >> 4;
-    const int m0 = blockIdx.y * 16, n0 = blockIdx.x * 32;
+    const long long row0 = ((long long)blockIdx.z * gridDim.y + blockIdx.y) * 16;
+    if (row0 >= M) return;
+    const int m0 = (int)row0, n0 = blockIdx.x * 32;
     f4 acc[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
     float bs[2] = {0.0f, 0.0f};
     auto loadA = [&](int k0) {
@@ -153,7 +155,7 @@ __global__ void __launch_bounds__(64 * NW) k_mm(const float *__restrict A, int l
             }
             C[o] = c;
         }
-        if (EPI == EPI_SUM && blockIdx.y == 0 && l < 16) {
+        if (EPI == EPI_SUM && m0 == 0 && l < 16) {
             float t = 0.0f;
             for (int w = 0; w < NW; ++w)
                 t += (bpart[w][h][l] + bpart[w][h][l + 16]) + (bpart[w][h][l + 32] + bpart[w][h][l + 48]);
@@ -276,12 +278,19 @@ int ok() { return hipGetLastError() == hipSuccess ? 0 : -3; }
 
 unsigned nblk(long long n) { return (unsigned)((n + 255) / 256); }
 
+// tiles of rows over the grid's y and z: y alone ends at 65535, a million rows
+dim3 row_grid(int columns, long long rows)
+{
+    const unsigned gy = (unsigned)std::min<long long>(rows, 32768);
+    return dim3(columns, gy, (unsigned)((rows + gy - 1) / gy));
+}
+
 template <int TA, int TB, int EPI, int NW>
 int mm(const float *A, int lda, const float *B, int ldb, float *C, float *A_out, const float *aux, float *bsum, int M,
        int N, int K, void *stream)
 {
     if (M <= 0 || N <= 0) return 0;
-    const dim3 grid((N + 31) / 32, (M + 15) / 16);
+    const dim3 grid = row_grid((N + 31) / 32, ((long long)M + 15) / 16);
     // operands read along k take four values with one load where every row starts aligned
     const bool ok_a = TA || (lda % 4 == 0 && (uintptr_t)A % 16 == 0), ok_b = !TB || (ldb % 4 == 0 && (uintptr_t)B % 16 == 0);
     if (K % 4 == 0 && ok_a && ok_b)

@@ -226,3 +226,30 @@ def test_mlp_ragged_layers_match_oracle(fk, torch, n, dims):
     for k in range(len(dims) - 1):
         assert np.max(np.abs(gW[k].cpu().numpy() - dWo[k])) <= 1e-4 * np.max(np.abs(dWo[k]))
         assert np.max(np.abs(gb[k].cpu().numpy() - dbo[k])) <= 1e-4 * np.max(np.abs(dbo[k]))
+
+
+def test_mlp_more_rows_than_one_grid_dimension(fk, torch):
+    """1050011 rows are more 16-row tiles than a grid's y can count (65535, at
+    1048560 rows).  Small layers against the same sums in FP64 on the device: an
+    output is a sum of at most 8 products (errors below 8 2^-23 of sum |ab|), a
+    weight gradient a sum over the rows, whose FP32 parts of n / 16 random terms
+    err by about 2^-24 sqrt(n) of its own size; held to 1e-5 and, as above, 1e-4
+    of the largest value."""
+    n, dims = 1050011, [3, 8, 5]
+    Ws, bs = _rand_mlp(23, dims)
+    Wd, bd = _to(torch, Ws), _to(torch, bs)
+    g = torch.Generator(device="cuda").manual_seed(24)
+    X = torch.randn(n, dims[0], device="cuda", generator=g)
+    dY = torch.randn(n, dims[-1], device="cuda", generator=g) + 0.5
+    work = fk.mlp_work(Wd, n)
+    Y = fk.mlp_forward(Wd, bd, X, work)
+    W64 = [w.double().requires_grad_() for w in Wd]
+    b64 = [v.double().requires_grad_() for v in bd]
+    Yo = torch.nn.functional.silu(X.double() @ W64[0] + b64[0]) @ W64[1] + b64[1]
+    assert float((Y - Yo.detach()).abs().max()) <= 1e-5 * float(Yo.detach().abs().max())
+    (Yo * dY.double()).sum().backward()
+    gW = [torch.full_like(W, 7.0) for W in Wd]
+    gb = [torch.full_like(b, 7.0) for b in bd]
+    fk.mlp_backward(Wd, bd, X, work, dY, gW, gb)
+    for got, want in zip(gW + gb, W64 + b64):
+        assert float((got - want.grad).abs().max()) <= 1e-4 * float(want.grad.abs().max())
