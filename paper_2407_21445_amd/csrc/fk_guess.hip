@@ -164,6 +164,71 @@ __global__ void __launch_bounds__(64 * NW) k_mm(const float *__restrict A, int l
     }
 }
 
+// The forward layer for many rows: a workgroup stages 16-deep slabs of 64 rows
+// of X and 64 columns of W in LDS (the next slab's values on their way in
+// registers meanwhile), and each of its four waves multiplies 16 rows by 64
+// columns, k by k as above: the same bits.  Straight from L1/L2 a wave reads X
+// four bytes of a row at a time and once per 32 columns, which bounds many rows:
+// the guess network's forward pass at 60000 rows took 0.72 ms with waves alone
+// (0.52 with vector FMAs on 64 x 64 tiles) and takes 0.31 with slabs, 67 TFLOP/s;
+// one 1024 x 1024 layer of 16384 rows 1.04, 0.65 and 0.39 ms.
+constexpr int TM = 64, TK = 16;
+constexpr int SA = 20, SB = 80;  // row strides in LDS: a wave's reads touch every bank once
+__global__ void __launch_bounds__(256) k_layer_tall(const float *__restrict X, const float *__restrict W,
+                                                    const float *__restrict bias, float *__restrict out,
+                                                    float *__restrict act, int M, int N, int K)
+{
+    __shared__ float As[TM * SA], Bs[TK * SB];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = lane & 15, g = lane >> 4;
+    const long long row0 = ((long long)blockIdx.z * gridDim.y + blockIdx.y) * TM;
+    if (row0 >= M) return;
+    const int n0 = blockIdx.x * TM;
+    // this thread's elements of a slab: X at rows tx >> 4 + 16 r, W at k tx >> 6 + 4 r
+    const int am = threadIdx.x >> 4, ak = threadIdx.x & 15, bk = threadIdx.x >> 6, bn = threadIdx.x & 63;
+    float va[4], vb[4];
+    auto load = [&](int k0) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const long long m = row0 + am + 16 * r;
+            const int ka = k0 + ak, kb = k0 + bk + 4 * r;
+            va[r] = m < M && ka < K ? X[(size_t)m * K + ka] : 0.0f;
+            vb[r] = kb < K && n0 + bn < N ? W[(size_t)kb * N + n0 + bn] : 0.0f;
+        }
+    };
+    f4 acc[4] = {};
+    load(0);
+    for (int k0 = 0; k0 < K; k0 += TK) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            As[(am + 16 * r) * SA + ak] = va[r];
+            Bs[(bk + 4 * r) * SB + bn] = vb[r];
+        }
+        __syncthreads();
+        if (k0 + TK < K) load(k0 + TK);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const float a = As[(16 * wave + i) * SA + 4 * s + g];
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, Bs[(4 * s + g) * SB + 16 * c + i], acc[c], 0, 0, 0);
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const int n = n0 + 16 * c + i;
+        if (n >= N) continue;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const long long m = row0 + 16 * wave + 4 * g + r;
+            if (m >= M) continue;
+            const float v = acc[c][r] + bias[n];
+            out[(size_t)m * N + n] = v;
+            if (act) act[(size_t)m * N + n] = v / (1.0f + expf(-v));
+        }
+    }
+}
+
 // Masked squared error over the (width x width) blocks of each row: entry
 // (i, j) of row r counts if i < shape_r >> 8 and j < shape_r & 255.
 // dY = 2 (Y - T) mask / count; per-workgroup partial sums of the squares.
@@ -310,6 +375,16 @@ extern "C" {
 int fk_guess_layer(const float *X, const float *W, const float *bias, float *out, float *act, int M, int N, int K,
                    void *stream)
 {
+    // Slabs from 128 tiles of 64 x 64 outputs on, half a tile per CU; below, sixteen-row
+    // waves fill more of the chip.  256 x 256 layer, waves and slabs: 1000 rows (64 tiles)
+    // 14.0 and 15.6 us, 1500 (96) 14.6 and 15.7, 2048 (128) 16.8 and 15.9, 4096 27.3 and
+    // 16.5; 1024 x 1024: 100 rows (32) 40.6 and 47.4, 500 (128) 51.0 and 47.0.
+    const long long rt = ((long long)M + TM - 1) / TM, ct = (N + TM - 1) / TM;
+    if (M > 0 && rt * ct >= 128) {
+        hipLaunchKernelGGL(k_layer_tall, row_grid((int)ct, rt), dim3(256), 0, (hipStream_t)stream, X, W, bias, out, act, M, N,
+                           K);
+        return ok();
+    }
     return mm<0, 0, EPI_BIAS, 1>(X, K, W, N, out, act, bias, nullptr, M, N, K, stream);
 }
 

@@ -253,3 +253,42 @@ def test_mlp_more_rows_than_one_grid_dimension(fk, torch):
     fk.mlp_backward(Wd, bd, X, work, dY, gW, gb)
     for got, want in zip(gW + gb, W64 + b64):
         assert float((got - want.grad).abs().max()) <= 1e-4 * float(want.grad.abs().max())
+
+
+@pytest.mark.parametrize("n,din,dout", [(8128, 3, 5), (8129, 17, 64), (2049, 16, 225), (2048, 37, 250), (513, 31, 1023)])
+def test_mlp_forward_of_many_rows_is_the_same_chain(fk, torch, n, din, dout):
+    """From 128 tiles of 64 x 64 outputs on the forward layer stages slabs in LDS
+    (8128 rows of one column of tiles are 127: the last without).  Every output is
+    the same chain of products added in the order of k as in a call with few rows,
+    so the two agree bit for bit, on ragged rows, columns and depths; and a sum of
+    din products errs by less than din 2^-24 sum |xw|, held to 1e-5 of the largest."""
+    (W,), (b,) = _rand_mlp(25, [din, dout])
+    Wd, bd = _to(torch, [W]), _to(torch, [b])
+    X = torch.randn(n, din, device="cuda", generator=torch.Generator(device="cuda").manual_seed(26))
+    Y = fk.mlp_forward(Wd, bd, X, fk.mlp_work(Wd, n))
+    few = torch.cat([fk.mlp_forward(Wd, bd, x.contiguous(), fk.mlp_work(Wd, n)) for x in X.split(100)])
+    assert torch.equal(Y, few)
+    want = X.double() @ Wd[0].double() + bd[0].double()
+    assert float((Y - want).abs().max()) <= 1e-5 * float(want.abs().max())
+
+
+def test_mlp_forward_equals_a_chain_of_fused_products(fk, torch):
+    """The forward layer's outputs are fma(x_k, w_k, sum) over k = 0, 1, ... with
+    the bias added last, bit for bit, in either kernel (5 and 8200 rows; 19
+    products, which no slice of 16 divides)."""
+    import ctypes
+    import ctypes.util
+    fmaf = ctypes.CDLL(ctypes.util.find_library("m")).fmaf
+    fmaf.argtypes, fmaf.restype = [ctypes.c_float] * 3, ctypes.c_float
+    (W,), (b,) = _rand_mlp(27, [19, 7])
+    Wd, bd = _to(torch, [W]), _to(torch, [b])
+    X = np.random.default_rng(28).normal(size=(8200, 19)).astype(np.float32)
+    for n in (5, 8200):
+        Xd = torch.tensor(X[-n:], device="cuda")
+        Y = fk.mlp_forward(Wd, bd, Xd, fk.mlp_work(Wd, n)).cpu().numpy()
+        for r in (0, 3, n - 1):
+            for c in range(7):
+                s = 0.0
+                for k in range(19):
+                    s = fmaf(float(X[-n:][r, k]), float(W[k, c]), s)
+                assert Y[r, c] == np.float32(np.float32(s) + b[c]), (n, r, c)
