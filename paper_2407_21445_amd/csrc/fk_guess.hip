@@ -29,16 +29,18 @@ namespace {
 // A training step's products are small (2048 x 256 x 256) and chained, so what
 // counts is the time of one tile and how many run at once, not operand reuse: a
 // workgroup computes 16 x 32 outputs, operands coming from L1/L2 straight into
-// registers.  The forward layers give each tile to one wave, which multiplies k
-// by k: the matrix instruction adds its four products one after the other, so
-// an output is the same chain of FMAs as in a scalar loop (equal bit for bit),
-// and 2048 rows make 1024 waves.  The backward products split K over NW waves
-// (every NW-th 16-deep slice; the lane group g takes k = 4 g + j in step j, so
-// that a lane reads four consecutive k with one load) and add the waves' parts
-// in LDS in a fixed order: 16 waves turn a weight gradient's sum over 2048 rows,
-// which had 16 workgroups of 64 x 64 outputs, into 128 workgroups of 8 slices
-// per wave.  Forward, loss and backward at 2048 rows: 1.54 ms with vector FMAs
-// in 64 x 64 tiles, 0.13 ms with these (0.10 with the forward split as well,
+// registers.  The forward layers (of few rows; many stage slabs, k_layer_tall)
+// give each tile to one wave, which multiplies k by k: the matrix instruction
+// adds its four products one after the other, so an output is the same chain of
+// FMAs as in a scalar loop (equal bit for bit); its operands are read value by
+// value in that order.  The backward products split K over NW waves (4 for the
+// input gradient, 16 for the weight gradient; every NW-th 16-deep slice; the lane
+// group g takes k = 4 g + j in step j, so that the input gradient, whose operands
+// both lie along k, reads four consecutive k with one load) and add the waves'
+// parts in LDS in a fixed order: 16 waves turn a weight gradient's sum over 2048
+// rows, which had 16 workgroups of 64 x 64 outputs, into 128 workgroups of 8
+// slices per wave.  Forward, loss and backward at 2048 rows: 1.54 ms with vector
+// FMAs in 64 x 64 tiles, 0.13 ms with these (0.10 with the forward split as well,
 // whose sums round differently).
 constexpr int EPI_BIAS = 0, EPI_SILU = 1, EPI_SUM = 2;
 typedef float f4 __attribute__((ext_vector_type(4)));
@@ -356,10 +358,11 @@ int mm(const float *A, int lda, const float *B, int ldb, float *C, float *A_out,
 {
     if (M <= 0 || N <= 0) return 0;
     const dim3 grid = row_grid((N + 31) / 32, ((long long)M + 15) / 16);
-    // operands read along k take four values with one load where every row starts aligned
-    const bool ok_a = TA || (lda % 4 == 0 && (uintptr_t)A % 16 == 0), ok_b = !TB || (ldb % 4 == 0 && (uintptr_t)B % 16 == 0);
-    if (K % 4 == 0 && ok_a && ok_b)
-        hipLaunchKernelGGL((k_mm<TA, TB, EPI, NW, true>), grid, dim3(64 * NW), 0, (hipStream_t)stream, A, lda, B, ldb, C,
+    // both operands read along k (the input gradient): four values with one load
+    // where every row starts aligned
+    constexpr bool along_k = !TA && TB;
+    if (along_k && K % 4 == 0 && lda % 4 == 0 && ldb % 4 == 0 && (uintptr_t)A % 16 == 0 && (uintptr_t)B % 16 == 0)
+        hipLaunchKernelGGL((k_mm<TA, TB, EPI, NW, along_k>), grid, dim3(64 * NW), 0, (hipStream_t)stream, A, lda, B, ldb, C,
                            A_out, aux, bsum, M, N, K);
     else
         hipLaunchKernelGGL((k_mm<TA, TB, EPI, NW, false>), grid, dim3(64 * NW), 0, (hipStream_t)stream, A, lda, B, ldb, C,
