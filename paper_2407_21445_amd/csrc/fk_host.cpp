@@ -40,22 +40,15 @@ constexpr int kKrowLdsMaxWide = 160 * 1024;
 // streams besides the caller's for the class launches of fk_build_jk, and how
 // many of them a build uses.  Classes of a small molecule leave most of the
 // chip idle, so four streams in all (the hardware queues of a process) beat
-// three there; where the classes fill the chip a fourth only splits it further.
-// Times with four streams over those with three, one molecule, s to d shells (up
-// to 21 classes): 57 functions 0.85, 118 0.94, 251 0.94, 350 1.00, 384 0.95; 422
-// 1.02, 425 1.03, 450 1.04, 460 1.01, 525 1.01, 574 1.02, 625 1.02, 1000 1.02,
-// 1600 1.00.  With more launches there is more to overlap: f shells (55 classes)
-// 0.96 (324 functions), 0.99 (414), 0.96 (462), 1.01 (558), the twins of the
-// precision split and the J engine's buckets 0.88 to 1.00 from 61 to 725.  Batches
-// by their average: 0.94 to 0.98 with molecules of 61 to 190 functions, up to a
-// hundred of them.  Few classes (s and p only: six) gain or lose by chance, 0.86
-// (112 functions) to 1.28 (42), and keep three.
+// three: C20H42 7.65 ms per build against 8.05, organic batch of five 7.51
+// against 7.69, C6H14 1.10 against 1.14 (2.13 on one stream).  (H2O)64, whose
+// classes fill the chip, took 219.1 ms on four and 217.4 on three; with few
+// classes ((H2O)4 / STO-3G: six) the fourth stream's events cost more than it
+// gives (126 against 145 us).
 constexpr int kAuxStreams = 3;
-constexpr int64_t kFourStreams = 400, kFourStreamsMore = 724;  // functions, up to 21 launches and with more
-inline int aux_streams_used(size_t nclass, int64_t nmat, bool jeng)
+inline int aux_streams_used(size_t nclass, int64_t nmat)
 {
-    const int64_t n = nclass > 21 || jeng ? kFourStreamsMore : kFourStreams;
-    return nclass >= 12 && nmat <= n * n ? 3 : 2;
+    return nclass >= 12 && nmat * 8 <= (4 << 20) ? 3 : 2;
 }
 // Work tiles (fk_build_quartets): no tile takes more than kTileShare times the
 // serial work that one of two waves per SIMD would have if the class filled the
@@ -1910,7 +1903,7 @@ int build_jk_impl(fk_ctx *c, const double *D, double *J, double *K, unsigned fla
     // atomics; the other streams fork from and join the caller's.
     std::vector<hipStream_t> cls_st(c->qclasses.size(), st), jp_st(kJengNB * kJengNB, st);
     int nfork = 0;
-    const int nst = 1 + std::min((int)c->aux.size(), aux_streams_used(c->qclasses.size(), (int64_t)nn / c->nmol, jeng));
+    const int nst = 1 + std::min((int)c->aux.size(), aux_streams_used(c->qclasses.size(), (int64_t)nn / c->nmol));
     if (multi && nst > 1 && !c->timed && (want_rys || jeng) && c->qclasses.size() > 1) {
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         HIPCHK(c, hipStreamIsCapturing(st, &cs));
