@@ -40,11 +40,17 @@ constexpr int kKrowLdsMaxWide = 160 * 1024;
 // streams besides the caller's for the class launches of fk_build_jk, and how
 // many of them a build uses.  Classes of a small molecule leave most of the
 // chip idle, so four streams in all (the hardware queues of a process) beat
-// three: C20H42 7.65 ms per build against 8.05, organic batch of five 7.51
-// against 7.69, C6H14 1.10 against 1.14 (2.13 on one stream).  (H2O)64, whose
-// classes fill the chip, took 219.1 ms on four and 217.4 on three; with few
-// classes ((H2O)4 / STO-3G: six) the fourth stream's events cost more than it
-// gives (126 against 145 us).
+// three there; where the classes fill the chip a fourth only splits it further.
+// Times with four streams over those with three: up to 400 functions four win
+// (57 functions 0.85, 118 0.94, 251 0.94, 324 with f shells 0.96, 384 0.95, 350
+// 1.00; batches of molecules of 61 to 190 functions 0.94 to 0.98; precision split
+// and J engine 0.88 to 0.99).  From there to 724, where the density outgrows one
+// L2, either may: 0.96 to 1.05 over 30 builds ((H2O)18 cc-pVDZ-type 1.03, (H2O)30
+// 6-31G*-type 0.97, K of (H2O)21 with every primitive pair 0.99, f shells 0.96 and
+// 1.01, split and J engine 0.97 to 1.00), as the tails of the last classes happen
+// to fall; four are kept.  Beyond, three: 900 functions 1.01, 1000 1.02, 1200 1.02,
+// 1600 1.00.  Few classes (s and p only: six) gain or lose by chance, 0.86 (112
+// functions) to 1.28 (42), and keep three.
 constexpr int kAuxStreams = 3;
 inline int aux_streams_used(size_t nclass, int64_t nmat)
 {
