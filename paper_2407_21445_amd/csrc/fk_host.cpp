@@ -113,7 +113,6 @@ struct QuartetClass {
     int blocks_per_cu;
     double grid_frac = 1.0;   // share of the resident-workgroup grid launched
     int bra_block = 1, kets_per_tile = 64;  // the schedule in effect
-    int bra_slot;             // doubles per wave of staged bra primitive records
     int prec;                 // 0: FP64 launch, 1: FP32 launch of the precision split
     int engine = 0;           // 0: Rys quadrature, 1: HGP (classes with info.hgp only)
     int64_t task_off = 0, ntask = 0;  // block tasks (0: none)
@@ -668,7 +667,6 @@ int validate_lists(fk_ctx *c)
         }
     }
     if (c->blk_pos.size() != c->blk_bra.size()) return fail(c, FK_ERR_STATE, "internal: bra block arrays differ in size");
-    std::vector<int> blk_npp(c->blocks.size(), 0);  // the largest count of a block's bras
     for (size_t b = 0; b < c->blocks.size(); ++b) {
         const FkBraBlock &B = c->blocks[b];
         if (B.first < 0 || B.count < 1 || B.count > FK_MAX_BRA_BLOCK || (size_t)B.first + B.count > c->blk_bra.size())
@@ -678,7 +676,6 @@ int validate_lists(fk_ctx *c)
             if (p < 0 || p >= npair || q < 0 || q >= nl || c->ket_list_all[q] != p ||
                 c->pr_sa[p] != c->pr_sa[c->blk_bra[B.first]] || c->pr_cls[p] != c->pr_cls[c->blk_bra[B.first]])
                 return fail(c, FK_ERR_STATE, "internal: bra block %zu member %d is inconsistent", b, j);
-            blk_npp[b] = std::max(blk_npp[b], c->pr_npp[p]);
         }
     }
     for (const QuartetClass &qc : c->qclasses) {
@@ -692,8 +689,8 @@ int validate_lists(fk_ctx *c)
             if (B.count > qc.info.bra_block)
                 return fail(c, FK_ERR_STATE, "internal: tile %lld has %d bras, its class kernel takes %d",
                             (long long)t, B.count, qc.info.bra_block);
-            if (blk_npp[T.blk] * FK_NFLD > qc.bra_slot || c->pr_cls[c->blk_bra[B.first]] != qc.P)
-                return fail(c, FK_ERR_STATE, "internal: tile %lld has bras that do not fit its class", (long long)t);
+            if (c->pr_cls[c->blk_bra[B.first]] != qc.P)
+                return fail(c, FK_ERR_STATE, "internal: tile %lld has bras of another class", (long long)t);
             const FkGroup &G = c->groups[gid];
             if (T.ket_begin < G.begin || T.ket_begin + T.ket_count > G.begin + G.len)
                 return fail(c, FK_ERR_STATE, "internal: tile %lld leaves its group", (long long)t);
@@ -1241,9 +1238,6 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
             qc.grid_frac = sch.gf;
             qc.engine = (sch.eng != 0 && qc.info.hgp) ? sch.eng : 0;
             const int qpw = qc.info.wave_per_quartet == 0 ? 64 : (qc.info.wave_per_quartet == 3 ? 1 : 64 / ts);
-            int max_bra_npp = 1;
-            for (int p : LP) max_bra_npp = std::max(max_bra_npp, c->pr_npp[p]);
-            qc.bra_slot = max_bra_npp * FK_NFLD;
             qc.prec = 0;
             qc.nquartet = 0; qc.nprim = 0; qc.prim_slots = 0;
             std::vector<FkTile> tl;
@@ -1279,7 +1273,7 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
                 // waves per CU of a launch (0: the LDS does not fit); without a
                 // device the LDS bound alone decides
                 auto waves_cu = [&](int nw, int nbk, int nc) {
-                    const int lds = fk_kernels_jk_lds_bytes(P, Q, qc.bra_slot, nc, kind, nbk, nw);
+                    const int lds = fk_kernels_jk_lds_bytes(P, Q, nc, kind, nbk, nw);
                     if (lds < 0 || lds > (nw == 4 && kind == 0 ? kKrowLdsMax : kKrowLdsMaxWide)) return 0;
                     if (!dev) return nw;
                     return wgs_per_cu(lds, nw) * nw;
@@ -1379,9 +1373,10 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
             // A tile is one wave's serial work.  Where a class has few tiles, whole
             // blocks against deeply contracted kets would leave most of the chip
             // waiting for a handful of waves, so a tile's serial work is bounded
-            // (kTileShare, kMinTileFlops, kMaxTileFlops): first the block is cut into runs of bras (each
-            // a block of its own), then a single bra's tile over the kets'
-            // primitive pairs.  Large classes keep their whole blocks.
+            // (kTileShare, kMinTileFlops, kMaxTileFlops): first the block is cut into
+            // runs of bras (each a block of its own), then a single bra's tile over the
+            // kets' primitive pairs.  In large classes the share is large and
+            // kMaxTileFlops alone cuts the longest blocks.
             const double share = kTileShare * serial_total / (8.0 * (c->ncu > 0 ? c->ncu : 256));
             const double t_max = std::max(kMinTileFlops, std::min(kMaxTileFlops, share));
             // runs of the present block by (first, count): the block they were cut from, and their own
@@ -1512,8 +1507,8 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
                 }
                 q.blocks_per_cu = 1;
                 if (dev) {
-                    const int lds = fk_kernels_jk_lds_bytes(P, Q, q.bra_slot, q.ntask > 0 ? q.krow_ncol : 0,
-                                                            q.info.wave_per_quartet, q.krow_nbk, q.nw);
+                    const int lds = fk_kernels_jk_lds_bytes(P, Q, q.ntask > 0 ? q.krow_ncol : 0, q.info.wave_per_quartet,
+                                                            q.krow_nbk, q.nw);
                     if (const int nb = wgs_per_cu(lds, q.nw)) q.blocks_per_cu = nb;
                 }
                 if ((int)c->qclasses.size() >= FK_MAX_QCLASS)
@@ -1697,8 +1692,10 @@ int ensure_jeng(fk_ctx *c)
     c->jeng_toff.assign(kJengNB * kJengNB + 1, 0);
     c->jeng_work.assign(kJengNB * kJengNB, 0.0);
     for (int k = 0; k < kJengNB * kJengNB; ++k) {
-        // tiles of bounded serial work, as for the quartet classes: cut over the
-        // bra's primitive pairs (their J_p are separate sums), then the kets'
+        // tiles of bounded serial work by kTileShare and kMinTileFlops, as for the
+        // quartet classes (kMaxTileFlops changed them by 2 % or less and is left
+        // out): cut over the bra's primitive pairs (their J_p are separate sums),
+        // then the kets'
         const int lp = k / kJengNB, lq = k % kJengNB, nr = (lp + lq) / 2 + 1;
         const double f_prim = 60.0 + nr * (36.0 + 3.0 * (lp + lq) * 4 + 4.0 * nherm_host(lp + lq)) +
                               2.0 * nherm_host(lp) * nherm_host(lq);
@@ -2000,7 +1997,6 @@ int build_jk_impl(fk_ctx *c, const double *D, double *J, double *K, unsigned fla
         }
         a.rys_tab = c->d_rys.p + rys_staged_offset(qc.info.nroot);
         a.counters = b.cnt + 2 * i;
-        a.bra_slot = qc.bra_slot;
         a.prec = qc.prec;
         // a class with an FP32 twin splits its work by the per-quartet bound
         bool twin = false;
@@ -2599,7 +2595,6 @@ int fk_check_indices(fk_ctx *c)
             const int sa = c->sh_loc[gsa], sb = c->sh_loc[gsb];
             const long long ppo = c->pr_ppoff[bra], bnp = c->pr_npp[bra];
             if (ppo < 0 || ppo + bnp > nppr) return fail(c, FK_ERR_STATE, "tile %lld: bra records", (long long)t);
-            if (bnp * FK_NFLD > qc.bra_slot) return fail(c, FK_ERR_STATE, "tile %lld: LDS bra slot", (long long)t);
             const long long oa = c->sh_lbf[gsa], ob = c->sh_lbf[gsb];
             if (oa + NA > n || ob + NB > n || ncart(c->sh_l[gsa]) != NA || ncart(c->sh_l[gsb]) != NB)
                 return fail(c, FK_ERR_STATE, "tile %lld: bra shells do not match the class", (long long)t);

@@ -104,7 +104,6 @@ struct FkJKArgs {
     double tau;
     const double *rys_tab;   // staged Rys segment (table + Gauss-Hermite) of this class's root count
     unsigned long long *counters;  // [2]: contracted quartets, primitive quartets
-    int bra_slot;            // doubles per wave for the staged bra primitive records
     int prec;                // 0: FP64 kernel, 1: FP32 kernel of the precision split
     int engine;              // 0: Rys quadrature, 1: HGP with early contraction
     int kind;                // kernel kind of the launch: the class's own, or 1 for a lane class's team alternative
@@ -186,7 +185,7 @@ int fk_kernels_launch_debug(int P, int Q, const FkDebugArgs *args, void *stream)
 int fk_kernels_raise_lds(const void *kernel, int bytes);
 int fk_kernels_max_blocks(int P, int Q, int dyn_lds_bytes, int engine, int kind, int nw, int *blocks_per_cu);
 // dynamic LDS of a class launch; krow_ncol > 0 adds the block-task K rows
-int fk_kernels_jk_lds_bytes(int P, int Q, int bra_slot, int krow_ncol, int kind, int nbk, int nw);
+int fk_kernels_jk_lds_bytes(int P, int Q, int krow_ncol, int kind, int nbk, int nw);
 int fk_kernels_launch_prep(const double *D, const double *bf_scale, const FkMolArgs *m, double *Ds, double *Dsh,
                            void *stream);
 int fk_kernels_launch_finalize(const double *XJ, const double *XK, long long xcopy, int ncopy, const double *bf_scale,

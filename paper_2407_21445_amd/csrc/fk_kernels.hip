@@ -1788,16 +1788,14 @@ struct Disp {
         return (int)sizeof(double) * (rys_lds_size(fk::QClass<LA, LB, LC, LD>::NR) +
                                       FK_WAVES * (ncol > 0 ? T::RED_TASK : T::RED) + (ncol > 0 ? task_rows(ncol, nbk) : 0));
     }
-    static int lds_bytes(int bra_slot, int krow_ncol, int kind = KIND, int nbk = 0, int nw = FK_WAVES)
+    static int lds_bytes(int krow_ncol, int kind = KIND, int nbk = 0, int nw = FK_WAVES)
     {
         if constexpr (ALT) {
             if (kind == 1)
                 return team_lds<1>(krow_ncol, nbk);
         }
-        // the Rys segment, and per wave the team reductions (bra records are
-        // read from memory by scalar loads: bra_slot needs no LDS); block
-        // tasks add the block's K rows and X_J[a, b_j]
-        (void)bra_slot;
+        // the Rys segment, per wave the team reductions or stages, and with block
+        // tasks the block's K rows and X_J[a, b_j]
         using C = fk::QClass<LA, LB, LC, LD>;
         int extra = 0, rows = 0;
         if constexpr (KIND == 0)
@@ -1810,7 +1808,7 @@ struct Disp {
     {
         if constexpr (!BUILT) return -2;
         else {
-            const int lds = lds_bytes(a->bra_slot, a->ntask > 0 ? a->krow_ncol : 0, a->kind, a->krow_nbk, a->nw);
+            const int lds = lds_bytes(a->ntask > 0 ? a->krow_ncol : 0, a->kind, a->krow_nbk, a->nw);
             const bool low = a->prec == 1;
             const int eng = a->engine;
             if (a->kind != KIND && !(ALT && a->kind == 1)) return -2;
@@ -2015,12 +2013,12 @@ int host_q(int q, const int *o, const int *n, const double *ab, const double *pp
                       : host_q<P, Q + 1>(q, o, n, ab, pp, qs, nq, out, eng);
 }
 template <int P, int Q = 0>
-int lds_q(int q, int slot, int ncol, int kind, int nbk, int nw)
+int lds_q(int q, int ncol, int kind, int nbk, int nw)
 {
     if constexpr (Q > P) return -1;
     else
-        return q == Q ? Disp<P, Q>::lds_bytes(slot, ncol, kind, nbk, nw)
-                      : lds_q<P, Q + 1>(q, slot, ncol, kind, nbk, nw);
+        return q == Q ? Disp<P, Q>::lds_bytes(ncol, kind, nbk, nw)
+                      : lds_q<P, Q + 1>(q, ncol, kind, nbk, nw);
 }
 template <int P, int Q = 0>
 const void *kern_q(int q, int eng, int kind, int nw)
@@ -2292,9 +2290,9 @@ const void *FK_CAT(fk_kp, FK_ONLY_P, _kern)(int Q, int eng, int kind, int nw)
 {
     return kern_q<FK_ONLY_P>(Q, eng, kind, nw);
 }
-int FK_CAT(fk_kp, FK_ONLY_P, _lds)(int Q, int slot, int ncol, int kind, int nbk, int nw)
+int FK_CAT(fk_kp, FK_ONLY_P, _lds)(int Q, int ncol, int kind, int nbk, int nw)
 {
-    return lds_q<FK_ONLY_P>(Q, slot, ncol, kind, nbk, nw);
+    return lds_q<FK_ONLY_P>(Q, ncol, kind, nbk, nw);
 }
 }
 #else
@@ -2442,7 +2440,7 @@ __global__ void k_finalize(const double *__restrict XJ, const double *__restrict
     int fk_kp##P##_host(int, const int *, const int *, const double *, const double *, const int *, int,    \
                         double *, int);                                                                      \
     const void *fk_kp##P##_kern(int, int, int, int);                                                         \
-    int fk_kp##P##_lds(int, int, int, int, int, int);
+    int fk_kp##P##_lds(int, int, int, int, int);
 extern "C" {
 FK_DECL_P(0) FK_DECL_P(1) FK_DECL_P(2) FK_DECL_P(3) FK_DECL_P(4)
 FK_DECL_P(5) FK_DECL_P(6) FK_DECL_P(7) FK_DECL_P(8) FK_DECL_P(9)
@@ -2488,9 +2486,9 @@ static const void *kern_of(int P, int Q, int engine, int kind, int nw)
     return nullptr;
 }
 
-int fk_kernels_jk_lds_bytes(int P, int Q, int bra_slot, int krow_ncol, int kind, int nbk, int nw)
+int fk_kernels_jk_lds_bytes(int P, int Q, int krow_ncol, int kind, int nbk, int nw)
 {
-    FK_SWITCH_P(P, lds(Q, bra_slot, krow_ncol, kind, nbk, nw))
+    FK_SWITCH_P(P, lds(Q, krow_ncol, kind, nbk, nw))
     return -1;
 }
 

@@ -123,7 +123,6 @@ static int check_validation()
     BREAK(c->pr_G[p], std::nan(""));
     BREAK(c->pr_ppoff[p], -1);
     QuartetClass &q = const_cast<QuartetClass &>(*task);
-    BREAK(q.bra_slot, 1);
     BREAK(q.krow_ncol, 1);
     BREAK(q.krow_nbk, 0);
     BREAK(c->tasks[q.task_off].y, c->tasks[q.task_off].y + 1);
@@ -177,7 +176,7 @@ static int check_lds()
     const int P = pair_class(1, 1);
     auto probe = [&](int ncol) {
         int nb = 0;
-        const int lds = fk_kernels_jk_lds_bytes(P, P, 0, ncol, 1, 8, 4);
+        const int lds = fk_kernels_jk_lds_bytes(P, P, ncol, 1, 8, 4);
         if (lds <= 65536 || lds > 160 * 1024) std::printf("%d columns take %d bytes\n", ncol, lds);
         return fk_kernels_max_blocks(P, P, lds, 0, 1, 4, &nb) == 0 && nb == 1 && lds > 65536 && lds <= 160 * 1024;
     };
