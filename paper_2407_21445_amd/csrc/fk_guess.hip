@@ -95,9 +95,7 @@ __global__ void __launch_bounds__(64 * NW) k_mm(const float *__restrict A, int l
     __shared__ float bpart[NW][2][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int i = lane & 15, g = lane >> 4;
-    const long long row0 = ((long long)blockIdx.z * gridDim.y + blockIdx.y) * 16;
-    if (row0 >= M) return;
-    const int m0 = (int)row0, n0 = blockIdx.x * 32;
+    const int m0 = blockIdx.y * 16, n0 = blockIdx.x * 32;
     f4 acc[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
     float bs[2] = {0.0f, 0.0f};
     auto loadA = [&](int k0) {
@@ -157,7 +155,7 @@ __global__ void __launch_bounds__(64 * NW) k_mm(const float *__restrict A, int l
             }
             C[o] = c;
         }
-        if (EPI == EPI_SUM && m0 == 0 && l < 16) {
+        if (EPI == EPI_SUM && blockIdx.y == 0 && l < 16) {
             float t = 0.0f;
             for (int w = 0; w < NW; ++w)
                 t += (bpart[w][h][l] + bpart[w][h][l + 16]) + (bpart[w][h][l + 32] + bpart[w][h][l + 48]);
@@ -182,16 +180,14 @@ __global__ void __launch_bounds__(256) k_layer_tall(const float *__restrict X, c
 {
     __shared__ float As[TM * SA], Bs[TK * SB];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = lane & 15, g = lane >> 4;
-    const long long row0 = ((long long)blockIdx.z * gridDim.y + blockIdx.y) * TM;
-    if (row0 >= M) return;
-    const int n0 = blockIdx.x * TM;
+    const int row0 = blockIdx.y * TM, n0 = blockIdx.x * TM;
     // this thread's elements of a slab: X at rows tx >> 4 + 16 r, W at k tx >> 6 + 4 r
     const int am = threadIdx.x >> 4, ak = threadIdx.x & 15, bk = threadIdx.x >> 6, bn = threadIdx.x & 63;
     float va[4], vb[4];
     auto load = [&](int k0) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const long long m = row0 + am + 16 * r;
+            const int m = row0 + am + 16 * r;
             const int ka = k0 + ak, kb = k0 + bk + 4 * r;
             va[r] = m < M && ka < K ? X[(size_t)m * K + ka] : 0.0f;
             vb[r] = kb < K && n0 + bn < N ? W[(size_t)kb * N + n0 + bn] : 0.0f;
@@ -222,7 +218,7 @@ __global__ void __launch_bounds__(256) k_layer_tall(const float *__restrict X, c
         if (n >= N) continue;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const long long m = row0 + 16 * wave + 4 * g + r;
+            const int m = row0 + 16 * wave + 4 * g + r;
             if (m >= M) continue;
             const float v = acc[c][r] + bias[n];
             out[(size_t)m * N + n] = v;
@@ -345,19 +341,17 @@ int ok() { return hipGetLastError() == hipSuccess ? 0 : -3; }
 
 unsigned nblk(long long n) { return (unsigned)((n + 255) / 256); }
 
-// tiles of rows over the grid's y and z: y alone ends at 65535, a million rows
-dim3 row_grid(int columns, long long rows)
-{
-    const unsigned gy = (unsigned)std::min<long long>(rows, 32768);
-    return dim3(columns, gy, (unsigned)((rows + gy - 1) / gy));
-}
+// Rows per launch of the products whose rows are a call's: at 16 to a tile half
+// of what a grid's y may count (65535).  Rows on z as well would cost a call of
+// few rows 0.3 us per kernel, which then has to find out whether its tile exists.
+constexpr long long MAX_ROWS = 1 << 19;
 
 template <int TA, int TB, int EPI, int NW>
 int mm(const float *A, int lda, const float *B, int ldb, float *C, float *A_out, const float *aux, float *bsum, int M,
        int N, int K, void *stream)
 {
     if (M <= 0 || N <= 0) return 0;
-    const dim3 grid = row_grid((N + 31) / 32, ((long long)M + 15) / 16);
+    const dim3 grid((N + 31) / 32, (M + 15) / 16);
     // both operands read along k (the input gradient): four values with one load
     // where every row starts aligned
     constexpr bool along_k = !TA && TB;
@@ -382,19 +376,27 @@ int fk_guess_layer(const float *X, const float *W, const float *bias, float *out
     // waves fill more of the chip.  256 x 256 layer, waves and slabs: 1000 rows (64 tiles)
     // 14.0 and 15.6 us, 1500 (96) 14.6 and 15.7, 2048 (128) 16.8 and 15.9, 4096 27.3 and
     // 16.5; 1024 x 1024: 100 rows (32) 40.6 and 47.4, 500 (128) 51.0 and 47.0.
-    const long long rt = ((long long)M + TM - 1) / TM, ct = (N + TM - 1) / TM;
-    if (M > 0 && rt * ct >= 128) {
-        hipLaunchKernelGGL(k_layer_tall, row_grid((int)ct, rt), dim3(256), 0, (hipStream_t)stream, X, W, bias, out, act, M, N,
-                           K);
-        return ok();
+    const int ct = (N + TM - 1) / TM;
+    for (long long r = 0; r < M; r += MAX_ROWS) {
+        const int rows = (int)std::min(MAX_ROWS, M - r), rt = (rows + TM - 1) / TM;
+        const float *x = X + r * K;
+        float *y = out + r * N, *a = act ? act + r * N : nullptr;
+        if (rt * ct >= 128)
+            hipLaunchKernelGGL(k_layer_tall, dim3(ct, rt), dim3(256), 0, (hipStream_t)stream, x, W, bias, y, a, rows, N, K);
+        else if (mm<0, 0, EPI_BIAS, 1>(x, K, W, N, y, a, bias, nullptr, rows, N, K, stream))
+            return -3;
     }
-    return mm<0, 0, EPI_BIAS, 1>(X, K, W, N, out, act, bias, nullptr, M, N, K, stream);
+    return ok();
 }
 
 // out[M][N] = (G[M][K] W^T) SiLU'(Z), W stored [N][K]
 int fk_guess_layer_back(const float *G, const float *W, const float *Z, float *out, int M, int N, int K, void *stream)
 {
-    return mm<0, 1, EPI_SILU, 4>(G, K, W, K, out, nullptr, Z, nullptr, M, N, K, stream);
+    for (long long r = 0; r < M; r += MAX_ROWS)
+        if (mm<0, 1, EPI_SILU, 4>(G + r * K, K, W, K, out + r * N, nullptr, Z + r * N, nullptr,
+                                  (int)std::min(MAX_ROWS, M - r), N, K, stream))
+            return -3;
+    return 0;
 }
 
 // gW[M][N] = X^T G and gb[N] = column sums of G, X stored [rows][M], G [rows][N]
