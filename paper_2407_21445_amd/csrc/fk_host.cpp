@@ -1447,6 +1447,8 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
             qc.ntask = 0;
             qc.tile_off = (int64_t)c->tiles.size();
             qc.ntile = (int64_t)tl.size();
+            c->tiles.resize(c->tiles.size() + tl.size());
+            FkTile *out = c->tiles.data() + qc.tile_off;
             if (qc.krow_ncol > 0) {
                 // the tiles block by block, by cost within a block
                 std::vector<uint64_t> bkey(tl.size());
@@ -1486,14 +1488,16 @@ int fk_build_quartets(fk_ctx *c, const fk_screen_opts *o)
                 std::vector<int> ord_c;
                 order_descending(ccost, ord_c);
                 qc.task_off = (int64_t)c->tasks.size();
+                int first = 0;
                 for (int k : ord_c) {
-                    const int first = (int)((int64_t)c->tiles.size() - qc.tile_off);
-                    for (size_t x = chunks[k].begin; x < chunks[k].end; x += chunks[k].step) c->tiles.push_back(tl[tord[x]]);
-                    c->tasks.push_back(int2{first, (int)((int64_t)c->tiles.size() - qc.tile_off) - first});
+                    int n = 0;
+                    for (size_t x = chunks[k].begin; x < chunks[k].end; x += chunks[k].step) out[first + n++] = tl[tord[x]];
+                    c->tasks.push_back(int2{first, n});
+                    first += n;
                 }
                 qc.ntask = (int64_t)chunks.size();
             } else {
-                for (int t : tord) c->tiles.push_back(tl[t]);
+                for (size_t t = 0; t < tl.size(); ++t) out[t] = tl[tord[t]];
             }
             c->flops_schwarz += qc.nprim * qc.flops_prim() + qc.nquartet * qc.flops_quartet();
             c->nq_schwarz += qc.nquartet;
